@@ -27,6 +27,7 @@
 // upsampled and skip inputs directly instead of a materialised concatenation.
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <cmath>
 #include <cstdarg>
 #include <cstdint>
@@ -34,6 +35,7 @@
 #include <cstring>
 
 #include "../../include/isis_mg.h"
+#include "device.hpp"
 
 namespace {
 
@@ -51,6 +53,7 @@ using bf16_t = uint16_t;
 typedef short s4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf8v __attribute__((ext_vector_type(8)));
 typedef float f4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u4 __attribute__((ext_vector_type(4)));  // (HIP's uint4 arrays go to scratch)
 
 constexpr int kThreads = 256;
 constexpr int kMaxGrid = 65536;
@@ -444,31 +447,316 @@ __global__ __launch_bounds__(kThreads) void k_conv3_dw(const bf16_t* __restrict_
     }
 }
 
-// out[e] = sum_c part[c][e] in chunk order (deterministic), optionally added.
+// The weight gradient on sides >= 16, staged in LDS.  A workgroup owns one
+// 16 x 16 (output, input) channel tile and a region of the grid: TY rows and Z
+// columns, streamed along x over xc planes.  Per plane it holds the 16 input
+// channels of x (rows y0-1 .. y0+TY of the NDI planes its taps read) and the
+// 16 output channels of dy (one voxel of z halo) as they lie in memory, 32
+// bytes per voxel; the transposing LDS read ds_read_b64_tr_b16 turns four
+// consecutive voxels into the K-contiguous operands of the 16x16x32 MFMA, so
+// neither a transposed copy nor an alignment of the z shift is needed.  The
+// z shift dk is taken on dy (three A operands per 32-voxel window), di and
+// dj on x (one B operand per staged row), and rows are walked in order with
+// the B operands of three rows kept in registers: 3 A + 3 NDI B operands per
+// 9 NDI MFMAs, where the per-tap kernel loaded 8 + 8 two-byte values from
+// memory per MFMA.  The four waves take different windows (K) of the region
+// and are summed in LDS in a fixed order; regions are summed by k_sum_chunks.
+// Bound: LDS reads and the MFMA issue about equally (NDI = 3); x and dy are
+// read 1.5 and (per channel tile) 1.03 times.
+//   48 -> 16 at 128^3: 5.0 -> 0.11 ms (0.79 PFLOP/s); 16 -> 16: 3.9 -> 0.037 ms;
+//   64 -> 64 at 32^3: 0.45 -> 0.025 ms, at 16^3 0.44 -> 0.020 ms.
+// NDI = 3: all 27 taps in one workgroup (sides >= 64); NDI = 1: one x offset
+// per workgroup (blockIdx), for the small grids whose few regions would leave
+// most of the device idle.
+template <int Z_, int TY_, int NDI_>
+struct DwTile {
+    static constexpr int Z = Z_, TY = TY_, NDI = NDI_;
+    static constexpr int XR = TY + 2, XPL = XR * Z * 16;      // staged x plane, elements
+    static constexpr int DZ = Z + 2, DPL = TY * DZ * 16;      // staged dy plane
+    static constexpr int XU = XPL / 8, DU = DPL / 8;          // 16-byte units
+    static constexpr int XPT = (XU + kThreads - 1) / kThreads, DPT = (DU + kThreads - 1) / kThreads;
+    static constexpr int RS = Z >= 32 ? 1 : 32 / Z;           // rows per 32-voxel window
+    static constexpr int ZW = Z >= 32 ? Z / 32 : 1;           // windows per row
+    static constexpr int RW = TY / (4 / ZW);                  // rows per wave
+    static constexpr int LDS = (NDI * XPL + DPL) * 2;
+    static_assert(4 % ZW == 0 && TY % (4 / ZW) == 0 && RW % RS == 0, "four waves share the tile");
+    static_assert(LDS >= 9 * NDI * 256 * 4, "the reduction reuses the staging buffers");
+};
+typedef __attribute__((address_space(3))) s4 lds_s4;
+
+template <class G>
+__global__ __launch_bounds__(kThreads, 2) void k_conv3_dw_tiled(const bf16_t* __restrict__ x, int n,
+                                                                int cin,
+                                                                const bf16_t* __restrict__ dy,
+                                                                int cout, int xc,
+                                                                float* __restrict__ part)
+{
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    bf16_t* xs = reinterpret_cast<bf16_t*>(smem_raw);  // NDI planes of x
+    bf16_t* ds = xs + G::NDI * G::XPL;                 // one plane of dy
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int m = lane & 15, g = lane >> 4;
+    const int msk = n - 1;
+    const int tn = cin >> 4, tiles = tn * (cout >> 4);
+    const int nb = gridDim.x;
+    int b = blockIdx.x;
+    if ((nb & 7) == 0) b = (b & 7) * (nb >> 3) + (b >> 3);  // a region's tiles share an XCD's L2
+    const int tile = b % tiles;
+    b /= tiles;
+    int d0 = -1;  // x offset of the first staged plane
+    if constexpr (G::NDI == 1) {
+        d0 = b % 3 - 1;
+        b /= 3;
+    }
+    const int reg = b;
+    const int nzt = n / G::Z, nyt = n / G::TY;
+    const int zt = b % nzt, yt = (b / nzt) % nyt, xt = b / (nzt * nyt);
+    const int x0 = xt * xc, y0 = yt * G::TY, z0 = zt * G::Z;
+    const int ci0 = (tile % tn) * 16, co0 = (tile / tn) * 16;
+    const size_t xplane = (size_t)n * n * cin, dplane = (size_t)n * n * cout;
+
+    unsigned xo[G::XPT], dof[G::DPT];  // element offsets in a plane (tail clamped)
+#pragma unroll
+    for (int q = 0; q < G::XPT; ++q) {
+        const int e = min(tid + q * kThreads, G::XU - 1);
+        const int v = e >> 1, r = v / G::Z, z = v % G::Z;
+        xo[q] = (unsigned)((((y0 - 1 + r) & msk) * n + z0 + z) * cin + ci0 + 8 * (e & 1));
+    }
+#pragma unroll
+    for (int q = 0; q < G::DPT; ++q) {
+        const int e = min(tid + q * kThreads, G::DU - 1);
+        const int v = e >> 1, r = v / G::DZ, z = v % G::DZ;
+        dof[q] = (unsigned)(((y0 + r) * n + ((z0 - 1 + z) & msk)) * cout + co0 + 8 * (e & 1));
+    }
+    u4 xr[G::XPT], dr[G::DPT];
+    auto load_x = [&](int xp) __attribute__((always_inline)) {
+        const bf16_t* p = x + (size_t)(xp & msk) * xplane;
+#pragma unroll
+        for (int q = 0; q < G::XPT; ++q) xr[q] = *reinterpret_cast<const u4*>(p + xo[q]);
+    };
+    auto load_d = [&](int xp) __attribute__((always_inline)) {
+        const bf16_t* p = dy + (size_t)(xp & msk) * dplane;
+#pragma unroll
+        for (int q = 0; q < G::DPT; ++q) dr[q] = *reinterpret_cast<const u4*>(p + dof[q]);
+    };
+    auto put_x = [&](int slot) __attribute__((always_inline)) {
+        u4* d = reinterpret_cast<u4*>(xs + slot * G::XPL);
+#pragma unroll
+        for (int q = 0; q < G::XPT; ++q) {
+            const int e = tid + q * kThreads;
+            if ((q + 1) * kThreads <= G::XU || e < G::XU) d[e] = xr[q];
+        }
+    };
+    auto put_d = [&]() __attribute__((always_inline)) {
+        u4* d = reinterpret_cast<u4*>(ds);
+#pragma unroll
+        for (int q = 0; q < G::DPT; ++q) {
+            const int e = tid + q * kThreads;
+            if ((q + 1) * kThreads <= G::DU || e < G::DU) d[e] = dr[q];
+        }
+    };
+
+    f4 acc[G::NDI][3][3];
+#pragma unroll
+    for (int a = 0; a < G::NDI; ++a)
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+#pragma unroll
+            for (int k = 0; k < 3; ++k) acc[a][j][k] = f4{0.f, 0.f, 0.f, 0.f};
+
+    // this wave's window column and first row; this lane's address in a
+    // transposing read: voxel 4g + m/4 of 16, channels 4 (m % 4) ..
+    const int zw = (wv % G::ZW) * 32, r0 = (wv / G::ZW) * G::RW;
+    const int lo = (4 * g + (m >> 2)) * 16 + 4 * (m & 3);
+    // operand of the 32-voxel window whose first 16 voxels start at p and
+    // the others `second` elements further
+    auto operand = [&](const bf16_t* p, int second) __attribute__((always_inline)) {
+        const s4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4*)(p + lo));
+        const s4 c = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4*)(p + second + lo));
+        return __builtin_bit_cast(bf8v, __builtin_shufflevector(a, c, 0, 1, 2, 3, 4, 5, 6, 7));
+    };
+    constexpr int XSEC = G::RS == 1 ? 16 * 16 : G::Z * 16;   // second half: 16 voxels on, or the next row
+    constexpr int DSEC = G::RS == 1 ? 16 * 16 : G::DZ * 16;
+
+    load_x(x0 + d0);
+    put_x(0);
+    if constexpr (G::NDI == 3) {
+        load_x(x0);
+        put_x(1);
+        load_x(x0 + 1);
+    }
+    load_d(x0);
+    int head = 0;  // slot of plane xp - 1 (NDI = 3)
+    for (int xp = x0; xp < x0 + xc; ++xp) {
+        if constexpr (G::NDI == 3) put_x(head == 0 ? 2 : head - 1);
+        else if (xp > x0) put_x(0);
+        put_d();
+        __syncthreads();
+        // the next plane's values are in flight during this plane's MFMAs
+        // (past the region's end they are loaded and dropped: branch-free)
+        load_x(G::NDI == 3 ? xp + 2 : xp + 1 + d0);
+        load_d(xp + 1);
+        const bf16_t* xp_[G::NDI];
+#pragma unroll
+        for (int a = 0; a < G::NDI; ++a) {
+            const int s = head + a;
+            xp_[a] = xs + (G::NDI == 3 && s >= 3 ? s - 3 : s) * G::XPL + zw * 16;
+        }
+        const bf16_t* dp = ds + zw * 16;
+        bf8v bq[3][G::NDI];  // rows r - 1, r, r + 1 (RS = 1: slot = row mod 3)
+        if constexpr (G::RS == 1) {
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int a = 0; a < G::NDI; ++a) bq[j][a] = operand(xp_[a] + (r0 + j) * G::Z * 16, XSEC);
+        }
+#pragma unroll
+        for (int r = 0; r < G::RW; r += G::RS) {
+            bf8v aq[3];
+#pragma unroll
+            for (int k = 0; k < 3; ++k)  // x at z, dy at z - dk (dk = k - 1; ds starts at z0 - 1)
+                aq[k] = operand(dp + ((r0 + r) * G::DZ + 2 - k) * 16, DSEC);
+            if constexpr (G::RS == 1) {
+#pragma unroll
+                for (int a = 0; a < G::NDI; ++a)
+                    bq[(r + 2) % 3][a] = operand(xp_[a] + (r0 + r + 2) * G::Z * 16, XSEC);
+            } else {
+#pragma unroll
+                for (int j = 0; j < 3; ++j)
+#pragma unroll
+                    for (int a = 0; a < G::NDI; ++a)
+                        bq[j][a] = operand(xp_[a] + (r0 + r + j) * G::Z * 16, XSEC);
+            }
+#pragma unroll
+            for (int j = 0; j < 3; ++j)
+#pragma unroll
+                for (int a = 0; a < G::NDI; ++a)
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) {
+                        const bf8v bb = G::RS == 1 ? bq[(r + j) % 3][a] : bq[j][a];
+                        acc[a][j][k] =
+                            __builtin_amdgcn_mfma_f32_16x16x32_bf16(aq[k], bb, acc[a][j][k], 0, 0, 0);
+                    }
+        }
+        __syncthreads();  // the oldest plane's slot and dy are refilled next
+        if constexpr (G::NDI == 3) head = head == 2 ? 0 : head + 1;
+    }
+    // waves 0 .. 3 summed in order, then D[row = 4g + r][col = m] of each tap
+    float* red = reinterpret_cast<float*>(smem_raw);
+    for (int w = 0; w < 4; ++w) {
+        if (wv == w) {
+#pragma unroll
+            for (int a = 0; a < G::NDI; ++a)
+#pragma unroll
+                for (int j = 0; j < 3; ++j)
+#pragma unroll
+                    for (int k = 0; k < 3; ++k)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            float* q = red + ((a * 3 + j) * 3 + k) * 256 + (4 * g + r) * 16 + m;
+                            *q = w == 0 ? acc[a][j][k][r] : *q + acc[a][j][k][r];
+                        }
+        }
+        __syncthreads();
+    }
+    float* out = part + ((size_t)reg * 27 + 9 * (d0 + 1)) * cout * cin;
+    for (int e = tid; e < 9 * G::NDI * 256; e += kThreads) {
+        const int t = e >> 8, co = (e >> 4) & 15, ci = e & 15;
+        out[((size_t)t * cout + co0 + co) * cin + ci0 + ci] = red[e];
+    }
+}
+
+// out[e] = sum_c part[c][e] (deterministic): a workgroup sums 16 elements, 16
+// threads per element each taking every 16th chunk in order, then those 16
+// sums in order.  (One thread per element walked all chunks: 512 dependent
+// loads, 0.14 ms for 48 -> 16 weights at 128^3; now 0.016 ms.)
 __global__ __launch_bounds__(kThreads) void k_sum_chunks(const float* __restrict__ part,
                                                          int nchunk, long elems,
                                                          float* __restrict__ out)
 {
-    for (long e = (long)blockIdx.x * blockDim.x + threadIdx.x; e < elems;
-         e += (long)gridDim.x * blockDim.x) {
-        float s = 0.f;
-        for (int c = 0; c < nchunk; ++c) s += part[(long)c * elems + e];
+    __shared__ float red[kThreads];
+    const int tid = threadIdx.x, l = tid >> 4;
+    const long e = (long)blockIdx.x * 16 + (tid & 15);
+    float s = 0.f;
+    if (e < elems) {
+        int c = l;
+        for (; c + 48 < nchunk; c += 64) {  // four loads in flight
+            const float v0 = part[(long)c * elems + e], v1 = part[(long)(c + 16) * elems + e];
+            const float v2 = part[(long)(c + 32) * elems + e], v3 = part[(long)(c + 48) * elems + e];
+            s += v0;
+            s += v1;
+            s += v2;
+            s += v3;
+        }
+        for (; c < nchunk; c += 16) s += part[(long)c * elems + e];
+    }
+    red[tid] = s;
+    __syncthreads();
+    if (tid < 16 && e < elems) {
+        for (int k = 1; k < 16; ++k) s += red[k * 16 + tid];
         out[e] = s;
     }
 }
 
-// Per-channel sums of a [nvox][C] bf16 tensor: partial sums per block of
-// voxels (fixed chunking), reduced by k_sum_chunks.
-__global__ __launch_bounds__(kThreads) void k_chan_sum(const bf16_t* __restrict__ a, long nvox,
-                                                       int C, int chunk, float* __restrict__ part)
+// Per-channel sums of a [nvox][C] bf16 tensor (C a power of two, 16 .. 256):
+// partial sums per chunk of voxels, reduced by k_sum_chunks.  A thread sums
+// the 8 channels of one 16-byte vector over every (2048 / C)th voxel, so a
+// workgroup reads contiguous memory (one thread per channel walked the voxels
+// two bytes at a time: 0.55 ms for 16 channels at 128^3, now 0.015 ms).
+// MASK: g = g * (o > 0) first (the ReLU gradient, exact in bf16), written back
+// in the same pass.
+constexpr int kSumVecs = 8 * kThreads;  // 16-byte vectors per workgroup
+template <bool MASK>
+__global__ __launch_bounds__(kThreads) void k_chan_sum(bf16_t* __restrict__ a,
+                                                       const bf16_t* __restrict__ o, long nvox,
+                                                       int C, float* __restrict__ part)
 {
-    // block b handles voxels [b*chunk, (b+1)*chunk); thread t sums channel t
-    const long v0 = (long)blockIdx.x * chunk;
-    for (int c = threadIdx.x; c < C; c += blockDim.x) {
-        float s = 0.f;
-        for (long v = v0; v < v0 + chunk && v < nvox; ++v) s += bf2f(a[v * C + c]);
-        part[(long)blockIdx.x * C + c] = s;
+    __shared__ float red[4 * kThreads];
+    const int tid = threadIdx.x;
+    const int U = C >> 3;  // vectors per voxel, a divisor of 256: one channel group per thread
+    const long u0 = (long)blockIdx.x * kSumVecs + tid, end = nvox * U;
+    u4* av = reinterpret_cast<u4*>(a);
+    const u4* ov = reinterpret_cast<const u4*>(o);
+    float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    u4 v[8], p[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        const long u = min(u0 + k * kThreads, end - 1);  // (clamped: branch-free loads)
+        v[k] = av[u];
+        if constexpr (MASK) p[k] = ov[u];
     }
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        const long u = u0 + k * kThreads;
+        if (u >= end) break;
+        if constexpr (MASK) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if (!(bf2f((bf16_t)(p[k][i] & 0xffffu)) > 0.f)) v[k][i] &= 0xffff0000u;
+                if (!(bf2f((bf16_t)(p[k][i] >> 16)) > 0.f)) v[k][i] &= 0xffffu;
+            }
+            av[u] = v[k];
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            s[2 * i] += bf2f((bf16_t)(v[k][i] & 0xffffu));
+            s[2 * i + 1] += bf2f((bf16_t)(v[k][i] >> 16));
+        }
+    }
+    // lanes U apart hold the same channels: summed across the wave, then the
+    // four waves in order
+    for (int d = 32; d >= U; d >>= 1) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) s[i] += __shfl_xor(s[i], d, 64);
+    }
+    const int lane = tid & 63, wv = tid >> 6;
+    if (lane < U) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) red[wv * C + lane * 8 + i] = s[i];
+    }
+    __syncthreads();
+    if (tid < C)
+        part[(long)blockIdx.x * C + tid] = ((red[tid] + red[C + tid]) + red[2 * C + tid]) + red[3 * C + tid];
 }
 
 // Weights for the data gradient: wt[t'][ci][co] = w[26 - t][co][ci] (bf16).
@@ -606,14 +894,6 @@ __global__ void k_skip_grad(const bf16_t* __restrict__ dcat, int nf, int cs, int
         const float pb = bf2f(f2bf(bf2f(dlo[V * S + c]) * 0.125f));
         out[e] = f2bf(bf2f(dcat[v * cs + C + c]) + pb);
     }
-}
-
-// g = g * (o > 0) (ReLU gradient; exact in bf16).
-__global__ void k_relu_mask(bf16_t* __restrict__ g, const bf16_t* __restrict__ o, long total)
-{
-    for (long e = (long)blockIdx.x * blockDim.x + threadIdx.x; e < total;
-         e += (long)gridDim.x * blockDim.x)
-        if (!(bf2f(o[e]) > 0.f)) g[e] = 0;
 }
 
 // Input channels: log(eta)/2, a, phi_cold, zeros (16 channels).
@@ -802,45 +1082,77 @@ size_t dw_part_floats(long nvox, int cin, int cout)
     return (size_t)(nvox / dw_chunk(nvox)) * 27 * cin * cout;
 }
 
+// dw = sum over the nchunk partial sums in part.
+int launch_sum_chunks(const float* part, int nchunk, long elems, float* out, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_sum_chunks, dim3((unsigned)((elems + 15) / 16)), dim3(kThreads), 0, s, part,
+                       nchunk, elems, out);
+    ULAUNCH("k_sum_chunks");
+    return ISIS_OK;
+}
+
+// One k_conv3_dw_tiled launch: regions of xc planes; one region writes dw itself.
+template <class G>
+int launch_dw_tiled(const bf16_t* x, int n, int cin, const bf16_t* dy, int cout, int xc,
+                    float* part, float* dw, hipStream_t s)
+{
+    static std::atomic<unsigned> lds_done{0};  // per instantiation: devices set up
+    auto kern = k_conv3_dw_tiled<G>;
+    UCHECK(isis::ensure_dynamic_lds((const void*)kern, G::LDS, lds_done));
+    const int regions = (n / G::Z) * (n / G::TY) * (n / xc);
+    const int blocks = regions * (cin / 16) * (cout / 16) * (3 / G::NDI);
+    hipLaunchKernelGGL(kern, dim3(blocks), dim3(kThreads), G::LDS, s, x, n, cin, dy, cout, xc,
+                       regions == 1 ? dw : part);
+    ULAUNCH("k_conv3_dw_tiled");
+    return regions == 1 ? (int)ISIS_OK : launch_sum_chunks(part, regions, 27L * cin * cout, dw, s);
+}
+
 int launch_conv_dw(const bf16_t* x, int n, int cin, const bf16_t* dy, int cout, float* part,
                    float* dw, hipStream_t s)
 {
     const long nvox = (long)n * n * n;
-    const int chunk = dw_chunk(nvox);
-    const int nchunk = (int)(nvox / chunk);
-    bool ok = false;
-#define DW_CASE(CI, CO)                                                                     \
-    if (cin == CI && cout == CO) {                                                          \
-        hipLaunchKernelGGL((k_conv3_dw<CI, CO>), dim3(27 * nchunk), dim3(kThreads), 0, s, x, \
-                           n, dy, chunk, part);                                             \
-        ok = true;                                                                          \
-    }
-    DW_CASE(16, 16) DW_CASE(16, 32) DW_CASE(32, 32) DW_CASE(32, 64) DW_CASE(64, 64)
-    DW_CASE(128, 64) DW_CASE(96, 32) DW_CASE(48, 16)
-#undef DW_CASE
-    if (!ok) {
+    bool known = false;  // the network's layer shapes
+    for (const ConvSpec& c : kConvs) known = known || (c.cin == cin && c.cout == cout);
+    if (!known) {
         uerr("no weight-gradient kernel for %d -> %d channels", cin, cout);
         return ISIS_ERR_UNSUPPORTED;
     }
+    // Regions per launch stay within the caller's n^3 / 4096 partial sums.
+    // Planes per region: 8 up to 128^3 (512 regions there, two workgroups per
+    // CU for one channel tile), 16 at 256^3, 32 above (fewer partial sums).
+    if (n >= 64) {
+        const int xc = n <= 128 ? 8 : n == 256 ? 16 : 32;
+        return launch_dw_tiled<DwTile<64, 8, 3>>(x, n, cin, dy, cout, xc, part, dw, s);
+    }
+    if (n == 32) return launch_dw_tiled<DwTile<32, 8, 1>>(x, n, cin, dy, cout, 16, part, dw, s);
+    if (n == 16) return launch_dw_tiled<DwTile<16, 16, 1>>(x, n, cin, dy, cout, 16, part, dw, s);
+    // sides below 16: no 16-voxel windows along z
+    const int chunk = dw_chunk(nvox);
+    const int nchunk = (int)(nvox / chunk);
+#define DW_CASE(CI, CO)                                                                     \
+    if (cin == CI && cout == CO)                                                            \
+        hipLaunchKernelGGL((k_conv3_dw<CI, CO>), dim3(27 * nchunk), dim3(kThreads), 0, s, x, \
+                           n, dy, chunk, part);
+    DW_CASE(16, 16) DW_CASE(16, 32) DW_CASE(32, 32) DW_CASE(32, 64) DW_CASE(64, 64)
+    DW_CASE(128, 64) DW_CASE(96, 32) DW_CASE(48, 16)
+#undef DW_CASE
     ULAUNCH("k_conv3_dw");
-    const long elems = 27L * cin * cout;
-    hipLaunchKernelGGL(k_sum_chunks, dim3(grid_of(elems)), dim3(kThreads), 0, s, part, nchunk,
-                       elems, dw);
-    ULAUNCH("k_sum_chunks");
-    return ISIS_OK;
+    return launch_sum_chunks(part, nchunk, 27L * cin * cout, dw, s);
 }
 
-int launch_chan_sum(const bf16_t* a, long nvox, int C, float* part, float* out, hipStream_t s)
+// out[c] = sum of channel c of a (C = 16, 32, 64); with o: a = a * (o > 0) first.
+// Scratch: one partial sum per kSumVecs vectors, less than the weight gradient's.
+int launch_chan_sum(bf16_t* a, const bf16_t* o, long nvox, int C, float* part, float* out,
+                    hipStream_t s)
 {
-    const int chunk = 4096;
-    const int nb = (int)((nvox + chunk - 1) / chunk);
-    hipLaunchKernelGGL(k_chan_sum, dim3(nb), dim3(kThreads), 0, s, a, nvox, C, chunk, part);
+    const int nb = (int)((nvox * (C / 8) + kSumVecs - 1) / kSumVecs);
+    if (o)
+        hipLaunchKernelGGL(k_chan_sum<true>, dim3(nb), dim3(kThreads), 0, s, a, o, nvox, C, part);
+    else
+        hipLaunchKernelGGL(k_chan_sum<false>, dim3(nb), dim3(kThreads), 0, s, a, o, nvox, C, part);
     ULAUNCH("k_chan_sum");
-    hipLaunchKernelGGL(k_sum_chunks, dim3(1), dim3(kThreads), 0, s, part, nb, (long)C, out);
-    ULAUNCH("k_sum_chunks");
-    return ISIS_OK;
+    return launch_sum_chunks(part, nb, (long)C, out, s);
 }
-
 
 // ---------------------------------------------------------------------------
 // The network: workspace plan, forward, backward.
@@ -1001,13 +1313,10 @@ int run_backward(const Plan& P, const float* params, hipStream_t s)
         const int lv = level_of(c);
         const long nv = P.nv[lv];
         const int ci = kConvs[c].cin, co = kConvs[c].cout;
-        hipLaunchKernelGGL(k_relu_mask, dim3(grid_of(nv * co)), dim3(kThreads), 0, s, g, P.o[c],
-                           nv * co);
-        ULAUNCH("k_relu_mask");
         float* gw = P.grad + param_offset(c);
-        int rr = launch_conv_dw(x, P.n[lv], ci, g, co, P.part, gw, s);
+        int rr = launch_chan_sum(g, P.o[c], nv, co, P.part, gw + 27L * ci * co, s);
         if (rr) return rr;
-        rr = launch_chan_sum(g, nv, co, P.part, gw + 27L * ci * co, s);
+        rr = launch_conv_dw(x, P.n[lv], ci, g, co, P.part, gw, s);
         if (rr) return rr;
         if (!dx) return ISIS_OK;
         return launch_conv(g, P.n[lv], co, P.wb[c], nullptr, ci, 0, dx, nullptr, s);
@@ -1143,8 +1452,7 @@ int isis_unet_backward(const float* params, const double* phi_cold, const double
     hipLaunchKernelGGL(k_head_bwd, dim3(hb), dim3(kThreads), 0, s, P.out, phi_target, phi_cold,
                        P.o[13], head, P.nv[0], hchunk, P.hpart, P.ga);
     ULAUNCH("k_head_bwd");
-    hipLaunchKernelGGL(k_sum_chunks, dim3(1), dim3(kThreads), 0, s, P.hpart, hb, 18L, P.hsum);
-    ULAUNCH("k_sum_chunks");
+    TRY(launch_sum_chunks(P.hpart, hb, 18L, P.hsum, s));
     // head gradient (16 weights, 1 bias) into the flat gradient
     UCHECK(hipMemcpyAsync(P.grad + param_offset(14), P.hsum, 17 * sizeof(float),
                           hipMemcpyDeviceToDevice, s));
@@ -1278,7 +1586,9 @@ int isis_conv3_bwd_weight(const uint16_t* x, int n, int cin, const uint16_t* dy,
     }
     hipStream_t s = (hipStream_t)stream;
     TRY(launch_conv_dw(x, n, cin, dy, cout, (float*)workspace, dw, s));
-    if (db) TRY(launch_chan_sum(dy, (long)n * n * n, cout, (float*)workspace, db, s));
+    if (db)  // (dy is only read)
+        TRY(launch_chan_sum(const_cast<uint16_t*>(dy), nullptr, (long)n * n * n, cout,
+                            (float*)workspace, db, s));
     return ISIS_OK;
 }
 

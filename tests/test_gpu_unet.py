@@ -167,6 +167,32 @@ def test_conv_weight_gradient(cin, cout, n):
     assert torch.equal(dw, dw2)
 
 
+@pytest.mark.parametrize("cin,cout,n", [(c, o, 16) for c, o in SHAPES] +
+                         [(16, 16, 128), (32, 64, 128), (16, 16, 256)])
+def test_conv_weight_gradient_tiled(cin, cout, n):
+    """The staged weight gradient at its smallest side (one region, no partial
+    sums) and where its regions are longest, against float64 sums on the
+    device.  Tolerance: the exact products are summed in float32 in at most
+    n^3 / 4096 partial sums of 4096 terms or more; for random signs the error
+    is below 2e-5 of sqrt(n^3) standard deviations, as for the other sizes."""
+    g = torch.Generator(device="cuda").manual_seed(cin + 2 * cout + n)
+    x = torch.randn((n, n, n, cin), generator=g, device="cuda").bfloat16()
+    dy = torch.randn((n, n, n, cout), generator=g, device="cuda").bfloat16()
+    ws_bytes = lib().isis_conv3_bwd_weight_workspace(n, cin, cout)
+    ws = torch.empty(ws_bytes, dtype=torch.uint8, device="cuda")
+    dw = torch.empty((27, cout, cin), dtype=torch.float32, device="cuda")
+    db = torch.empty(cout, dtype=torch.float32, device="cuda")
+    assert lib().isis_conv3_bwd_weight(P(x), n, cin, P(dy), cout, P(dw), P(db), P(ws), ws_bytes,
+                                       None) == 0
+    d2 = dy.reshape(-1, cout).double()
+    scale = np.sqrt(n ** 3) * 3
+    for t in range(27):
+        sh = (1 - t // 9, 1 - (t // 3) % 3, 1 - t % 3)
+        xr = torch.roll(x, sh, (0, 1, 2)).reshape(-1, cin).double()
+        assert (dw[t].double() - d2.t().contiguous() @ xr).abs().max().item() <= 2e-5 * scale, t
+    assert (db.double() - d2.sum(0)).abs().max().item() <= 2e-5 * scale
+
+
 def _sample(n, seed):
     rng = np.random.default_rng(seed)
     eta = np.exp(1.2 * rng.standard_normal((n, n, n)))
