@@ -51,6 +51,7 @@ void uerr(const char* fmt, ...)
 
 using bf16_t = uint16_t;
 typedef short s4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf4v __attribute__((ext_vector_type(4)));
 typedef __bf16 bf8v __attribute__((ext_vector_type(8)));
 typedef float f4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u4 __attribute__((ext_vector_type(4)));  // (HIP's uint4 arrays go to scratch)
@@ -74,6 +75,37 @@ __device__ __forceinline__ bf16_t f2bf(float f)
 // ---------------------------------------------------------------------------
 // Convolution (forward; also the data gradient with prepared weights).
 // ---------------------------------------------------------------------------
+
+// Four consecutive channels of one voxel (element offset o, a multiple of 4):
+// ReLU, then to the bf16 and / or FP32 output; vec: as one 8- and 16-byte
+// store (the outputs' base addresses are that much aligned).
+__device__ __forceinline__ void store4(f4 v, int relu, int vec, bf16_t* y, float* yf, size_t o)
+{
+    if (relu) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[r] = fmaxf(v[r], 0.f);
+    }
+    if (vec) {
+        if (y) *reinterpret_cast<bf4v*>(y + o) = __builtin_convertvector(v, bf4v);
+        if (yf) *reinterpret_cast<f4*>(yf + o) = v;
+    } else {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            if (y) y[o + r] = f2bf(v[r]);
+            if (yf) yf[o + r] = v[r];
+        }
+    }
+}
+
+__device__ __forceinline__ f4 bias4(const float* bias, int co)
+{
+    f4 b = f4{0.f, 0.f, 0.f, 0.f};
+    if (bias) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) b[r] = bias[co + r];
+    }
+    return b;
+}
 
 // y[v][co] = sum_t sum_ci x[v + d_t][ci] * w[t][co][ci] (+ bias, ReLU).
 // Any power-of-two side n >= 2; grid = ceil(n^3 / 256) workgroups of four
@@ -154,53 +186,75 @@ __global__ __launch_bounds__(kThreads) void k_conv3(const bf16_t* __restrict__ x
         }
 }
 
-// The same convolution with its input staged in LDS (sides n >= 64).  A
-// workgroup computes a 4 (y) x 64 (z) tile of one x-plane, one z-row of 64
-// voxels per wave (four M tiles of 16).  For each 16-channel slice of the
-// input it stages the 3 x 6 x 66 voxels its 27 taps read (38 KB), so every
-// input value comes from L2 about 4.6 times per convolution instead of once
-// per tap.  LDS holds a slice as two arrays of 16-byte units, one per half
-// of 8 channels ([half][plane][row][z]), read by the 16x16x32 BF16 MFMA two
-// taps at a time: lane g = lane / 16 takes channel half g & 1 of tap 2p + (g
-// >> 1), so the 16 lanes of one (half, tap) group read 256 contiguous bytes
-// (a voxel-major layout put lanes m, m+4, m+8, m+12 on one bank).  The 27th
-// tap is a 14th pair whose second half is zero, so every product runs on the
-// 16x16x32 MFMA.  Tiles are dealt to the 8 XCDs in contiguous ranges with x
-// fastest, so neighbouring planes share an L2.
-constexpr int kLY = 4, kLZ = 64;                   // output tile (y, z)
-constexpr int kLPY = kLY + 2, kLPZ = kLZ + 2;      // with the halo
-constexpr int kLVox = 3 * kLPY * kLPZ;             // staged voxels per slice
+// The same convolution with its input and weights staged in LDS (sides n >=
+// 64).  A workgroup of NW waves computes 16 NT output channels of an NW (y) x
+// 64 (z) tile of two x-planes, one z-row of 64 voxels of both planes per wave
+// (eight M tiles of 16).  For each 16-channel slice of the input it stages the
+// 4 x (NW + 2) x 66 voxels its 27 taps read and the slice's 27 x 16 NT
+// weights.  LDS holds both as arrays of 16-byte units, one per half of 8
+// channels ([half][plane][row][z], [tap][half][channel]), read by the 16x16x32
+// BF16 MFMA two taps at a time: lane g = lane / 16 takes channel half g & 1 of
+// tap 2p + (g >> 1), so the 16 lanes of one (half, tap) group read 256
+// contiguous bytes.  The 27th tap is a 14th pair whose second half is zero, so
+// every product runs on the 16x16x32 MFMA.  Tiles are dealt to the 8 XCDs in
+// contiguous ranges with x fastest, so neighbouring planes share an L2.
+// Bound: with one plane per wave and the weights read from memory by each
+// wave, the weight reads (32 lines of 32 bytes per operand) held the kernel at
+// 0.38-0.55 PFLOP/s; now it reaches 0.5 (NT = 1: one LDS operand per MFMA) to
+// 0.9 (NT = 3, 4).  What is left is the L2: a 32-byte slice of a voxel fetches
+// its whole line, which is often gone before the next slice.  Each output adds
+// slices, taps and channels in the same order as before.
+//   48 -> 16 at 128^3: 0.218 -> 0.171 ms; 64 -> 64 at 64^3: 0.166 -> 0.084 ms;
+//   64 -> 128 at 64^3: 0.293 -> 0.133 ms; 96 -> 32 at 128^3: 0.73 -> 0.48 ms
+constexpr int kLZ = 64;                            // output columns (z)
+constexpr int kLPX = 2, kLPZ = kLZ + 2;            // output planes; staged columns
+template <int NT, int NW>
+struct ConvTile {
+    static constexpr int NTH = 64 * NW;
+    static constexpr int PY = NW + 2;
+    static constexpr int VOX = (kLPX + 2) * PY * kLPZ;      // staged voxels per slice
+    static constexpr int XU = 2 * VOX, WU = 27 * 16 * NT * 2;  // 16-byte units: input, weights
+    static constexpr int XPT = (XU + NTH - 1) / NTH, WPT = (WU + NTH - 1) / NTH;
+    static constexpr int LDS = (XU + WU) * 16;
+};
 
 //
 // CLO > 0: the input is the concatenation [nearest upsampling of lo, x] of a
 // coarse [(n/2)^3][CLO] tensor and a fine [n^3][CIN - CLO] tensor (the
 // decoder's skip), read directly instead of materialised.
-template <int CIN, int COUT, int CLO = 0>
-__global__ __launch_bounds__(kThreads) void k_conv3_lds(const bf16_t* __restrict__ x, int n,
-                                                        const bf16_t* __restrict__ w,
-                                                        const float* __restrict__ bias, int relu,
-                                                        bf16_t* __restrict__ y,
-                                                        float* __restrict__ yf,
-                                                        const bf16_t* __restrict__ lo = nullptr)
+template <int CIN, int COUT, int NT, int NW, int CLO = 0>
+__global__ __launch_bounds__(64 * NW, 2) void k_conv3_lds(const bf16_t* __restrict__ x, int n,
+                                                          const bf16_t* __restrict__ w,
+                                                          const float* __restrict__ bias, int relu,
+                                                          bf16_t* __restrict__ y,
+                                                          float* __restrict__ yf, int vec,
+                                                          const bf16_t* __restrict__ lo = nullptr)
 {
-    static_assert(CIN % 16 == 0 && COUT % 16 == 0 && CLO % 16 == 0 && CLO < CIN,
+    using G = ConvTile<NT, NW>;
+    static_assert(CIN % 16 == 0 && COUT % (16 * NT) == 0 && CLO % 16 == 0 && CLO < CIN,
                   "whole 16-channel slices");
-    constexpr int NT = COUT / 16;
-    __shared__ uint4 tile[2 * kLVox];  // [8-channel half][plane][row][z]
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    u4* tile = reinterpret_cast<u4*>(smem_raw);  // [8-channel half][plane][row][z]
+    u4* wl = tile + G::XU;                       // [tap][8-channel half][output channel]
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int m = lane & 15, g = lane >> 4;
-    const int msk = n - 1, nyt = n / kLY;
+    const int msk = n - 1, nx = n / kLPX, nyt = n / NW;
     const int nb = gridDim.x;
     int b = blockIdx.x;
     if ((nb & 7) == 0) b = (b & 7) * (nb >> 3) + (b >> 3);
-    const int x0 = b % n, yt = (b / n) % nyt, zt = b / (n * nyt);
-    const int y0 = yt * kLY, z0 = zt * kLZ;
+    constexpr int NCO = COUT / (16 * NT);  // channel groups: neighbours, their input stays in L2
+    const int co0 = (b % NCO) * 16 * NT;
+    b /= NCO;
+    const int x0 = (b % nx) * kLPX, yt = (b / nx) % nyt, zt = b / (nx * nyt);
+    const int y0 = yt * NW, z0 = zt * kLZ;
 
-    f4 acc[4][NT];
+    f4 acc[kLPX][4][NT];
 #pragma unroll
-    for (int t = 0; t < 4; ++t)
+    for (int p = 0; p < kLPX; ++p)
 #pragma unroll
-        for (int u = 0; u < NT; ++u) acc[t][u] = f4{0.f, 0.f, 0.f, 0.f};
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int u = 0; u < NT; ++u) acc[p][t][u] = f4{0.f, 0.f, 0.f, 0.f};
 
     // k of the 16x16x32 MFMA = two taps of one slice: lanes g = 0, 1 carry
     // channels 8g..8g+7 of tap 2p, lanes g = 2, 3 those of tap 2p + 1.  The
@@ -209,27 +263,61 @@ __global__ __launch_bounds__(kThreads) void k_conv3_lds(const bf16_t* __restrict
     // tap measured wrong sums for the 32 -> 16 instantiation, whose schedule
     // interleaves the two shapes on renamed accumulators.)
     const int hh = g & 1, side = g >> 1;
-    const uint4* th = tile + hh * kLVox;  // this lane's 8-channel half
-    for (int c0 = 0; c0 < CIN; c0 += 16) {
-        if (c0) __syncthreads();  // the previous slice has been consumed
-        for (int e = tid; e < kLVox * 2; e += kThreads) {
-            const int vox = e >> 1, h = e & 1;
-            const int zz = vox % kLPZ, rr = (vox / kLPZ) % kLPY, pp = vox / (kLPZ * kLPY);
+    const u4* th = tile + hh * G::VOX + wv * kLPZ + m;  // this lane's half, row and column
+    const u4* wh = wl + hh * 16 * NT + m;
+    // staged vectors of this thread (tail clamped; its stores are skipped):
+    // offsets computed once for all slices of a source
+    const int h = tid & 1;  // an even stride: a thread's vectors share a channel half
+    unsigned vo[G::XPT], wo[G::WPT];
+    auto offsets = [&](int sh) __attribute__((always_inline)) {  // sh = 1: of the coarse tensor
+        const int nn = n >> sh;
+#pragma unroll
+        for (int q = 0; q < G::XPT; ++q) {
+            const int vox = min(tid + q * G::NTH, G::XU - 1) >> 1;
+            const int zz = vox % kLPZ, rr = (vox / kLPZ) % G::PY, pp = vox / (kLPZ * G::PY);
             const int xf = (x0 - 1 + pp) & msk, yf_ = (y0 - 1 + rr) & msk, zf = (z0 - 1 + zz) & msk;
-            const bf16_t* src;
-            if constexpr (CLO > 0) {
-                if (c0 < CLO) {
-                    const int nc = n >> 1;
-                    const long V = ((long)(xf >> 1) * nc + (yf_ >> 1)) * nc + (zf >> 1);
-                    src = lo + V * CLO + c0 + 8 * h;
-                } else {
-                    src = x + (((long)xf * n + yf_) * n + zf) * (CIN - CLO) + (c0 - CLO) + 8 * h;
-                }
-            } else {
-                src = x + (((long)xf * n + yf_) * n + zf) * CIN + c0 + 8 * h;
-            }
-            tile[h * kLVox + vox] = *reinterpret_cast<const uint4*>(src);
+            vo[q] = (unsigned)(((xf >> sh) * nn + (yf_ >> sh)) * nn + (zf >> sh));
         }
+    };
+#pragma unroll
+    for (int q = 0; q < G::WPT; ++q) {
+        const int e = min(tid + q * G::NTH, G::WU - 1) >> 1;  // tap * 16 NT + channel
+        wo[q] = (unsigned)((e / (16 * NT) * COUT + co0 + e % (16 * NT)) * CIN + 8 * h);
+    }
+    u4 v[G::XPT], wr[G::WPT];
+    // slice at channel c0 of src's C channels (w's channel wc) into registers
+    auto load = [&](const bf16_t* src, int C, int c0, int wc) __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = 0; q < G::XPT; ++q)
+            v[q] = *reinterpret_cast<const u4*>(src + (size_t)vo[q] * C + c0 + 8 * h);
+#pragma unroll
+        for (int q = 0; q < G::WPT; ++q) wr[q] = *reinterpret_cast<const u4*>(w + wo[q] + wc);
+    };
+    auto put = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = 0; q < G::XPT; ++q) {
+            const int e = tid + q * G::NTH;
+            if ((q + 1) * G::NTH <= G::XU || e < G::XU) tile[h * G::VOX + (e >> 1)] = v[q];
+        }
+#pragma unroll
+        for (int q = 0; q < G::WPT; ++q) {
+            const int e = tid + q * G::NTH, k = e >> 1;
+            if ((q + 1) * G::NTH <= G::WU || e < G::WU)
+                wl[(k / (16 * NT) * 2 + h) * 16 * NT + k % (16 * NT)] = wr[q];
+        }
+    };
+    offsets(CLO > 0 ? 1 : 0);
+    for (int c0 = 0; c0 < CIN; c0 += 16) {
+        // (the next slice held in registers during this one's MFMAs measured
+        // 10 to 30 % slower: the registers cost waves)
+        if (CLO > 0 && c0 < CLO) {
+            load(lo, CLO, c0, c0);
+        } else {
+            if (CLO > 0 && c0 == CLO) offsets(0);
+            load(x, CIN - CLO, c0 - CLO, c0);
+        }
+        if (c0) __syncthreads();  // the previous slice has been consumed
+        put();
         __syncthreads();
 #pragma unroll
         for (int pr = 0; pr < 14; ++pr) {
@@ -237,67 +325,82 @@ __global__ __launch_bounds__(kThreads) void k_conv3_lds(const bf16_t* __restrict
             // read tap 26's (valid) addresses and zero what they loaded
             const bool live = pr < 13 || side == 0;
             const int tap = live ? 2 * pr + side : 26;
-            const int off = ((tap / 9) * kLPY + wv + (tap / 3) % 3) * kLPZ + m + tap % 3;
-            const bf16_t* wt = w + (long)tap * COUT * CIN;
+            const int off = ((tap / 9) * G::PY + (tap / 3) % 3) * kLPZ + tap % 3;
             bf8v bw[NT];
 #pragma unroll
             for (int u = 0; u < NT; ++u) {
-                bw[u] = *reinterpret_cast<const bf8v*>(wt + (long)(16 * u + m) * CIN + c0 + 8 * hh);
+                bw[u] = *reinterpret_cast<const bf8v*>(wh + (tap * 2 * NT + u) * 16);
                 if (!live) bw[u] = bf8v{};
             }
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                bf8v a = *reinterpret_cast<const bf8v*>(th + off + 16 * t);
-                if (!live) a = bf8v{};
+            for (int p = 0; p < kLPX; ++p)
 #pragma unroll
-                for (int u = 0; u < NT; ++u)
-                    acc[t][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bw[u], acc[t][u], 0, 0, 0);
-            }
+                for (int t = 0; t < 4; ++t) {
+                    bf8v a = *reinterpret_cast<const bf8v*>(th + off + p * G::PY * kLPZ + 16 * t);
+                    if (!live) a = bf8v{};
+#pragma unroll
+                    for (int u = 0; u < NT; ++u)
+                        acc[p][t][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bw[u], a, acc[p][t][u], 0, 0, 0);
+                }
         }
     }
-    // D[row = 4g + r][col = m]: voxel z0 + 16t + 4g + r of row y0 + wv, channel 16u + m
-    const long v0 = ((long)x0 * n + (y0 + wv)) * n + z0;
+    // the weights are the row operand: D[row = 4g + r][col = m] is channel
+    // co0 + 16u + 4g + r of voxel z0 + 16t + m, four channels per 8-byte store
 #pragma unroll
-    for (int t = 0; t < 4; ++t)
+    for (int p = 0; p < kLPX; ++p) {
+        const size_t v0 = ((size_t)(x0 + p) * n + (y0 + wv)) * n + z0 + m;
 #pragma unroll
         for (int u = 0; u < NT; ++u) {
-            const int co = 16 * u + m;
-            const float bb = bias ? bias[co] : 0.f;
+            const int co = co0 + 16 * u + 4 * g;
+            const f4 bb = bias4(bias, co);
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const long v = v0 + 16 * t + 4 * g + r;
-                float val = acc[t][u][r] + bb;
-                if (relu) val = fmaxf(val, 0.f);
-                if (y) y[v * COUT + co] = f2bf(val);
-                if (yf) yf[v * COUT + co] = val;
-            }
+            for (int t = 0; t < 4; ++t)
+                store4(acc[p][t][u] + bb, relu, vec, y, yf, (v0 + 16 * t) * COUT + co);
         }
+    }
 }
 
-// 16 input channels (sides n >= 64): the 4 x 64 tile streams along x over
-// xc planes through a ring of three staged planes (6 x 66 voxels, 32 B
-// each), so each output plane stages one new input plane instead of three;
-// the next plane is loaded into registers while the current one is computed.
-template <int COUT>
-__global__ __launch_bounds__(kThreads) void k_conv3_ring(const bf16_t* __restrict__ x, int n,
-                                                         int xc, const bf16_t* __restrict__ w,
-                                                         const float* __restrict__ bias, int relu,
-                                                         bf16_t* __restrict__ y,
-                                                         float* __restrict__ yf)
+// 16 input channels (sides n >= 64): a 4 x 64 (y, z) tile streams along x over
+// xc output planes, 16 output channels per workgroup, one row of 64 voxels
+// per wave (two rows spill).  An input plane contributes to three output planes -- its taps
+// 0..8 to the next one, 9..17 to its own, 18..26 to the previous one -- so
+// three sets of accumulators are live and every plane is staged and read from
+// LDS once: a fragment (row, dk) feeds three MFMAs instead of one, and
+// each output still adds its taps in the order 0..26 (bit for bit the sums of
+// k_conv3).  The 27 weight fragments stay in registers.  The weights are the
+// MFMA's row operand, so a lane ends with four consecutive channels of one
+// voxel and a tile is stored as 512 contiguous bytes (two-byte stores before).
+// LDS holds a plane as four arrays of 4-channel units, one per k-group of the
+// 16x16x16 MFMA, each 128 bytes out of phase modulo the 64 banks.
+// Bound: the MFMA issue (66 % busy at 256^3; the 16x16x16 shape runs at half
+// the rate of 16x16x32, which adds in another order).
+//   16 -> 16 at 256^3: 0.46 -> 0.39 ms; at 128^3: 0.060 -> 0.049 ms;
+//   16 -> 48 at 128^3: 0.254 -> 0.13 ms
+constexpr int kRY = 4, kRW = 1;                    // tile rows, rows per wave
+constexpr int kRPY = kRY + 2, kRPZ = kLZ + 2;
+constexpr int kRVox = kRPY * kRPZ;                 // staged voxels per plane
+constexpr int kRPad = kRVox + (48 - kRVox % 32) % 32;  // = 16 mod 32
+__global__ __launch_bounds__(kThreads, 2) void k_conv3_ring(const bf16_t* __restrict__ x, int n,
+                                                            int xc, const bf16_t* __restrict__ w,
+                                                            const float* __restrict__ bias,
+                                                            int cout, int relu,
+                                                            bf16_t* __restrict__ y,
+                                                            float* __restrict__ yf, int vec)
 {
-    constexpr int CIN = 16, NT = COUT / 16;
-    constexpr int PVOX = kLPY * kLPZ;                   // voxels per staged plane
-    constexpr int PV = PVOX * 2;                        // 16-byte input vectors per plane
+    constexpr int CIN = 16;
+    constexpr int PV = kRVox * 2;                        // 16-byte input vectors per plane
     constexpr int PER = (PV + kThreads - 1) / kThreads;  // of them per thread
-    __shared__ uint2 ring[3 * 4 * PVOX];  // [slot][4-channel group][row][z] (see k_conv3_lds)
+    __shared__ s4 buf[2][4 * kRPad];  // [plane parity][4-channel group][row][z]
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int m = lane & 15, g = lane >> 4;
-    const int msk = n - 1, nyt = n / kLY, nzt = n / kLZ;
+    const int msk = n - 1, nyt = n / kRY, nzt = n / kLZ, nco = cout >> 4;
     const int nb = gridDim.x;
     int b = blockIdx.x;
     if ((nb & 7) == 0) b = (b & 7) * (nb >> 3) + (b >> 3);
+    const int cg = b % nco;  // a tile's channel groups are neighbours: its input stays in L2
+    b /= nco;
     const int yt = b % nyt, zt = (b / nyt) % nzt, xq = b / (nyt * nzt);
-    const int y0 = yt * kLY, z0 = zt * kLZ, x0 = xq * xc;
+    const int y0 = yt * kRY, z0 = zt * kLZ, x0 = xq * xc;
     const size_t plane = (size_t)n * n * CIN;
     // in-plane element offsets of this thread's vectors (tail clamped; its
     // stores are skipped)
@@ -306,78 +409,95 @@ __global__ __launch_bounds__(kThreads) void k_conv3_ring(const bf16_t* __restric
     for (int q = 0; q < PER; ++q) {
         const int e = min(tid + q * kThreads, PV - 1);
         const int vox = e >> 1, h = e & 1;
-        const int zz = vox % kLPZ, rr = vox / kLPZ;
+        const int zz = vox % kRPZ, rr = vox / kRPZ;
         poff[q] = (unsigned)((((y0 - 1 + rr) & msk) * n + ((z0 - 1 + zz) & msk)) * CIN + 8 * h);
     }
-    uint4 pre[PER];
+    u4 pre[PER];
     auto load = [&](int xp) __attribute__((always_inline)) {
         const bf16_t* pl = x + (size_t)(xp & msk) * plane;
 #pragma unroll
-        for (int q = 0; q < PER; ++q) pre[q] = *reinterpret_cast<const uint4*>(pl + poff[q]);
+        for (int q = 0; q < PER; ++q) pre[q] = *reinterpret_cast<const u4*>(pl + poff[q]);
     };
-    auto put = [&](int xp) __attribute__((always_inline)) {
-        uint2* dst = ring + ((xp - x0 + 1) % 3) * 4 * PVOX;
+    auto put = [&](int par) __attribute__((always_inline)) {
 #pragma unroll
         for (int q = 0; q < PER; ++q) {
             const int e = tid + q * kThreads;
             if ((q + 1) * kThreads <= PV || e < PV) {
                 const int vox = e >> 1, h = e & 1;
-                dst[(2 * h) * PVOX + vox] = uint2{pre[q].x, pre[q].y};
-                dst[(2 * h + 1) * PVOX + vox] = uint2{pre[q].z, pre[q].w};
+                s4* d = buf[par] + 2 * h * kRPad + vox;
+                d[0] = __builtin_bit_cast(s4, __builtin_shufflevector(pre[q], pre[q], 0, 1));
+                d[kRPad] = __builtin_bit_cast(s4, __builtin_shufflevector(pre[q], pre[q], 2, 3));
+            }
+        }
+    };
+    s4 bw[27];
+#pragma unroll
+    for (int t = 0; t < 27; ++t)
+        bw[t] = *reinterpret_cast<const s4*>(w + ((size_t)t * cout + 16 * cg + m) * CIN + 4 * g);
+    const f4 bb = bias4(bias, 16 * cg + 4 * g);
+    f4 acc[3][kRW][4];
+    // input plane xp (in buf[par]): taps 0..8 into S (output plane xp + 1,
+    // begun here), 9..17 into M (xp), 18..26 into F (xp - 1, stored)
+    auto step = [&](int xp, int par, f4 (&S)[kRW][4], f4 (&M)[kRW][4], f4 (&F)[kRW][4])
+        __attribute__((always_inline)) {
+        __syncthreads();  // plane xp is in LDS; the other buffer's last readers are done
+        if (xp < x0 + xc) {
+            put(par ^ 1);
+            load(xp + 2);  // (past the last plane loaded and dropped)
+        }
+#pragma unroll
+        for (int r = 0; r < kRW; ++r)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) S[r][t] = f4{0.f, 0.f, 0.f, 0.f};
+        const s4* base = buf[par] + g * kRPad + wv * kRW * kRPZ + m;
+        // groups (input row j, dk): the next group's fragments are read before
+        // this group's MFMAs; sets outside the region's planes are skipped
+        s4 a[2][4];
+        auto mac = [&](int q, int t0, f4 (&C)[kRW][4]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int r = 0; r < kRW; ++r) {
+                const int dj = q / 3 - r;  // this input row is output row r's tap row dj
+                if (dj < 0 || dj > 2) continue;
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+                    C[r][t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(bw[t0 + 3 * dj + q % 3],
+                                                                        a[q & 1][t], C[r][t], 0, 0, 0);
+            }
+        };
+#pragma unroll
+        for (int t = 0; t < 4; ++t) a[0][t] = base[16 * t];
+#pragma unroll
+        for (int q = 0; q < 3 * (kRW + 2); ++q) {
+            if (q + 1 < 3 * (kRW + 2)) {
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+                    a[(q + 1) & 1][t] = base[((q + 1) / 3) * kRPZ + (q + 1) % 3 + 16 * t];
+            }
+            if (xp + 1 < x0 + xc) mac(q, 0, S);
+            if (xp >= x0 && xp < x0 + xc) mac(q, 9, M);
+            if (xp > x0) mac(q, 18, F);
+        }
+        if (xp > x0) {
+            // D[row = 4g + r][col = m]: channel 16 cg + 4g + r, voxel z0 + 16t + m
+#pragma unroll
+            for (int r = 0; r < kRW; ++r) {
+                const size_t v0 = ((size_t)(xp - 1) * n + (y0 + wv * kRW + r)) * n + z0 + m;
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const size_t o = (v0 + 16 * t) * cout + 16 * cg + 4 * g;
+                    store4(F[r][t] + bb, relu, vec, y, yf, o);
+                }
             }
         }
     };
     load(x0 - 1);
-    put(x0 - 1);
+    put(0);
     load(x0);
-    put(x0);
-    load(x0 + 1);
-    for (int xi = x0; xi < x0 + xc; ++xi) {
-        put(xi + 1);  // into the slot of plane xi - 2, free since the last barrier
-        __syncthreads();
-        if (xi + 2 <= x0 + xc) load(xi + 2);  // in flight during this plane's taps
-        f4 acc[4][NT];
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-#pragma unroll
-            for (int u = 0; u < NT; ++u) acc[t][u] = f4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int tap = 0; tap < 27; ++tap) {
-            const int pi = tap / 9, rj = (tap / 3) % 3, zk = tap % 3;
-            const bf16_t* wt = w + (long)tap * COUT * CIN;
-            s4 bw[NT];
-#pragma unroll
-            for (int u = 0; u < NT; ++u)
-                bw[u] = *reinterpret_cast<const s4*>(wt + (16 * u + m) * CIN + 4 * g);
-            const int slot = (xi - 1 + pi - x0 + 1) % 3;
-            const uint2* tg = ring + (slot * 4 + g) * PVOX;  // this lane's k-group
-            const int base = (wv + rj) * kLPZ + m + zk;
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const s4 a = *reinterpret_cast<const s4*>(tg + base + 16 * t);
-#pragma unroll
-                for (int u = 0; u < NT; ++u)
-                    acc[t][u] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, bw[u], acc[t][u], 0,
-                                                                          0, 0);
-            }
-        }
-        const long v0 = ((long)xi * n + (y0 + wv)) * n + z0;
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-#pragma unroll
-            for (int u = 0; u < NT; ++u) {
-                const int co = 16 * u + m;
-                const float bb = bias ? bias[co] : 0.f;
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const long v = v0 + 16 * t + 4 * g + r;
-                    float val = acc[t][u][r] + bb;
-                    if (relu) val = fmaxf(val, 0.f);
-                    if (y) y[v * COUT + co] = f2bf(val);
-                    if (yf) yf[v * COUT + co] = val;
-                }
-            }
-        __syncthreads();  // the slot of plane xi - 1 is free for the next put
+    for (int xp = x0 - 1, par = 0; xp <= x0 + xc; xp += 3) {
+        step(xp, par, acc[0], acc[2], acc[1]);
+        if (xp + 1 <= x0 + xc) step(xp + 1, par ^ 1, acc[1], acc[0], acc[2]);
+        if (xp + 2 <= x0 + xc) step(xp + 2, par, acc[2], acc[1], acc[0]);
+        par ^= 1;
     }
 }
 
@@ -704,9 +824,19 @@ __global__ __launch_bounds__(kThreads) void k_sum_chunks(const float* __restrict
 // workgroup reads contiguous memory (one thread per channel walked the voxels
 // two bytes at a time: 0.55 ms for 16 channels at 128^3, now 0.015 ms).
 // MASK: g = g * (o > 0) first (the ReLU gradient, exact in bf16), written back
-// in the same pass.
+// in the same pass.  VEC = false: tensors not aligned to 16 bytes, the same
+// sums from two-byte accesses.
+template <bool VEC>
+__device__ __forceinline__ u4 load8(const bf16_t* p)
+{
+    if constexpr (VEC) return *reinterpret_cast<const u4*>(p);
+    u4 v;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = (uint32_t)p[2 * i] | ((uint32_t)p[2 * i + 1] << 16);
+    return v;
+}
 constexpr int kSumVecs = 8 * kThreads;  // 16-byte vectors per workgroup
-template <bool MASK>
+template <bool MASK, bool VEC>
 __global__ __launch_bounds__(kThreads) void k_chan_sum(bf16_t* __restrict__ a,
                                                        const bf16_t* __restrict__ o, long nvox,
                                                        int C, float* __restrict__ part)
@@ -715,15 +845,14 @@ __global__ __launch_bounds__(kThreads) void k_chan_sum(bf16_t* __restrict__ a,
     const int tid = threadIdx.x;
     const int U = C >> 3;  // vectors per voxel, a divisor of 256: one channel group per thread
     const long u0 = (long)blockIdx.x * kSumVecs + tid, end = nvox * U;
-    u4* av = reinterpret_cast<u4*>(a);
-    const u4* ov = reinterpret_cast<const u4*>(o);
+    static_assert(VEC || !MASK, "the network's own tensors are aligned");
     float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     u4 v[8], p[8];
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
         const long u = min(u0 + k * kThreads, end - 1);  // (clamped: branch-free loads)
-        v[k] = av[u];
-        if constexpr (MASK) p[k] = ov[u];
+        v[k] = load8<VEC>(a + u * 8);
+        if constexpr (MASK) p[k] = load8<true>(o + u * 8);
     }
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
@@ -735,7 +864,7 @@ __global__ __launch_bounds__(kThreads) void k_chan_sum(bf16_t* __restrict__ a,
                 if (!(bf2f((bf16_t)(p[k][i] & 0xffffu)) > 0.f)) v[k][i] &= 0xffff0000u;
                 if (!(bf2f((bf16_t)(p[k][i] >> 16)) > 0.f)) v[k][i] &= 0xffffu;
             }
-            av[u] = v[k];
+            *reinterpret_cast<u4*>(a + u * 8) = v[k];
         }
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -1020,31 +1149,54 @@ long param_total() { return param_offset(14) + kHeadIn + 1; }
         }                                                                             \
     } while (0)
 
+// Whether four-channel stores to these outputs are aligned.
+int vec_ok(const bf16_t* y, const float* yf)
+{
+    return ((uintptr_t)y & 7) == 0 && ((uintptr_t)yf & 15) == 0;
+}
+
+template <int CIN, int COUT, int CLO = 0>
+int launch_conv_lds(const bf16_t* x, int n, const bf16_t* w, const float* bias, int relu,
+                    bf16_t* y, float* yf, const bf16_t* lo, hipStream_t s)
+{
+    // output channels per workgroup: 16 NT; eight waves where the weights
+    // fill most of the LDS (one workgroup per CU), four otherwise (two per CU)
+    constexpr int NT = COUT == 16 ? 1 : COUT == 32 ? 2 : COUT == 96 ? 3 : 4;
+    constexpr int NW = NT >= 3 ? 8 : 4;
+    using G = ConvTile<NT, NW>;
+    static std::atomic<unsigned> lds_done{0};  // per instantiation: devices set up
+    auto kern = k_conv3_lds<CIN, COUT, NT, NW, CLO>;
+    UCHECK(isis::ensure_dynamic_lds((const void*)kern, G::LDS, lds_done));
+    const long blocks = (long)(n / kLPX) * (n / NW) * (n / kLZ) * (COUT / (16 * NT));
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(G::NTH), G::LDS, s, x, n, w, bias, relu,
+                       y, yf, vec_ok(y, yf), lo);
+    ULAUNCH("k_conv3_lds");
+    return ISIS_OK;
+}
+
 int launch_conv(const bf16_t* x, int n, int cin, const bf16_t* w, const float* bias, int cout,
                 int relu, bf16_t* y, float* yf, hipStream_t s)
 {
     const long nvox = (long)n * n * n;
     const int blocks = (int)((nvox + 255) / 256);
-    // sides >= 64 (powers of two): the LDS-staged kernel, one workgroup per
-    // 4 x 64 tile of an x-plane
-    const bool lds = n >= kLZ;
-    const long lblocks = (long)n * (n / kLY) * (n / kLZ);
-    // 16 input channels: planes per workgroup for the ring kernel, a power of
-    // two up to 16 that leaves >= 2048 workgroups
-    const long tiles2d = (long)(n / kLY) * (n / kLZ);
-    int xc = 1;
-    while (xc < 16 && tiles2d * (n / (2 * xc)) >= 2048) xc *= 2;
+    const bool lds = n >= kLZ;  // powers of two: whole tiles
+    if (lds && cin == 16 && (cout == 16 || cout == 32 || cout == 48)) {
+        // planes per workgroup: a power of two up to 64 that leaves >= 512
+        // workgroups (two per CU)
+        const long cols = (long)(n / kRY) * (n / kLZ) * (cout / 16);
+        int xc = 2;
+        while (xc < 64 && cols * (n / (2 * xc)) >= 512) xc *= 2;
+        hipLaunchKernelGGL(k_conv3_ring, dim3((unsigned)(cols * (n / xc))), dim3(kThreads), 0, s,
+                           x, n, xc, w, bias, cout, relu, y, yf, vec_ok(y, yf));
+        ULAUNCH("k_conv3_ring");
+        return ISIS_OK;
+    }
 #define CONV_CASE(CI, CO)                                                                   \
     if (cin == CI && cout == CO) {                                                          \
-        if (lds && CI == 16)                                                                \
-            hipLaunchKernelGGL((k_conv3_ring<CO>), dim3((unsigned)(tiles2d * (n / xc))),     \
-                               dim3(kThreads), 0, s, x, n, xc, w, bias, relu, y, yf);       \
-        else if (lds)                                                                       \
-            hipLaunchKernelGGL((k_conv3_lds<CI, CO>), dim3((unsigned)lblocks), dim3(kThreads), \
-                               0, s, x, n, w, bias, relu, y, yf);                           \
-        else                                                                                \
-            hipLaunchKernelGGL((k_conv3<CI, CO>), dim3(blocks), dim3(kThreads), 0, s, x, n, \
-                               w, bias, relu, y, yf);                                       \
+        if constexpr (CI > 16)                                                              \
+            if (lds) return launch_conv_lds<CI, CO>(x, n, w, bias, relu, y, yf, nullptr, s); \
+        hipLaunchKernelGGL((k_conv3<CI, CO>), dim3(blocks), dim3(kThreads), 0, s, x, n, w,  \
+                           bias, relu, y, yf);                                              \
         ULAUNCH("k_conv3");                                                                 \
         return ISIS_OK;                                                                     \
     }
@@ -1068,11 +1220,7 @@ int launch_conv_cat(const bf16_t* lo, const bf16_t* skip, int n, int cin, int cl
              clo, cout, n);
         return ISIS_ERR_UNSUPPORTED;
     }
-    const long lblocks = (long)n * (n / kLY) * (n / kLZ);
-    hipLaunchKernelGGL((k_conv3_lds<48, 16, 32>), dim3((unsigned)lblocks), dim3(kThreads), 0, s,
-                       skip, n, w, bias, relu, y, nullptr, lo);
-    ULAUNCH("k_conv3_lds (concatenated input)");
-    return ISIS_OK;
+    return launch_conv_lds<48, 16, 32>(skip, n, w, bias, relu, y, nullptr, lo, s);
 }
 
 int dw_chunk(long nvox) { return (int)std::min<long>(nvox, 4096); }
@@ -1120,13 +1268,14 @@ int launch_conv_dw(const bf16_t* x, int n, int cin, const bf16_t* dy, int cout, 
     // Regions per launch stay within the caller's n^3 / 4096 partial sums.
     // Planes per region: 8 up to 128^3 (512 regions there, two workgroups per
     // CU for one channel tile), 16 at 256^3, 32 above (fewer partial sums).
-    if (n >= 64) {
+    const bool vec = (((uintptr_t)x | (uintptr_t)dy) & 15) == 0;  // 16-byte loads
+    if (vec && n >= 64) {
         const int xc = n <= 128 ? 8 : n == 256 ? 16 : 32;
         return launch_dw_tiled<DwTile<64, 8, 3>>(x, n, cin, dy, cout, xc, part, dw, s);
     }
-    if (n == 32) return launch_dw_tiled<DwTile<32, 8, 1>>(x, n, cin, dy, cout, 16, part, dw, s);
-    if (n == 16) return launch_dw_tiled<DwTile<16, 16, 1>>(x, n, cin, dy, cout, 16, part, dw, s);
-    // sides below 16: no 16-voxel windows along z
+    if (vec && n == 32) return launch_dw_tiled<DwTile<32, 8, 1>>(x, n, cin, dy, cout, 16, part, dw, s);
+    if (vec && n == 16) return launch_dw_tiled<DwTile<16, 16, 1>>(x, n, cin, dy, cout, 16, part, dw, s);
+    // sides below 16 (no 16-voxel windows along z) and unaligned tensors
     const int chunk = dw_chunk(nvox);
     const int nchunk = (int)(nvox / chunk);
 #define DW_CASE(CI, CO)                                                                     \
@@ -1147,9 +1296,11 @@ int launch_chan_sum(bf16_t* a, const bf16_t* o, long nvox, int C, float* part, f
 {
     const int nb = (int)((nvox * (C / 8) + kSumVecs - 1) / kSumVecs);
     if (o)
-        hipLaunchKernelGGL(k_chan_sum<true>, dim3(nb), dim3(kThreads), 0, s, a, o, nvox, C, part);
+        hipLaunchKernelGGL((k_chan_sum<true, true>), dim3(nb), dim3(kThreads), 0, s, a, o, nvox, C, part);
+    else if (((uintptr_t)a & 15) == 0)
+        hipLaunchKernelGGL((k_chan_sum<false, true>), dim3(nb), dim3(kThreads), 0, s, a, o, nvox, C, part);
     else
-        hipLaunchKernelGGL(k_chan_sum<false>, dim3(nb), dim3(kThreads), 0, s, a, o, nvox, C, part);
+        hipLaunchKernelGGL((k_chan_sum<false, false>), dim3(nb), dim3(kThreads), 0, s, a, o, nvox, C, part);
     ULAUNCH("k_chan_sum");
     return launch_sum_chunks(part, nb, (long)C, out, s);
 }

@@ -92,6 +92,23 @@ def test_conv_forward_staged(cin, cout, n):
         assert np.array_equal(gb.reshape(got.shape)[sel], U.bf16(got[sel]).astype(np.float32))
 
 
+@pytest.mark.parametrize("cin,cout,n", [(16, 16, 64), (16, 48, 64), (32, 32, 64), (64, 64, 64),
+                                        (32, 96, 64), (48, 16, 64)])
+def test_conv_unaligned_outputs(cin, cout, n):
+    """Outputs at addresses that are not multiples of the vector stores (a view
+    one element into its storage): the same values as aligned ones."""
+    rng = np.random.default_rng(cin + cout + n)
+    x = raw(U.bf16(rng.standard_normal((n, n, n, cin))))
+    w = raw(U.bf16(rng.standard_normal((27, cout, cin)) * 0.1))
+    got = []
+    for off in (0, 1):
+        yb = torch.zeros(n ** 3 * cout + 1, dtype=torch.int16, device="cuda")[off:][:n ** 3 * cout]
+        yf = torch.zeros(n ** 3 * cout + 1, device="cuda")[off:][:n ** 3 * cout]
+        assert lib().isis_conv3_fwd(P(x), n, cin, P(w), None, cout, 1, P(yb), P(yf), None) == 0
+        got.append((yb, yf))
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+
+
 @pytest.mark.parametrize("cin,cout", SHAPES)
 def test_conv_data_gradient(cin, cout):
     """Flipped, transposed weights turn the forward kernel into the adjoint."""
@@ -191,6 +208,28 @@ def test_conv_weight_gradient_tiled(cin, cout, n):
         xr = torch.roll(x, sh, (0, 1, 2)).reshape(-1, cin).double()
         assert (dw[t].double() - d2.t().contiguous() @ xr).abs().max().item() <= 2e-5 * scale, t
     assert (db.double() - d2.sum(0)).abs().max().item() <= 2e-5 * scale
+
+
+@pytest.mark.parametrize("n", [2, 16, 32, 64])
+def test_conv_weight_gradient_unaligned(n):
+    """Inputs one element into their storage take the kernels without 16-byte
+    loads: the aligned result within the bound of the other sizes (twice, both
+    sides round)."""
+    cin, cout = 32, 64
+    g = torch.Generator(device="cuda").manual_seed(n)
+    src = [torch.randn(n ** 3 * c + 1, generator=g, device="cuda").bfloat16() for c in (cin, cout)]
+    ws_bytes = lib().isis_conv3_bwd_weight_workspace(n, cin, cout)
+    ws = torch.empty(ws_bytes, dtype=torch.uint8, device="cuda")
+    out = []
+    for shift in (False, True):
+        x, dy = (t[1:] if shift else t[1:].clone() for t in src)
+        dw = torch.empty(27 * cout * cin, device="cuda")
+        db = torch.empty(cout, device="cuda")
+        assert lib().isis_conv3_bwd_weight(P(x), n, cin, P(dy), cout, P(dw), P(db), P(ws),
+                                           ws_bytes, None) == 0
+        out.append((dw, db))
+    for a, b in zip(*out):
+        assert (a - b).abs().max().item() <= 4e-5 * 3 * np.sqrt(n ** 3)
 
 
 def _sample(n, seed):
