@@ -107,83 +107,192 @@ __device__ __forceinline__ f4 bias4(const float* bias, int co)
     return b;
 }
 
-// y[v][co] = sum_t sum_ci x[v + d_t][ci] * w[t][co][ci] (+ bias, ReLU).
-// Any power-of-two side n >= 2; grid = ceil(n^3 / 256) workgroups of four
-// waves, each wave 64 consecutive voxels (four M tiles of 16).  Lanes past the
-// last voxel load voxel 0 and store nothing.
-template <int CIN, int COUT>
+// y[v][co] = sum_t sum_ci x[v + d_t][ci] * w[t][co][ci] (+ bias, ReLU), sides
+// below 8.  Any power-of-two side n >= 2; each wave owns 16 consecutive
+// voxels and 16 output channels (a few hundred waves at most: these grids are
+// all latency).  Lanes past the last voxel load voxel 0 and store nothing.
+//   64 -> 64 at 4^3: 0.085 -> 0.025 ms
+template <int CIN>
 __global__ __launch_bounds__(kThreads) void k_conv3(const bf16_t* __restrict__ x, int n,
                                                     const bf16_t* __restrict__ w,
-                                                    const float* __restrict__ bias, int relu,
-                                                    bf16_t* __restrict__ y, float* __restrict__ yf)
+                                                    const float* __restrict__ bias, int cout,
+                                                    int relu, int vec, bf16_t* __restrict__ y,
+                                                    float* __restrict__ yf)
 {
-    constexpr int NT = COUT / 16;
     const int lane = threadIdx.x & 63;
-    const long wave = (long)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
-    const long v0 = wave * 64;  // first voxel of this wave
-    const long nvox = (long)n * n * n;
-    const int msk = n - 1;
+    const int wave = blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
+    const int nco = cout >> 4;
+    const int co0 = (wave % nco) * 16, v0 = (wave / nco) * 16;
+    const int nvox = n * n * n, msk = n - 1;
+    if (v0 >= nvox) return;
     const int m = lane & 15, g = lane >> 4;
-    // coordinates of this lane's voxel in each M tile (A operand row m)
-    int ci_[4], cj_[4], ck_[4];
+    const int v = v0 + m < nvox ? v0 + m : 0;
+    const int ck = v & msk, cj = (v / n) & msk, ci = v / (n * n);
+    constexpr int NS = CIN / 16;
+    // three taps (dk = -1, 0, 1) at a time, the next three in flight
+    s4 xa[2][3][NS], wa[2][3][NS];
+    auto load = [&](int t9, int p) __attribute__((always_inline)) {
+        const int di = t9 / 3 - 1, dj = t9 % 3 - 1;
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        long v = v0 + 16 * t + m;
-        if (v >= nvox) v = 0;
-        ck_[t] = (int)(v % n);
-        const long r = v / n;
-        cj_[t] = (int)(r % n);
-        ci_[t] = (int)(r / n);
-    }
-
-    f4 acc[4][NT];
+        for (int k = 0; k < 3; ++k) {
+            const bf16_t* xs = x + (((((ci + di) & msk) * n + ((cj + dj) & msk)) * n + ((ck + k - 1) & msk)) * CIN + 4 * g);
+            const bf16_t* wt = w + ((3 * t9 + k) * cout + co0 + m) * CIN + 4 * g;
 #pragma unroll
-    for (int t = 0; t < 4; ++t)
-#pragma unroll
-        for (int u = 0; u < NT; ++u) acc[t][u] = f4{0.f, 0.f, 0.f, 0.f};
-
-    for (int tap = 0; tap < 27; ++tap) {
-        const int di = tap / 9 - 1, dj = (tap / 3) % 3 - 1, dk = tap % 3 - 1;
-        const bf16_t* wt = w + (long)tap * COUT * CIN;
-        long src[4];
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-            src[t] = ((long)((ci_[t] + di) & msk) * n + ((cj_[t] + dj) & msk)) * n +
-                     ((ck_[t] + dk) & msk);
-#pragma unroll
-        for (int c0 = 0; c0 < CIN; c0 += 16) {
-            s4 a[4], b[NT];
-#pragma unroll
-            for (int t = 0; t < 4; ++t)
-                a[t] = *reinterpret_cast<const s4*>(x + src[t] * CIN + c0 + 4 * g);
-#pragma unroll
-            for (int u = 0; u < NT; ++u)
-                b[u] = *reinterpret_cast<const s4*>(wt + (long)(16 * u + m) * CIN + c0 + 4 * g);
-#pragma unroll
-            for (int t = 0; t < 4; ++t)
-#pragma unroll
-                for (int u = 0; u < NT; ++u)
-                    acc[t][u] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a[t], b[u], acc[t][u], 0,
-                                                                          0, 0);
-        }
-    }
-    // D[row = 4g + r][col = m]: voxel v0 + 16t + 4g + r, channel 16u + m
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-#pragma unroll
-        for (int u = 0; u < NT; ++u) {
-            const int co = 16 * u + m;
-            const float bb = bias ? bias[co] : 0.f;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const long v = v0 + 16 * t + 4 * g + r;
-                if (v >= nvox) continue;
-                float val = acc[t][u][r] + bb;
-                if (relu) val = fmaxf(val, 0.f);
-                if (y) y[v * COUT + co] = f2bf(val);
-                if (yf) yf[v * COUT + co] = val;
+            for (int s = 0; s < NS; ++s) {
+                xa[p][k][s] = *reinterpret_cast<const s4*>(xs + 16 * s);
+                wa[p][k][s] = *reinterpret_cast<const s4*>(wt + 16 * s);
             }
         }
+    };
+    f4 acc = f4{0.f, 0.f, 0.f, 0.f};
+    load(0, 0);
+#pragma unroll
+    for (int t9 = 0; t9 < 9; ++t9) {
+        if (t9 < 8) load(t9 + 1, (t9 + 1) & 1);
+        __builtin_amdgcn_sched_barrier(0);  // keep the loads ahead of these MFMAs
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+#pragma unroll
+            for (int s = 0; s < NS; ++s)
+                acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(wa[t9 & 1][k][s], xa[t9 & 1][k][s], acc, 0, 0, 0);
+    }
+    // the weights are the row operand: D[row = 4g + r][col = m] is channel
+    // co0 + 4g + r of voxel v0 + m
+    if (v0 + m < nvox)
+        store4(acc + bias4(bias, co0 + 4 * g), relu, vec, y, yf, (size_t)(v0 + m) * cout + co0 + 4 * g);
+}
+
+// The same convolution on sides 8, 16 and 32 (Z), all input channels staged in
+// LDS: a workgroup computes 16 NT output channels of TY rows of one x-plane,
+// MW M tiles of 16 voxels per wave.  LDS holds the 3 x (TY + 2) x (Z + 2)
+// voxels as arrays of 4-channel units, one per k-group of the 16x16x16 MFMA
+// (see k_conv3_ring), and two buffers of the weights of TPB taps each, filled
+// one stage ahead.  (Weight operands read from memory by every wave, 16 lines
+// of 32 bytes each, held 64 -> 64 at 32^3 at 0.058 ms.)  Taps, then channels
+// are added in the order of k_conv3.  Bound: at 32^3 one workgroup per CU,
+// LDS reads and MFMAs in about equal parts; at 16^3 latency.
+//   64 -> 64 at 32^3: 0.109 -> 0.024 ms; at 16^3: 0.107 -> 0.009 ms
+template <int CIN, int NT, int Z, int TY, int TPB>
+struct ConvSmall {
+    static constexpr int NS = CIN / 16;
+    static constexpr int ZP = Z + 2, VOX = 3 * (TY + 2) * ZP;
+    static constexpr int VP = VOX + (48 - VOX % 32) % 32;  // = 16 mod 32: groups 128 bytes out of phase
+    static constexpr int WU = TPB * 16 * NT * (CIN / 8);   // 16-byte units of weights per stage
+    static constexpr int WPT = (WU + kThreads - 1) / kThreads;
+    static constexpr int LDS = VP * CIN * 2 + 2 * WU * 16;
+    static constexpr int MW = TY * Z / 64;                 // M tiles (16 voxels of the tile's rows) per wave
+    static_assert(MW >= 1 && TY * Z % 64 == 0 && 27 % TPB == 0, "four waves share the tile");
+    static_assert(LDS <= 160 * 1024, "LDS overflow");
+};
+template <int CIN, int NT, int Z, int TY, int TPB>
+__global__ __launch_bounds__(kThreads, 1) void k_conv3_small(const bf16_t* __restrict__ x,
+                                                             const bf16_t* __restrict__ w,
+                                                             const float* __restrict__ bias,
+                                                             int cout, int relu, int vec,
+                                                             bf16_t* __restrict__ y,
+                                                             float* __restrict__ yf)
+{
+    using G = ConvSmall<CIN, NT, Z, TY, TPB>;
+    constexpr int n = Z, msk = n - 1, NS = G::NS;
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    s4* tile = reinterpret_cast<s4*>(smem_raw);  // [slice][4-channel group][plane][row][z]
+    s4* wl = tile + G::VP * (CIN / 4);           // [buffer][tap][slice][16 channels][group][channel]
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int m = lane & 15, g = lane >> 4;
+    const int nco = cout / (16 * NT);
+    int b = blockIdx.x;
+    const int co0 = (b % nco) * 16 * NT;
+    b /= nco;
+    const int y0 = (b % (n / TY)) * TY, x0 = b / (n / TY);
+    u4 wr[G::WPT];
+    // stage st's weights; unit e: 8 channels 8q .. of output channel co0 + c, tap t
+    auto load_w = [&](int st) __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < G::WPT; ++k) {
+            const int e = min(tid + k * kThreads, G::WU - 1);
+            const int q = e % (CIN / 8), c = (e / (CIN / 8)) % (16 * NT), t = e / (CIN / 8 * 16 * NT);
+            wr[k] = *reinterpret_cast<const u4*>(w + (size_t)((st * TPB + t) * cout + co0 + c) * CIN + 8 * q);
+        }
+    };
+    // channel c of group gg sits at position c ^ 2 (q mod 8), q = 8-channel
+    // index: the units of one output channel fall on different banks
+    auto put_w = [&](int buf) __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < G::WPT; ++k) {
+            const int e = tid + k * kThreads;
+            if ((k + 1) * kThreads <= G::WU || e < G::WU) {
+                const int q = e % (CIN / 8), c = (e / (CIN / 8)) % (16 * NT), t = e / (CIN / 8 * 16 * NT);
+                s4* d = wl + buf * 2 * G::WU +
+                        (((t * NS + (q >> 1)) * NT + (c >> 4)) * 4 + 2 * (q & 1)) * 16 +
+                        ((c & 15) ^ (2 * (q & 7)));
+                d[0] = __builtin_bit_cast(s4, __builtin_shufflevector(wr[k], wr[k], 0, 1));
+                d[16] = __builtin_bit_cast(s4, __builtin_shufflevector(wr[k], wr[k], 2, 3));
+            }
+        }
+    };
+    load_w(0);
+#pragma unroll 4
+    for (int e = tid; e < G::VOX * (CIN / 8); e += kThreads) {
+        const int q = e % (CIN / 8), v = e / (CIN / 8);  // 8 channels 8q .. of staged voxel v
+        const int zz = v % G::ZP, rr = (v / G::ZP) % (TY + 2), pp = v / (G::ZP * (TY + 2));
+        const int vox = (((x0 - 1 + pp) & msk) * n + ((y0 - 1 + rr) & msk)) * n + ((zz - 1) & msk);
+        const u4 r = *reinterpret_cast<const u4*>(x + (size_t)vox * CIN + 8 * q);
+        s4* d = tile + 2 * q * G::VP + v;
+        d[0] = __builtin_bit_cast(s4, __builtin_shufflevector(r, r, 0, 1));
+        d[G::VP] = __builtin_bit_cast(s4, __builtin_shufflevector(r, r, 2, 3));
+    }
+    f4 acc[G::MW][NT];
+#pragma unroll
+    for (int t = 0; t < G::MW; ++t)
+#pragma unroll
+        for (int u = 0; u < NT; ++u) acc[t][u] = f4{0.f, 0.f, 0.f, 0.f};
+    const s4* base[G::MW];  // this lane's voxel in its wave's tiles
+#pragma unroll
+    for (int t = 0; t < G::MW; ++t) {
+        const int q = (wv * G::MW + t) * 16 + m;
+        base[t] = tile + g * G::VP + (q / Z) * G::ZP + q % Z;
+    }
+    int wp[NS];  // this lane's weight position per slice
+#pragma unroll
+    for (int s = 0; s < NS; ++s) wp[s] = g * 16 + (m ^ (2 * ((2 * s + (g >> 1)) & 7)));
+    put_w(0);
+    if (27 / TPB > 1) load_w(1);
+    __syncthreads();
+    for (int st = 0; st < 27 / TPB; ++st) {
+        if (st + 1 < 27 / TPB) {
+            put_w((st + 1) & 1);
+            load_w(min(st + 2, 27 / TPB - 1));
+        }
+        const s4* ws = wl + (st & 1) * 2 * G::WU;
+#pragma unroll
+        for (int tt = 0; tt < TPB; ++tt) {
+            const int tap = st * TPB + tt;
+            const int off = ((tap / 9) * (TY + 2) + (tap / 3) % 3) * G::ZP + tap % 3;
+#pragma unroll
+            for (int s = 0; s < NS; ++s) {
+                s4 wq[NT];
+#pragma unroll
+                for (int u = 0; u < NT; ++u) wq[u] = ws[((tt * NS + s) * NT + u) * 64 + wp[s]];
+#pragma unroll
+                for (int t = 0; t < G::MW; ++t) {
+                    const s4 a = base[t][off + 4 * s * G::VP];
+#pragma unroll
+                    for (int u = 0; u < NT; ++u)
+                        acc[t][u] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(wq[u], a, acc[t][u], 0, 0, 0);
+                }
+            }
+        }
+        __syncthreads();  // this stage's buffer is refilled next
+    }
+#pragma unroll
+    for (int t = 0; t < G::MW; ++t) {
+        const size_t v = ((size_t)x0 * n + y0) * n + (wv * G::MW + t) * 16 + m;
+#pragma unroll
+        for (int u = 0; u < NT; ++u) {
+            const int co = co0 + 16 * u + 4 * g;
+            store4(acc[t][u] + bias4(bias, co), relu, vec, y, yf, v * cout + co);
+        }
+    }
 }
 
 // The same convolution with its input and weights staged in LDS (sides n >=
@@ -1174,11 +1283,23 @@ int launch_conv_lds(const bf16_t* x, int n, const bf16_t* w, const float* bias, 
     return ISIS_OK;
 }
 
+template <int CIN, int NT, int Z, int TY, int TPB>
+int launch_conv_small(const bf16_t* x, const bf16_t* w, const float* bias, int cout, int relu,
+                      bf16_t* y, float* yf, hipStream_t s)
+{
+    constexpr int lds = ConvSmall<CIN, NT, Z, TY, TPB>::LDS;
+    static std::atomic<unsigned> lds_done{0};  // per instantiation: devices set up
+    auto kern = k_conv3_small<CIN, NT, Z, TY, TPB>;
+    UCHECK(isis::ensure_dynamic_lds((const void*)kern, lds, lds_done));
+    hipLaunchKernelGGL(kern, dim3(Z * (Z / TY) * (cout / (16 * NT))), dim3(kThreads), lds, s, x, w,
+                       bias, cout, relu, vec_ok(y, yf), y, yf);
+    ULAUNCH("k_conv3_small");
+    return ISIS_OK;
+}
+
 int launch_conv(const bf16_t* x, int n, int cin, const bf16_t* w, const float* bias, int cout,
                 int relu, bf16_t* y, float* yf, hipStream_t s)
 {
-    const long nvox = (long)n * n * n;
-    const int blocks = (int)((nvox + 255) / 256);
     const bool lds = n >= kLZ;  // powers of two: whole tiles
     if (lds && cin == 16 && (cout == 16 || cout == 32 || cout == 48)) {
         // planes per workgroup: a power of two up to 64 that leaves >= 512
@@ -1195,8 +1316,16 @@ int launch_conv(const bf16_t* x, int n, int cin, const bf16_t* w, const float* b
     if (cin == CI && cout == CO) {                                                          \
         if constexpr (CI > 16)                                                              \
             if (lds) return launch_conv_lds<CI, CO>(x, n, w, bias, relu, y, yf, nullptr, s); \
-        hipLaunchKernelGGL((k_conv3<CI, CO>), dim3(blocks), dim3(kThreads), 0, s, x, n, w,  \
-                           bias, relu, y, yf);                                              \
+        if (n == 32)  /* rows per workgroup: what fits the LDS */                           \
+            return launch_conv_small<CI, (CO % 64 == 0 ? 4 : CO % 32 == 0 ? 2 : 1), 32,     \
+                                     (CI > 64 ? 2 : 4), 1>(x, w, bias, CO, relu, y, yf, s); \
+        if (n == 16)                                                                        \
+            return launch_conv_small<CI, 1, 16, 4, 9>(x, w, bias, CO, relu, y, yf, s);      \
+        if (n == 8)                                                                         \
+            return launch_conv_small<CI, 1, 8, 8, 9>(x, w, bias, CO, relu, y, yf, s);       \
+        const int waves = (n * n * n + 15) / 16 * (CO / 16);                                \
+        hipLaunchKernelGGL((k_conv3<CI>), dim3((waves + 3) / 4), dim3(kThreads), 0, s, x,   \
+                           n, w, bias, CO, relu, vec_ok(y, yf), y, yf);                     \
         ULAUNCH("k_conv3");                                                                 \
         return ISIS_OK;                                                                     \
     }

@@ -63,6 +63,15 @@ def test_conv_forward(cin, cout, n):
         1e-5 * np.abs(ref).max()
 
 
+@pytest.mark.parametrize("cin,cout", SHAPES + [(64, 128), (32, 96), (16, 48)])
+@pytest.mark.parametrize("n", [2, 32])
+def test_conv_forward_sides(cin, cout, n):
+    """The smallest side (one wave covers more voxels than there are) and the
+    largest that keeps all channels in LDS, with the data gradients' channel
+    counts."""
+    test_conv_forward(cin, cout, n)
+
+
 @pytest.mark.parametrize("cin,cout,n", [(c, o, 64) for c, o in SHAPES] +
                          [(16, 48, 64), (16, 16, 128), (48, 16, 128)])
 def test_conv_forward_staged(cin, cout, n):
