@@ -1,5 +1,5 @@
 // The bottom of a V-cycle in one workgroup: from the first level of side
-// <= 16 down to the 4^3 coarsest grid and back (Sec. 3.2), with every array
+// <= 16 down to the 4^3 coarsest grid and back (Sec. 3.2), with every field
 // these levels touch held in LDS.  On the device each of these levels is a
 // dozen launches of a few microseconds each, almost all launch and drain;
 // here they are one launch whose phases are separated by workgroup barriers.
@@ -9,6 +9,17 @@
 // k_prolong_correct (with its weights PW) and the coarsest grid's sweeps of
 // k_coarse_solve.  Only the first level's field is written back; the coarser
 // levels' fields are rebuilt by every descent.
+//
+// Bound: the one CU's latency and VALU.  So the sides are compile-time (the
+// indices are shifts and masks; with runtime sides every cell paid five
+// integer divisions), the first level's density and source stay in the
+// registers of the thread that owns the cell, f(R)'s e^phi is computed once
+// per value beside the field instead of seven times per update, the defect is
+// computed once per fine cell, and the 4^3 grid lives in one wave's registers
+// (coarsest_sweeps).
+// First level 16^3, per call, before and with this: symmetron FP64 67 -> 25 us,
+// f(R) FP32 78 -> 42 and FP64 139 -> 79, chameleon FP32 70 -> 33 and FP64
+// 128 -> 62.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -18,274 +29,376 @@ namespace isis {
 
 constexpr int kBottomMaxN = 16;      // side of the first level handled
 constexpr int kBottomMaxLevels = 3;  // 16, 8, 4
-// threads: 1024 in single precision (16 waves hide LDS latency on the one
-// CU; every model's update fits 128 registers), 512 in double (up to 218)
-template <class T>
+// Threads: 1024 (16 waves hide the LDS latency on the one CU; up to 128
+// registers), 512 where the double-precision exponentials need more.
+template <class T, class M>
 constexpr int bottom_threads()
 {
-    return sizeof(T) == 4 ? 1024 : 512;
+    return sizeof(T) == 8 && StageOp<T, M>::kStaged ? 512 : 1024;
 }
 
 template <class T>
 struct BottomArgs {
-    int nlev;                        // levels handled, 2 or 3; sides 4 << (nlev - 1 - q)
     int nu_pre, nu_post, nu_coarse;
     T* phi0;                         // the first level's field, updated in place
     const T* sigma0;                 // the first level's FAS source (may be NULL: zero)
+    int from_rr;                     // sigma0 is its restricted defect: sigma = L(phi0) - rr
     const T* eta[kBottomMaxLevels];  // densities
     T ih2[kBottomMaxLevels];         // 1/h^2 per level
 };
 
-// LDS elements: per level field, density and FAS source, plus the first
-// level's fine-defect buffer and each coarser level's restricted field.
-__host__ __device__ constexpr int bottom_lds_elems(int nlev)
+// LDS elements: the first level's field and defect; per coarser level the
+// field, its restriction, density and FAS source; staged models: e^phi of
+// every level's field.  Sides 4 << (nlev - 1 - q), q < nlev.
+template <class T, class M>
+constexpr int bottom_lds_elems(int nlev)
 {
     int e = 0;
     for (int q = 0; q < nlev; ++q) {
         const int n = 4 << (nlev - 1 - q);
-        e += 4 * n * n * n;
+        e += ((q == 0 ? 2 : 4) + (StageOp<T, M>::kStaged ? 1 : 0)) * n * n * n;
     }
     return e;
 }
 
-// PW: the prolongation's weights (k_prolong_correct).
-template <class T, class M, bool FW, int PW = 0>
-__global__ __launch_bounds__(bottom_threads<T>()) void k_bottom_cycle(M m, BottomArgs<T> a)
+// Value of lane `lane ^ ...` patterns on the 4^3 grid in one wave (lane = 16 i
+// + 4 j + k): the k neighbours by a quad permutation, the j neighbours by a
+// rotation of the 16-lane row, the i neighbours through the LDS crossbar.
+// CTRL: DPP control word.
+template <int CTRL>
+__device__ __forceinline__ float lane_move(float v)
 {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+template <int CTRL>
+__device__ __forceinline__ double lane_move(double v)
+{
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
+}
+// order x-, x+, y-, y+, z-, z+ (x = i); every lane of the wave must call it
+template <class T>
+__device__ __forceinline__ void lane_neighbours(T v, int lane, T nb[6])
+{
+    nb[0] = __shfl(v, (lane - 16) & 63, 64);
+    nb[1] = __shfl(v, (lane + 16) & 63, 64);
+    nb[2] = lane_move<0x124>(v);  // row_ror:4: lane takes lane - 4 of its row
+    nb[3] = lane_move<0x12c>(v);  // row_ror:12
+    nb[4] = lane_move<0x93>(v);   // quad_perm [3, 0, 1, 2]
+    nb[5] = lane_move<0x39>(v);   // quad_perm [1, 2, 3, 0]
+}
+
+// nu red-black sweeps on the 4^3 grid in one wave64, one cell per lane, all in
+// registers.  Once a sweep leaves every value as it was, the remaining sweeps
+// would too, and are skipped (their safeguard activations, those of that
+// sweep again, are added).  Returns the lane's value.
+template <class T, class M>
+__device__ __forceinline__ T coarsest_sweeps(const M& m, T ih2, T p, T e, T s, int nu,
+                                             const double* exptab, unsigned& hits)
+{
+    using SO = StageOp<T, M>;
+    const int lane = threadIdx.x & 63;
+    const int par = ((lane >> 4) + (lane >> 2) + lane) & 1;
+    T ep = SO::stage(p, exptab);
+    for (int it = 0; it < nu; ++it) {
+        bool moved = false;
+        unsigned h = 0;
+#pragma unroll
+        for (int colour = 0; colour < 2; ++colour) {
+            T nb[6], enb[6];
+            lane_neighbours(p, lane, nb);
+            if constexpr (SO::kStaged) lane_neighbours(ep, lane, enb);
+            if (par == colour) {
+                T L, D;
+                SO::eval(m, p, nb, ep, enb, e, ih2, L, D);
+                if constexpr (M::kGuard) h += m.guarded(p, e);
+                const T v = p - m.limit(gs_step(L - s, D));
+                moved = moved || v != p;
+                p = v;
+                if constexpr (SO::kStaged) ep = SO::stage(p, exptab);
+            }
+        }
+        hits += h;
+        if (__ballot(moved) == 0) {
+            hits += h * (unsigned)(nu - 1 - it);
+            break;
+        }
+    }
+    return p;
+}
+
+// PW: the prolongation's weights (k_prolong_correct).
+template <class T, class M, int NLEV, bool FW, int PW = 0>
+__global__ __launch_bounds__((bottom_threads<T, M>())) void k_bottom_cycle(M m, BottomArgs<T> a)
+{
+    using SO = StageOp<T, M>;
+    constexpr bool STAGED = SO::kStaged;
+    constexpr int NT = bottom_threads<T, M>();
+    constexpr int N0 = 4 << (NLEV - 1), N3 = N0 * N0 * N0;
     extern __shared__ __align__(16) unsigned char smem_raw[];
+    __shared__ double exptab[SO::kTable ? kExpTable : 1];
     T* base = reinterpret_cast<T*>(smem_raw);
     const int tid = threadIdx.x;
-    constexpr int NT = bottom_threads<T>();
-    const int nlev = a.nlev;
-    // level q: phi, eta, sig, then aux (first level: the fine defect; coarser
-    // levels: phihat)
-    T *phi[kBottomMaxLevels], *eta[kBottomMaxLevels], *sig[kBottomMaxLevels],
-        *aux[kBottomMaxLevels];
-    int side[kBottomMaxLevels];
+    T *phi[NLEV], *ex[NLEV], *eta[NLEV], *sig[NLEV], *hat[NLEV];
+    T* dfine = base;  // the defect of the level being restricted
     {
-        int off = 0;
-        for (int q = 0; q < kBottomMaxLevels; ++q) {
-            const int n = q < nlev ? 4 << (nlev - 1 - q) : 0;
-            const int n3 = n * n * n;
-            side[q] = n;
+        int off = N3;
+#pragma unroll
+        for (int q = 0; q < NLEV; ++q) {
+            const int n3 = N3 >> (3 * q);
             phi[q] = base + off;
-            eta[q] = base + off + n3;
-            sig[q] = base + off + 2 * n3;
-            aux[q] = base + off + 3 * n3;
-            off += 4 * n3;
+            off += n3;
+            ex[q] = base + off;
+            if (STAGED) off += n3;
+            eta[q] = sig[q] = hat[q] = nullptr;
+            if (q > 0) {
+                eta[q] = base + off;
+                sig[q] = base + off + n3;
+                hat[q] = base + off + 2 * n3;
+                off += 3 * n3;
+            }
         }
     }
-    {
-        const int n3 = side[0] * side[0] * side[0];
-        for (int c = tid; c < n3; c += NT) {
-            phi[0][c] = a.phi0[c];
-            eta[0][c] = a.eta[0][c];
-            sig[0][c] = a.sigma0 ? a.sigma0[c] : T(0);
-        }
-        for (int q = 1; q < nlev; ++q) {
-            const int m3 = side[q] * side[q] * side[q];
-            for (int c = tid; c < m3; c += NT) eta[q][c] = a.eta[q][c];
-        }
+    if constexpr (SO::kTable) {
+        exp_table_fill(exptab);
+        __syncthreads();
     }
+    // cell t of a colour's list on a side-n grid (t < n^3 / 2)
+    auto cell_of = [](int n, int t, int colour, int& i, int& j, int& k)
+        __attribute__((always_inline)) {
+        const int ln = 31 - __builtin_clz(n);
+        const int kk = t & ((n >> 1) - 1);
+        j = (t >> (ln - 1)) & (n - 1);
+        i = t >> (2 * ln - 1);
+        k = 2 * kk + ((i + j + colour) & 1);
+    };
+    // operator of cell (i, j, k) of level q's field
+    auto oper = [&](int q, int n, int i, int j, int k, T e, T ih2, T& p, T& L, T& D)
+        __attribute__((always_inline)) {
+        const int w = n - 1, r = (i * n + j) * n;
+        const int c = r + k;
+        const int o[6] = {(((i - 1) & w) * n + j) * n + k, (((i + 1) & w) * n + j) * n + k,
+                          (i * n + ((j - 1) & w)) * n + k, (i * n + ((j + 1) & w)) * n + k,
+                          r + ((k - 1) & w), r + ((k + 1) & w)};
+        T nb[6], enb[6];
+#pragma unroll
+        for (int f = 0; f < 6; ++f) nb[f] = phi[q][o[f]];
+        p = phi[q][c];
+        T ep = T(0);
+        if constexpr (STAGED) {
+#pragma unroll
+            for (int f = 0; f < 6; ++f) enb[f] = ex[q][o[f]];
+            ep = ex[q][c];
+        }
+        SO::eval(m, p, nb, ep, enb, e, ih2, L, D);
+    };
+    auto put = [&](int q, int c, T v) __attribute__((always_inline)) {
+        phi[q][c] = v;
+        if constexpr (STAGED) ex[q][c] = SO::stage(v, exptab);
+    };
+
+    // the first level's cells of this thread: density and source, per colour
+    constexpr int PER = (N3 / 2 + NT - 1) / NT;
+    T eta0[2][PER], sig0[2][PER];
+#pragma unroll
+    for (int colour = 0; colour < 2; ++colour)
+#pragma unroll
+        for (int r = 0; r < PER; ++r) {
+            const int t = min(tid + r * NT, N3 / 2 - 1);
+            int i, j, k;
+            cell_of(N0, t, colour, i, j, k);
+            const int c = (i * N0 + j) * N0 + k;
+            eta0[colour][r] = a.eta[0][c];
+            sig0[colour][r] = a.sigma0 ? a.sigma0[c] : T(0);
+        }
+    for (int c = tid; c < N3; c += NT) put(0, c, a.phi0[c]);
+#pragma unroll
+    for (int q = 1; q < NLEV; ++q)
+        for (int c = tid; c < (N3 >> (3 * q)); c += NT) eta[q][c] = a.eta[q][c];
     __syncthreads();
+    if (a.from_rr) {
+#pragma unroll
+        for (int colour = 0; colour < 2; ++colour)
+#pragma unroll
+            for (int r = 0; r < PER; ++r) {
+                int i, j, k;
+                cell_of(N0, min(tid + r * NT, N3 / 2 - 1), colour, i, j, k);
+                T p, L, D;
+                oper(0, N0, i, j, k, eta0[colour][r], a.ih2[0], p, L, D);
+                sig0[colour][r] = L - sig0[colour][r];
+            }
+        __syncthreads();
+    }
     unsigned hits = 0;
 
-    // one colour of level q; cells t = tid, tid + stride, ...
-    auto colour_pass = [&](int q, int colour, int stride) __attribute__((always_inline)) {
-        const int n = side[q], hn = n >> 1;
-        const int total = n * n * hn;
-        T* f = phi[q];
-        const T ih2 = a.ih2[q];
-        for (int t = tid; t < total; t += stride) {
-            const int kk = t % hn, r = t / hn;
-            const int j = r % n, i = r / n;
-            const int k = 2 * kk + ((i + j + colour) & 1);
-            T nb[6];
-            const T p = gather(f, n, i, j, k, nb);
-            const long c = cell(n, i, j, k);
-            T L, D;
-            const T e = eta[q][c];
-            m.op(p, nb, e, ih2, L, D);
-            if constexpr (M::kGuard) hits += m.guarded(p, e);
-            const T eps = L - sig[q][c];
-            f[c] = p - m.limit(eps / D);
+    // f(cell, density, source) for this thread's cells of one colour of level q
+    auto each = [&](auto qc, int colour, auto&& f) __attribute__((always_inline)) {
+        constexpr int q = decltype(qc)::value, n = N0 >> q, half = n * n * n / 2;
+        if constexpr (q == 0) {
+#pragma unroll
+            for (int r = 0; r < PER; ++r)
+                if ((r + 1) * NT <= half || tid + r * NT < half) {
+                    int i, j, k;
+                    cell_of(n, tid + r * NT, colour, i, j, k);
+                    f(i, j, k, eta0[colour][r], sig0[colour][r]);
+                }
+        } else {
+            static_assert(half <= NT, "one cell per thread");
+            if (tid < half) {
+                int i, j, k;
+                cell_of(n, tid, colour, i, j, k);
+                const int c = (i * n + j) * n + k;
+                f(i, j, k, eta[q][c], sig[q][c]);
+            }
         }
     };
-    auto halfsweep = [&](int q, int colour) __attribute__((always_inline)) {
-        colour_pass(q, colour, NT);
-        __syncthreads();
+    auto sweep = [&](auto qc) __attribute__((always_inline)) {
+        constexpr int q = decltype(qc)::value, n = N0 >> q;
+#pragma unroll
+        for (int colour = 0; colour < 2; ++colour) {
+            each(qc, colour, [&](int i, int j, int k, T e, T s) __attribute__((always_inline)) {
+                T p, L, D;
+                oper(q, n, i, j, k, e, a.ih2[q], p, L, D);
+                if constexpr (M::kGuard) hits += m.guarded(p, e);
+                put(q, (i * n + j) * n + k, p - m.limit(gs_step(L - s, D)));
+            });
+            __syncthreads();
+        }
     };
 
-    auto descend = [&](int q) __attribute__((always_inline)) {
-        const int nf = side[q], nc = nf >> 1;
-        const int c3 = nc * nc * nc;
-        const T ih2 = a.ih2[q];
-        T* pc_ = phi[q + 1];
-        T* ph_ = aux[q + 1];
-        T* rr = sig[q + 1];  // the restricted defect, then Sigma in place
-        if constexpr (FW) {
-            // the fine defect into the first level's buffer (nf^3 <= its size)
-            T* dfine = aux[0];
-            const int f3 = nf * nf * nf;
-            for (int c = tid; c < f3; c += NT) {
-                const int k = c % nf, r = c / nf;
-                const int j = r % nf, i = r / nf;
-                T nb[6];
-                const T p = gather(phi[q], nf, i, j, k, nb);
-                T L, D;
-                m.op(p, nb, eta[q][c], ih2, L, D);
-                dfine[c] = L - sig[q][c];
-            }
-            __syncthreads();
-            const T w[4] = {T(0.125), T(0.375), T(0.375), T(0.125)};
-            for (int Q = tid; Q < c3; Q += NT) {
-                const int K = Q % nc, r = Q / nc;
-                const int J = r % nc, I = r / nc;
-                T sp = T(0);
+    auto descend = [&](auto qc) __attribute__((always_inline)) {
+        constexpr int q = decltype(qc)::value, nf = N0 >> q, nc = nf / 2, c3 = nc * nc * nc;
+        constexpr int lc = nc == 8 ? 3 : nc == 4 ? 2 : 1;
 #pragma unroll
-                for (int di = 0; di < 2; ++di)
+        for (int colour = 0; colour < 2; ++colour)
+            each(qc, colour, [&](int i, int j, int k, T e, T s) __attribute__((always_inline)) {
+                T p, L, D;
+                oper(q, nf, i, j, k, e, a.ih2[q], p, L, D);
+                dfine[(i * nf + j) * nf + k] = L - s;
+            });
+        __syncthreads();
+        const int K = tid & (nc - 1), J = (tid >> lc) & (nc - 1), I = tid >> (2 * lc);
+        T rr = T(0);
+        if (tid < c3) {
+            T sr = T(0), sp = T(0);
 #pragma unroll
-                    for (int dj = 0; dj < 2; ++dj)
+            for (int di = 0; di < 2; ++di)
 #pragma unroll
-                        for (int dk = 0; dk < 2; ++dk)
-                            sp += phi[q][cell(nf, 2 * I + di, 2 * J + dj, 2 * K + dk)];
-                T sx = T(0);
+                for (int dj = 0; dj < 2; ++dj)
+#pragma unroll
+                    for (int dk = 0; dk < 2; ++dk) {
+                        const int c = ((2 * I + di) * nf + 2 * J + dj) * nf + 2 * K + dk;
+                        sr += dfine[c];
+                        sp += phi[q][c];
+                    }
+            const T pc = sp / T(8);
+            put(q + 1, tid, pc);
+            hat[q + 1][tid] = pc;
+            rr = sr / T(8);
+            if constexpr (FW) {
+                const T w[4] = {T(0.125), T(0.375), T(0.375), T(0.125)};
+                rr = T(0);
 #pragma unroll
                 for (int aa = 0; aa < 4; ++aa) {
-                    const int i = (2 * I - 1 + aa + nf) % nf;
+                    const int i = (2 * I - 1 + aa) & (nf - 1);
                     T sy = T(0);
 #pragma unroll
                     for (int bb = 0; bb < 4; ++bb) {
-                        const int j = (2 * J - 1 + bb + nf) % nf;
+                        const int j = (2 * J - 1 + bb) & (nf - 1);
                         const T* row = dfine + (i * nf + j) * nf;
                         T sz = T(0);
 #pragma unroll
-                        for (int cc = 0; cc < 4; ++cc) sz += w[cc] * row[(2 * K - 1 + cc + nf) % nf];
+                        for (int cc = 0; cc < 4; ++cc) sz += w[cc] * row[(2 * K - 1 + cc) & (nf - 1)];
                         sy += w[bb] * sz;
                     }
-                    sx += w[aa] * sy;
+                    rr += w[aa] * sy;
                 }
-                const T pcv = sp / T(8);
-                pc_[Q] = pcv;
-                ph_[Q] = pcv;
-                rr[Q] = sx;
-            }
-        } else {
-            for (int Q = tid; Q < c3; Q += NT) {
-                const int K = Q % nc, r = Q / nc;
-                const int J = r % nc, I = r / nc;
-                T sr = T(0), sp = T(0);
-#pragma unroll
-                for (int di = 0; di < 2; ++di)
-#pragma unroll
-                    for (int dj = 0; dj < 2; ++dj)
-#pragma unroll
-                        for (int dk = 0; dk < 2; ++dk) {
-                            const int i = 2 * I + di, j = 2 * J + dj, k = 2 * K + dk;
-                            const long c = cell(nf, i, j, k);
-                            T nb[6];
-                            const T p = gather(phi[q], nf, i, j, k, nb);
-                            T L, D;
-                            m.op(p, nb, eta[q][c], ih2, L, D);
-                            sr += L - sig[q][c];
-                            sp += p;
-                        }
-                const T pcv = sp / T(8);
-                pc_[Q] = pcv;
-                ph_[Q] = pcv;
-                rr[Q] = sr / T(8);
             }
         }
         __syncthreads();
-        // Sigma_c = L_c(phi_c) - rr_c, cell by cell in place
-        const T ih2c = a.ih2[q + 1];
-        for (int Q = tid; Q < c3; Q += NT) {
-            const int K = Q % nc, r = Q / nc;
-            const int J = r % nc, I = r / nc;
-            T nb[6];
-            const T p = gather(pc_, nc, I, J, K, nb);
-            T L, D;
-            m.op(p, nb, eta[q + 1][Q], ih2c, L, D);
-            rr[Q] = L - rr[Q];
+        // Sigma_c = L_c(phi_c) - rr
+        if (tid < c3) {
+            T p, L, D;
+            oper(q + 1, nc, I, J, K, eta[q + 1][tid], a.ih2[q + 1], p, L, D);
+            sig[q + 1][tid] = L - rr;
         }
         __syncthreads();
     };
 
-    auto prolong = [&](int q) __attribute__((always_inline)) {
-        const int nf = side[q], nc = nf >> 1;
-        const int f3 = nf * nf * nf;
+    // one thread per coarse cell updates its 8 children (see k_prolong_pairs)
+    auto prolong = [&](auto qc) __attribute__((always_inline)) {
+        constexpr int q = decltype(qc)::value, nf = N0 >> q, nc = nf / 2, c3 = nc * nc * nc;
+        constexpr int lc = nc == 8 ? 3 : nc == 4 ? 2 : 1;
         const T* co = phi[q + 1];
-        const T* ch = aux[q + 1];
+        const T* ch = hat[q + 1];
         const T w[2] = {T(0.75), T(0.25)};
-        for (int c = tid; c < f3; c += NT) {
-            const int k = c % nf, r = c / nf;
-            const int j = r % nf, i = r / nf;
-            int I[2], J[2], K[2];
-            I[0] = i >> 1;
-            I[1] = (i & 1) ? wrap_inc(I[0], nc) : wrap_dec(I[0], nc);
-            J[0] = j >> 1;
-            J[1] = (j & 1) ? wrap_inc(J[0], nc) : wrap_dec(J[0], nc);
-            K[0] = k >> 1;
-            K[1] = (k & 1) ? wrap_inc(K[0], nc) : wrap_dec(K[0], nc);
-            T wx[2] = {w[0], w[1]}, wy[2] = {w[0], w[1]}, wz[2] = {w[0], w[1]};
-            if constexpr (PW != 0) {
-                const T hp = ch[cell(nc, I[0], J[0], K[0])];
-                wx[1] = prolong_weight<PW>(hp, ch[cell(nc, I[1], J[0], K[0])]);
-                wy[1] = prolong_weight<PW>(hp, ch[cell(nc, I[0], J[1], K[0])]);
-                wz[1] = prolong_weight<PW>(hp, ch[cell(nc, I[0], J[0], K[1])]);
-                wx[0] = T(1) - wx[1];
-                wy[0] = T(1) - wy[1];
-                wz[0] = T(1) - wz[1];
-            }
-            T s = T(0);
+        if (tid < c3) {
+            const int K = tid & (nc - 1), J = (tid >> lc) & (nc - 1), I = tid >> (2 * lc);
+            const int Ix[3] = {(I - 1) & (nc - 1), I, (I + 1) & (nc - 1)};
+            const int Jy[3] = {(J - 1) & (nc - 1), J, (J + 1) & (nc - 1)};
+            const int Kz[3] = {(K - 1) & (nc - 1), K, (K + 1) & (nc - 1)};
+            T d[3][3][3];
 #pragma unroll
-            for (int aa = 0; aa < 2; ++aa)
+            for (int x = 0; x < 3; ++x)
 #pragma unroll
-                for (int bb = 0; bb < 2; ++bb)
+                for (int y = 0; y < 3; ++y)
 #pragma unroll
-                    for (int dd = 0; dd < 2; ++dd) {
-                        const long qq = cell(nc, I[aa], J[bb], K[dd]);
-                        s += wx[aa] * wy[bb] * wz[dd] * (co[qq] - ch[qq]);
+                    for (int z = 0; z < 3; ++z) {
+                        const int c = (Ix[x] * nc + Jy[y]) * nc + Kz[z];
+                        d[x][y][z] = co[c] - ch[c];
                     }
-            phi[q][c] += s;
+            T wo[3][2] = {{w[1], w[1]}, {w[1], w[1]}, {w[1], w[1]}};
+            if constexpr (PW != 0) {
+                const T hp = ch[tid];
+#pragma unroll
+                for (int sd = 0; sd < 2; ++sd) {
+                    wo[0][sd] = prolong_weight<PW>(hp, ch[(Ix[2 * sd] * nc + J) * nc + K]);
+                    wo[1][sd] = prolong_weight<PW>(hp, ch[(I * nc + Jy[2 * sd]) * nc + K]);
+                    wo[2][sd] = prolong_weight<PW>(hp, ch[(I * nc + J) * nc + Kz[2 * sd]]);
+                }
+            }
+#pragma unroll
+            for (int di = 0; di < 2; ++di)
+#pragma unroll
+                for (int dj = 0; dj < 2; ++dj)
+#pragma unroll
+                    for (int dk = 0; dk < 2; ++dk) {
+                        const int ai[2] = {1, 2 * di}, bj[2] = {1, 2 * dj}, ck[2] = {1, 2 * dk};
+                        const T wx[2] = {PW ? T(1) - wo[0][di] : w[0], PW ? wo[0][di] : w[1]};
+                        const T wy[2] = {PW ? T(1) - wo[1][dj] : w[0], PW ? wo[1][dj] : w[1]};
+                        const T wz[2] = {PW ? T(1) - wo[2][dk] : w[0], PW ? wo[2][dk] : w[1]};
+                        T s = T(0);
+#pragma unroll
+                        for (int x = 0; x < 2; ++x)
+#pragma unroll
+                            for (int y = 0; y < 2; ++y)
+#pragma unroll
+                                for (int z = 0; z < 2; ++z)
+                                    s += wx[x] * wy[y] * wz[z] * d[ai[x]][bj[y]][ck[z]];
+                        const int c = ((2 * I + di) * nf + 2 * J + dj) * nf + 2 * K + dk;
+                        put(q, c, phi[q][c] + s);
+                    }
         }
         __syncthreads();
     };
 
-    for (int q = 0; q + 1 < nlev; ++q) {
-        for (int it = 0; it < a.nu_pre; ++it) {
-            halfsweep(q, 0);
-            halfsweep(q, 1);
-        }
-        descend(q);
-    }
-    // The 4^3 grid (32 cells per colour) in the first wave alone: a wave's
-    // LDS operations complete in issue order, so between colours it needs
-    // only the fences that keep the compiler from reordering its LDS accesses
-    // and wait for its writes; the other waves wait at the barrier below.
-    if (tid < 64) {
-        for (int it = 0; it < a.nu_coarse; ++it) {
-#pragma unroll
-            for (int colour = 0; colour < 2; ++colour) {
-                colour_pass(nlev - 1, colour, 64);
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-            }
-        }
+    static_for<0, NLEV - 1>([&](auto qc) {
+        for (int it = 0; it < a.nu_pre; ++it) sweep(qc);
+        descend(qc);
+    });
+    if (tid < 64) {  // the 4^3 grid in the first wave
+        constexpr int q = NLEV - 1;
+        phi[q][tid] = coarsest_sweeps(m, a.ih2[q], phi[q][tid], eta[q][tid], sig[q][tid],
+                                      a.nu_coarse, exptab, hits);
     }
     __syncthreads();
-    for (int q = nlev - 2; q >= 0; --q) {
-        prolong(q);
-        for (int it = 0; it < a.nu_post; ++it) {
-            halfsweep(q, 0);
-            halfsweep(q, 1);
-        }
-    }
-    {
-        const int n3 = side[0] * side[0] * side[0];
-        for (int c = tid; c < n3; c += NT) a.phi0[c] = phi[0][c];
-    }
+    static_for<0, NLEV - 1>([&](auto rc) {
+        constexpr std::integral_constant<int, NLEV - 2 - decltype(rc)::value> qc{};
+        prolong(qc);
+        for (int it = 0; it < a.nu_post; ++it) sweep(qc);
+    });
+    for (int c = tid; c < N3; c += NT) a.phi0[c] = phi[0][c];
     guard_flush(m, hits);
 }
 

@@ -39,7 +39,7 @@ struct ForceTile {
 };
 using ForceTileF = ForceTile<8, 64, 32>;
 
-template <ScalarForce SF, bool POT>
+template <ScalarForce SF, bool POT, int XC>
 __global__ __launch_bounds__(kBlock) void k_force_tiled(int n, double inv2h, double c,
                                                         const double* __restrict__ field,
                                                         const double* __restrict__ pot,
@@ -47,7 +47,7 @@ __global__ __launch_bounds__(kBlock) void k_force_tiled(int n, double inv2h, dou
                                                         double* __restrict__ fy,
                                                         double* __restrict__ fz)
 {
-    using G = ForceTileF;
+    using G = ForceTile<8, 64, XC>;
     using VD = typename Vec2<double>::type;
     constexpr bool FLD = SF != ScalarForce::kNone;
     __shared__ __align__(16) double rf[FLD ? 3 : 1][FLD ? G::PLANE : 2];
@@ -162,12 +162,8 @@ __global__ __launch_bounds__(kBlock) void k_force_cells(int n, double inv2h, dou
                                                         double* __restrict__ fz)
 {
     constexpr bool FLD = SF != ScalarForce::kNone;
-    const long total = (long)n * n * n;
-    for (long q = (long)blockIdx.x * blockDim.x + threadIdx.x; q < total;
-         q += (long)gridDim.x * blockDim.x) {
-        const int k = (int)(q % n);
-        const long r = q / n;
-        const int j = (int)(r % n), i = (int)(r / n);
+    for_planes(n, n, n, [&](int i, int j, int k) __attribute__((always_inline)) {
+        const long q = cell(n, i, j, k);
         const long nb[6] = {cell(n, wrap_dec(i, n), j, k), cell(n, wrap_inc(i, n), j, k),
                             cell(n, i, wrap_dec(j, n), k), cell(n, i, wrap_inc(j, n), k),
                             cell(n, i, j, wrap_dec(k, n)), cell(n, i, j, wrap_inc(k, n))};
@@ -181,7 +177,7 @@ __global__ __launch_bounds__(kBlock) void k_force_cells(int n, double inv2h, dou
         fx[q] = a3[0];
         fy[q] = a3[1];
         fz[q] = a3[2];
-    }
+    });
 }
 
 }  // namespace isis

@@ -19,31 +19,26 @@ __global__ __launch_bounds__(kBlock) void k_restrict_fw(int nf, const T* __restr
                                                         T* __restrict__ coarse)
 {
     const int nc = nf >> 1;
-    const long total = (long)nc * nc * nc;
     const T w[4] = {T(0.125), T(0.375), T(0.375), T(0.125)};
-    for (long q = (long)blockIdx.x * blockDim.x + threadIdx.x; q < total;
-         q += (long)gridDim.x * blockDim.x) {
-        const int K = (int)(q % nc);
-        const long r = q / nc;
-        const int J = (int)(r % nc), I = (int)(r / nc);
+    for_planes(nc, nc, nc, [&](int I, int J, int K) __attribute__((always_inline)) {
         T sx = T(0);
 #pragma unroll
         for (int a = 0; a < 4; ++a) {
-            const int i = (2 * I - 1 + a + nf) % nf;
+            const int i = wrap(2 * I - 1 + a, nf);
             T sy = T(0);
 #pragma unroll
             for (int b = 0; b < 4; ++b) {
-                const int j = (2 * J - 1 + b + nf) % nf;
+                const int j = wrap(2 * J - 1 + b, nf);
                 const T* row = fine + ((long)i * nf + j) * nf;
                 T sz = T(0);
 #pragma unroll
-                for (int c = 0; c < 4; ++c) sz += w[c] * row[(2 * K - 1 + c + nf) % nf];
+                for (int c = 0; c < 4; ++c) sz += w[c] * row[wrap(2 * K - 1 + c, nf)];
                 sy += w[b] * sz;
             }
             sx += w[a] * sy;
         }
-        coarse[q] = sx;
-    }
+        coarse[cell(nc, I, J, K)] = sx;
+    });
 }
 
 // LDS-staged version: each workgroup owns a TJ x TK tile of coarse (y, z)

@@ -84,16 +84,6 @@ __device__ __forceinline__ void row_split(int it, int R, int L, int& r, int& c)
     }
 }
 
-// Compile-time loop: f(std::integral_constant<int, i>) for i in [B, E).
-template <int B, int E, class F>
-__device__ __forceinline__ void static_for(F&& f)
-{
-    if constexpr (B < E) {
-        f(std::integral_constant<int, B>{});
-        static_for<B + 1, E>(f);
-    }
-}
-
 // Shared-memory footprint of one workgroup, in bytes.
 template <class T, class M, int TB, int TY, int TZ, bool PROL = false>
 constexpr int fused_lds_bytes()

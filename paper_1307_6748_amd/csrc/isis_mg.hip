@@ -51,6 +51,14 @@ int grid_for(long work)
     return (int)std::max(1L, std::min(b, (long)kMaxGrid));
 }
 
+// Grid of a for_planes kernel: at most max_blocks workgroups.
+dim3 plane_grid(int planes, long items, int max_blocks = kMaxGrid)
+{
+    const long bx = std::max(1L, std::min((items + kBlock - 1) / kBlock, (long)max_blocks));
+    return dim3((unsigned)bx, (unsigned)std::max(1L, std::min((long)planes, max_blocks / bx)));
+}
+dim3 plane_grid(int n) { return plane_grid(n, (long)n * n); }
+
 bool is_pow2_ge(int n, int lo)
 {
     return n >= lo && (n & (n - 1)) == 0;
@@ -264,8 +272,8 @@ int launch_halfsweep(const M& m, int n, double h, T* phi, const T* eta, const T*
                      int colour, hipStream_t s, char* err)
 {
     T ih2 = (T)(1.0 / (h * h));
-    hipLaunchKernelGGL((k_halfsweep<T, M>), dim3(grid_for((long)n * n * n / 2)), dim3(kBlock), 0,
-                       s, m, n, ih2, phi, eta, sigma, colour);
+    hipLaunchKernelGGL((k_halfsweep<T, M>), plane_grid(n, (long)n * n / 2), dim3(kBlock), 0, s, m,
+                       n, ih2, phi, eta, sigma, colour);
     LAUNCH_CHECK(err, "k_halfsweep");
     return ISIS_OK;
 }
@@ -465,8 +473,7 @@ int launch_restrict_fw(int nf, const T* fine, T* coarse, hipStream_t s, char* er
         hipLaunchKernelGGL((k_restrict_fw_tiled<T>), dim3((nc / FG::TK) * (nc / FG::TJ) * (nc / FG::XC)),
                            dim3(kBlock), 0, s, nf, fine, coarse);
     else
-        hipLaunchKernelGGL((k_restrict_fw<T>), dim3(grid_for((long)nc * nc * nc)), dim3(kBlock), 0,
-                           s, nf, fine, coarse);
+        hipLaunchKernelGGL((k_restrict_fw<T>), plane_grid(nc), dim3(kBlock), 0, s, nf, fine, coarse);
     LAUNCH_CHECK(err, "k_restrict_fw");
     return ISIS_OK;
 }
@@ -514,7 +521,7 @@ int launch_descend(const M& m, int nf, double hf, const T* phi_f, const T* eta_f
                                                                eta_c, sigma_c, s, err);
         if (r) return r;
     } else if (nf >= 4) {
-        hipLaunchKernelGGL((k_defect_restrict_pairs<T, M>), dim3(grid_for(c3)), dim3(kBlock), 0, s,
+        hipLaunchKernelGGL((k_defect_restrict_pairs<T, M>), plane_grid(nc), dim3(kBlock), 0, s,
                            m, nf, ih2f, phi_f, eta_f, sigma_f, phi_c, phihat_c, rr_c, dfine);
     } else {
         if (dfine) {
@@ -529,7 +536,7 @@ int launch_descend(const M& m, int nf, double hf, const T* phi_f, const T* eta_f
         int r = launch_restrict_fw<T>(nf, dfine, rr_c, s, err);
         if (r) return r;
     }
-    hipLaunchKernelGGL((k_fas_sigma<T, M>), dim3(grid_for(c3)), dim3(kBlock), 0, s, m, nc, ih2c,
+    hipLaunchKernelGGL((k_fas_sigma<T, M>), plane_grid(nc), dim3(kBlock), 0, s, m, nc, ih2c,
                        phi_c, eta_c, rr_c, sigma_c);
     LAUNCH_CHECK(err, "k_fas_sigma");
     return ISIS_OK;
@@ -547,7 +554,7 @@ int launch_prolong(int nf, T* fine, const T* coarse, const T* coarse_hat, hipStr
                            dim3((nc / PG::TK) * (nc / PG::TJ) * (nc / PG::XC)), dim3(kBlock), 0, s,
                            nf, fine, coarse, coarse_hat);
     else if (nf >= 4)
-        hipLaunchKernelGGL((k_prolong_pairs<T, PW>), dim3(grid_for(f3 / 8)), dim3(kBlock), 0, s,
+        hipLaunchKernelGGL((k_prolong_pairs<T, PW>), plane_grid(nc), dim3(kBlock), 0, s,
                            nf, fine, coarse, coarse_hat);
     else
         hipLaunchKernelGGL((k_prolong_correct<T, PW>), dim3(grid_for(f3)), dim3(kBlock), 0, s, nf,
@@ -560,8 +567,7 @@ template <class T>
 int launch_restrict(int nf, const T* fine, T* coarse, hipStream_t s, char* err,
                     float* fine32 = nullptr)
 {
-    long c3 = (long)(nf / 2) * (nf / 2) * (nf / 2);
-    hipLaunchKernelGGL((k_restrict<T>), dim3(grid_for(c3)), dim3(kBlock), 0, s, nf, fine, coarse,
+    hipLaunchKernelGGL((k_restrict<T>), plane_grid(nf / 2), dim3(kBlock), 0, s, nf, fine, coarse,
                        fine32);
     LAUNCH_CHECK(err, "k_restrict");
     return ISIS_OK;
@@ -736,6 +742,13 @@ bool valid_desc(const isis_mg_desc* d, char* err)
     return true;
 }
 
+// Workgroups of the tiled norm and setup kernels at side n.
+int norm_blocks(int n)
+{
+    using NG = NormTileF;
+    return (int)std::min<long>(kReduceBlocks, (long)(n / NG::TZ) * (n / NG::TY) * (n / norm_planes(n)));
+}
+
 // The FP64 defect L(phi) of an n^3 level with spacing h (into res unless
 // NULL) and the sum of its squares: per-block partial sums in
 // partial[0 .. kReduceBlocks), their fixed-order total in *total (device).
@@ -744,19 +757,23 @@ int launch_defect_norm(const M& m, int n, double h, const TF* phi, const double*
                        double* res, double* partial, double* total, hipStream_t s, char* err,
                        double uscale = 1.0, double uoffset = 0.0)
 {
-    const long n3 = (long)n * n * n;
-    int g = std::min(kReduceBlocks, grid_for(n3 / 2));
+    int g;
     using NG = NormTileF;
     const bool tiled = (n & (n - 1)) == 0 && n % NG::TZ == 0 && n % NG::TY == 0 && n % NG::XC == 0;
     if (tiled) {
-        const long tiles = (long)(n / NG::TZ) * (n / NG::TY) * (n / NG::XC);
-        g = (int)std::min<long>(kReduceBlocks, tiles);
-        hipLaunchKernelGGL((k_defect_norm_tiled<TF, M>), dim3(g), dim3(kBlock), 0, s, m, n,
+        g = norm_blocks(n);
+        auto kern = n >= 256   ? k_defect_norm_tiled<TF, M, double, norm_planes(256)>
+                    : n == 128 ? k_defect_norm_tiled<TF, M, double, norm_planes(128)>
+                               : k_defect_norm_tiled<TF, M, double, norm_planes(64)>;
+        hipLaunchKernelGGL(kern, dim3(g), dim3(kBlock), 0, s, m, n, 1.0 / (h * h), uscale, uoffset,
+                           phi, eta, res, partial);
+    }
+    if (!tiled) {
+        const dim3 pg = plane_grid(n, (long)n * n / 2, kReduceBlocks);
+        g = (int)(pg.x * pg.y);
+        hipLaunchKernelGGL((k_defect_norm_pairs<TF, M>), pg, dim3(kBlock), 0, s, m, n,
                            1.0 / (h * h), uscale, uoffset, phi, eta, res, partial);
     }
-    if (!tiled)
-        hipLaunchKernelGGL((k_defect_norm_pairs<TF, M>), dim3(g), dim3(kBlock), 0, s, m, n,
-                           1.0 / (h * h), uscale, uoffset, phi, eta, res, partial);
     LAUNCH_CHECK(err, "k_defect_norm");
     hipLaunchKernelGGL(k_reduce, dim3(1), dim3(kBlock), 0, s, partial, g, total);
     LAUNCH_CHECK(err, "k_reduce");
@@ -791,14 +808,15 @@ inline bool norm_tiled(int n)
 template <class M>
 int fine_rms_fp32(isis_mg* H, const M& m, const float* phi, const float* eta, double* out)
 {
-    using NG = NormTileF;
     const int n = H->d.N;
     const long n3 = (long)n * n * n;
     const double h = H->L64[0].h;
-    const long tiles = (long)(n / NG::TZ) * (n / NG::TY) * (n / NG::XC);
-    const int g = (int)std::min<long>(kReduceBlocks, tiles);
-    hipLaunchKernelGGL((k_defect_norm_tiled<float, M, float>), dim3(g), dim3(kBlock), 0, H->s, m,
-                       n, 1.0 / (h * h), 1.0, 0.0, phi, eta, nullptr, H->partial);
+    const int g = norm_blocks(n);
+    auto kern = n >= 256   ? k_defect_norm_tiled<float, M, float, norm_planes(256)>
+                : n == 128 ? k_defect_norm_tiled<float, M, float, norm_planes(128)>
+                           : k_defect_norm_tiled<float, M, float, norm_planes(64)>;
+    hipLaunchKernelGGL(kern, dim3(g), dim3(kBlock), 0, H->s, m, n, 1.0 / (h * h), 1.0, 0.0, phi, eta,
+                       nullptr, H->partial);
     LAUNCH_CHECK(H->err, "k_defect_norm_tiled");
     hipLaunchKernelGGL(k_reduce, dim3(1), dim3(kBlock), 0, H->s, H->partial, g, H->scal);
     LAUNCH_CHECK(H->err, "k_reduce");
@@ -897,37 +915,42 @@ int timed_sweeps(isis_mg* H, const M& m, LevP<T>& f, int l, int count, const T* 
     return timed_block<T, M>(H, m, f, l, count, nullptr, nullptr);
 }
 
+template <class T, class M, int NLEV>
+int launch_bottom_levels(isis_mg* H, const M& m, const BottomArgs<T>& a)
+{
+    constexpr int PWc = weighted_code<T, M>();
+    constexpr int lds = bottom_lds_elems<T, M>(NLEV) * (int)sizeof(T);
+    const bool pw = H->pw && PWc != 0;
+    auto kern = H->fw ? (pw ? k_bottom_cycle<T, M, NLEV, true, PWc> : k_bottom_cycle<T, M, NLEV, true, 0>)
+                      : (pw ? k_bottom_cycle<T, M, NLEV, false, PWc> : k_bottom_cycle<T, M, NLEV, false, 0>);
+    static std::atomic<unsigned> lds_done[4];  // per instantiation: devices set up
+    HIP_TRY(H->err, ensure_dynamic_lds((const void*)kern, lds, lds_done[(H->fw ? 1 : 0) + (pw ? 2 : 0)]));
+    hipLaunchKernelGGL(kern, dim3(1), dim3(bottom_threads<T, M>()), lds, H->s, m, a);
+    LAUNCH_CHECK(H->err, "k_bottom_cycle");
+    return ISIS_OK;
+}
+
 // Levels l .. nlev-1 of the V-cycle in one launch of k_bottom_cycle.
 template <class T, class M>
 int launch_bottom(isis_mg* H, const M& m, LevP<T>* L, int l, double* updates)
 {
     const isis_mg_desc& d = H->d;
     BottomArgs<T> a{};
-    a.nlev = H->nlev - l;
+    const int nlev = H->nlev - l;
     a.nu_pre = d.nu_pre;
     a.nu_post = H->nu_post;
     a.nu_coarse = d.nu_coarse;
     a.phi0 = L[l].phi;
     a.sigma0 = L[l].sigma;
-    for (int q = 0; q < a.nlev; ++q) {
+    for (int q = 0; q < nlev; ++q) {
         const LevP<T>& v = L[l + q];
         a.eta[q] = v.eta;
         a.ih2[q] = (T)(1.0 / (v.h * v.h));
         const double n3 = (double)v.n * v.n * v.n;
-        *updates += (q + 1 < a.nlev ? d.nu_pre + H->nu_post : d.nu_coarse) * n3;
+        *updates += (q + 1 < nlev ? d.nu_pre + H->nu_post : d.nu_coarse) * n3;
     }
-    constexpr int PWc = weighted_code<T, M>();
-    const bool pw = H->pw && PWc != 0;
-    auto kern = H->fw ? (pw ? k_bottom_cycle<T, M, true, PWc> : k_bottom_cycle<T, M, true, 0>)
-                      : (pw ? k_bottom_cycle<T, M, false, PWc> : k_bottom_cycle<T, M, false, 0>);
-    static std::atomic<unsigned> lds_done[4];  // per instantiation: devices set up
-    HIP_TRY(H->err, ensure_dynamic_lds((const void*)kern,
-                                       bottom_lds_elems(kBottomMaxLevels) * (int)sizeof(T),
-                                       lds_done[(H->fw ? 1 : 0) + (pw ? 2 : 0)]));
-    hipLaunchKernelGGL(kern, dim3(1), dim3(bottom_threads<T>()),
-                       bottom_lds_elems(a.nlev) * (int)sizeof(T), H->s, m, a);
-    LAUNCH_CHECK(H->err, "k_bottom_cycle");
-    return ISIS_OK;
+    return nlev == 3 ? launch_bottom_levels<T, M, 3>(H, m, a)
+                     : launch_bottom_levels<T, M, 2>(H, m, a);
 }
 
 template <class T, class M>
@@ -1033,9 +1056,11 @@ int solve_impl(isis_mg* H, const M64& m64, const M32& m32, const isis_model_para
         cold_pending = cold32;
         // one pass over the FP64 density: cold start, its copies, the
         // density's FP32 copy and first restriction, and both sums
-        const long tiles = (long)(N / NG::TZ) * (N / NG::TY) * (N / NG::XC);
-        const int g = (int)std::min<long>(kReduceBlocks, tiles);
-        hipLaunchKernelGGL((k_setup_tiled<M64>), dim3(g), dim3(kBlock), 0, H->s, m64, N,
+        const int g = norm_blocks(N);
+        auto kern = N >= 256   ? k_setup_tiled<M64, norm_planes(256)>
+                    : N == 128 ? k_setup_tiled<M64, norm_planes(128)>
+                               : k_setup_tiled<M64, norm_planes(64)>;
+        hipLaunchKernelGGL(kern, dim3(g), dim3(kBlock), 0, H->s, m64, N,
                            1.0 / (h0 * h0), density, cold_pending ? nullptr : cold,
                            cold32 ? H->L32[0].phi : nullptr,
                            M32::kVar, -shift32 * M32::kVar, mixed ? H->L32[0].eta : nullptr,
@@ -1362,13 +1387,17 @@ int launch_force_t(int n, double h, double c, const double* field, const double*
     using FG = ForceTileF;
     const double inv2h = 0.5 / h;
     if ((n & (n - 1)) == 0 && n % FG::TZ == 0 && n % FG::TY == 0 && n % FG::XC == 0) {
-        const long tiles = (long)(n / FG::TZ) * (n / FG::TY) * (n / FG::XC);
+        // planes per tile as for the norms: few tiles at 64^3 and 128^3
+        const int xc = norm_planes(n);
+        const long tiles = (long)(n / FG::TZ) * (n / FG::TY) * (n / xc);
         const int g = (int)std::min<long>(8192, tiles);
-        hipLaunchKernelGGL((k_force_tiled<SF, POT>), dim3(g), dim3(kBlock), 0, s, n, inv2h, c,
-                           field, pot, fx, fy, fz);
+        auto kern = xc == 32  ? k_force_tiled<SF, POT, norm_planes(256)>
+                    : xc == 8 ? k_force_tiled<SF, POT, norm_planes(128)>
+                              : k_force_tiled<SF, POT, norm_planes(64)>;
+        hipLaunchKernelGGL(kern, dim3(g), dim3(kBlock), 0, s, n, inv2h, c, field, pot, fx, fy, fz);
     } else {
-        hipLaunchKernelGGL((k_force_cells<SF, POT>), dim3(grid_for((long)n * n * n)),
-                           dim3(kBlock), 0, s, n, inv2h, c, field, pot, fx, fy, fz);
+        hipLaunchKernelGGL((k_force_cells<SF, POT>), plane_grid(n), dim3(kBlock),
+                           0, s, n, inv2h, c, field, pot, fx, fy, fz);
     }
     LAUNCH_CHECK(err, "k_force");
     return ISIS_OK;
@@ -1754,8 +1783,8 @@ int isis_op_defect(const isis_model_params* p, double a, int n, double h, const 
     if (!ptrs_aligned({phi, eta, sigma, out})) return ISIS_ERR_INVALID_ARG;
     return with_model<double>(*p, a, [&](auto m) {
         using M = decltype(m);
-        hipLaunchKernelGGL((k_defect<double, M>), dim3(grid_for((long)n * n * n)), dim3(kBlock),
-                           0, (hipStream_t)stream, m, n, 1.0 / (h * h), phi, eta, sigma, out);
+        hipLaunchKernelGGL((k_defect<double, M>), plane_grid(n), dim3(kBlock), 0,
+                           (hipStream_t)stream, m, n, 1.0 / (h * h), phi, eta, sigma, out);
         LAUNCH_CHECK(g_err, "k_defect");
         return (int)ISIS_OK;
     });

@@ -4,12 +4,14 @@
 // deterministic norm reductions and precision conversions.
 //
 // Grid layout: n^3 cells, index (i*n + j)*n + k with z (k) contiguous,
-// periodic.  Every kernel is a grid-stride loop over its output cells, so any
-// grid size is safe; launches use 256-thread blocks (four wave64s).
+// periodic.  Every kernel is a grid-stride loop over its output cells
+// (for_planes where it needs their coordinates), so any grid size is safe;
+// launches use 256-thread blocks (four wave64s).
 #pragma once
 #include <hip/hip_runtime.h>
 
 #include <atomic>
+#include <type_traits>
 
 #include "device.hpp"
 #include "model.hpp"
@@ -57,9 +59,56 @@ struct Vec2 {
 
 __device__ __forceinline__ int wrap_dec(int i, int n) { return i == 0 ? n - 1 : i - 1; }
 __device__ __forceinline__ int wrap_inc(int i, int n) { return i == n - 1 ? 0 : i + 1; }
+__device__ __forceinline__ int wrap(int i, int n) { return i < 0 ? i + n : i >= n ? i - n : i; }
 __device__ __forceinline__ long cell(int n, int i, int j, int k)
 {
     return ((long)i * n + j) * n + k;
+}
+
+// Compile-time loop: f(std::integral_constant<int, i>) for i in [B, E).
+template <int B, int E, class F>
+__device__ __forceinline__ void static_for(F&& f)
+{
+    if constexpr (B < E) {
+        f(std::integral_constant<int, B>{});
+        static_for<B + 1, E>(f);
+    }
+}
+
+// The Newton-Gauss-Seidel step eps / D of the per-level kernels: the quotient
+// in single precision, in double precision the product with the refined
+// reciprocal (within an ulp of the quotient, a third of its instructions).
+template <class T>
+__device__ __forceinline__ T gs_step(T eps, T D)
+{
+    if constexpr (sizeof(T) == 4)
+        return eps / D;
+    else
+        return eps * recip(D);
+}
+
+// Visits the items (i, j, k) of a [planes][rows][cols] grid: planes over
+// gridDim.y, the rows x cols items of a plane over gridDim.x, both strided, so
+// any grid size is safe.  One float product splits a plane's index (exact up
+// to 2^23 items with the correction by one) where flat 64-bit indices cost
+// every item two 64-bit divisions: 128^3 in double precision, symmetron, a
+// half-sweep 12.0 -> 11.8 us (it waits for the caches).
+__device__ __forceinline__ int split_row(int t, int cols, float inv)
+{
+    const int j = (int)((float)t * inv);
+    const int k = t - j * cols;
+    return j + (k < 0 ? -1 : k >= cols ? 1 : 0);
+}
+template <class F>
+__device__ __forceinline__ void for_planes(int planes, int rows, int cols, F&& f)
+{
+    const float inv = 1.0f / (float)cols;
+    const int items = rows * cols;
+    for (int i = blockIdx.y; i < planes; i += gridDim.y)
+        for (int t = blockIdx.x * kBlock + threadIdx.x; t < items; t += gridDim.x * kBlock) {
+            const int j = split_row(t, cols, inv);
+            f(i, j, t - j * cols);
+        }
 }
 
 // Gather the cell value and its six periodic neighbours (x-, x+, y-, y+, z-, z+).
@@ -97,26 +146,19 @@ __global__ __launch_bounds__(kBlock) void k_halfsweep(M m, int n, T ih2, T* __re
                                                       const T* __restrict__ eta,
                                                       const T* __restrict__ sigma, int colour)
 {
-    const int hn = n >> 1;
-    const long total = (long)n * n * hn;
     unsigned hits = 0;
-    for (long t = (long)blockIdx.x * blockDim.x + threadIdx.x; t < total;
-         t += (long)gridDim.x * blockDim.x) {
-        int kk = (int)(t % hn);
-        long r = t / hn;
-        int j = (int)(r % n);
-        int i = (int)(r / n);
-        int k = 2 * kk + ((i + j + colour) & 1);
+    for_planes(n, n, n >> 1, [&](int i, int j, int kk) __attribute__((always_inline)) {
+        const int k = 2 * kk + ((i + j + colour) & 1);
         T nb[6];
         T p = gather(phi, n, i, j, k, nb);
         long c = cell(n, i, j, k);
         T L, D;
         const T e = eta[c];
+        const T s = sigma ? sigma[c] : T(0);
         m.op(p, nb, e, ih2, L, D);
         if constexpr (M::kGuard) hits += m.guarded(p, e);
-        T eps = L - (sigma ? sigma[c] : T(0));
-        phi[c] = p - m.limit(eps / D);
-    }
+        phi[c] = p - m.limit(gs_step(L - s, D));
+    });
     guard_flush(m, hits);
 }
 
@@ -126,19 +168,14 @@ __global__ __launch_bounds__(kBlock) void k_defect(M m, int n, T ih2, const T* _
                                                    const T* __restrict__ eta,
                                                    const T* __restrict__ sigma, T* __restrict__ out)
 {
-    const long total = (long)n * n * n;
-    for (long c = (long)blockIdx.x * blockDim.x + threadIdx.x; c < total;
-         c += (long)gridDim.x * blockDim.x) {
-        int k = (int)(c % n);
-        long r = c / n;
-        int j = (int)(r % n);
-        int i = (int)(r / n);
+    for_planes(n, n, n, [&](int i, int j, int k) __attribute__((always_inline)) {
+        const long c = cell(n, i, j, k);
         T nb[6];
         T p = gather(phi, n, i, j, k, nb);
         T L, D;
         m.op(p, nb, eta[c], ih2, L, D);
         out[c] = L - (sigma ? sigma[c] : T(0));
-    }
+    });
 }
 
 // Block sum of a double (wave64 shuffles, then across the block's waves).
@@ -157,42 +194,6 @@ __device__ __forceinline__ double block_sum(double v)
     return s;
 }
 
-// Finest-level defect in double precision with per-block partial sums of r^2
-// (and of r, for diagnostics).  TF is the field's storage type: double, or
-// float for the FP64 defect of the FP32 iterate in mixed precision.  The model
-// M works in double.  res may be NULL.
-template <class TF, class M>
-__global__ __launch_bounds__(kBlock) void k_defect_norm(M m, int n, double ih2,
-                                                        const TF* __restrict__ phi,
-                                                        const double* __restrict__ eta,
-                                                        double* __restrict__ res,
-                                                        double* __restrict__ partial)
-{
-    const long total = (long)n * n * n;
-    double acc = 0.0;
-    for (long c = (long)blockIdx.x * blockDim.x + threadIdx.x; c < total;
-         c += (long)gridDim.x * blockDim.x) {
-        int k = (int)(c % n);
-        long r = c / n;
-        int j = (int)(r % n);
-        int i = (int)(r / n);
-        double nb[6];
-        nb[0] = (double)phi[cell(n, wrap_dec(i, n), j, k)];
-        nb[1] = (double)phi[cell(n, wrap_inc(i, n), j, k)];
-        nb[2] = (double)phi[cell(n, i, wrap_dec(j, n), k)];
-        nb[3] = (double)phi[cell(n, i, wrap_inc(j, n), k)];
-        nb[4] = (double)phi[cell(n, i, j, wrap_dec(k, n))];
-        nb[5] = (double)phi[cell(n, i, j, wrap_inc(k, n))];
-        double p = (double)phi[c];
-        double L, D;
-        m.op(p, nb, eta[c], ih2, L, D);
-        if (res) res[c] = L;
-        acc += L * L;
-    }
-    double s = block_sum(acc);
-    if (threadIdx.x == 0) partial[blockIdx.x] = s;
-}
-
 // Sum of a field (for the mean of the singular linear problem).
 template <class T>
 __global__ __launch_bounds__(kBlock) void k_sum(long total, const T* __restrict__ f,
@@ -206,13 +207,12 @@ __global__ __launch_bounds__(kBlock) void k_sum(long total, const T* __restrict_
     if (threadIdx.x == 0) partial[blockIdx.x] = s;
 }
 
-// out[0] = sum of partial[0..count) in a fixed order (one block).
-__global__ __launch_bounds__(kBlock) void k_reduce(const double* __restrict__ partial, int count,
-                                                   double* __restrict__ out)
+// Sum of partial[0..count) in a fixed order, by one block; valid in thread 0.
+// Each thread sums fixed runs of 8 consecutive partials (loads issued
+// together, added in order): deterministic, and a few load latencies instead
+// of count / blockDim dependent ones.
+__device__ __forceinline__ double reduce_runs(const double* __restrict__ partial, int count)
 {
-    // Each thread sums fixed runs of 8 consecutive partials (loads issued
-    // together, added in order): deterministic, and a few load latencies
-    // instead of count / blockDim dependent ones.
     double acc = 0.0;
     for (int q0 = threadIdx.x * 8; q0 < count; q0 += blockDim.x * 8) {
         double v[8];
@@ -221,7 +221,12 @@ __global__ __launch_bounds__(kBlock) void k_reduce(const double* __restrict__ pa
 #pragma unroll
         for (int j = 0; j < 8; ++j) acc += v[j];
     }
-    double s = block_sum(acc);
+    return block_sum(acc);
+}
+__global__ __launch_bounds__(kBlock) void k_reduce(const double* __restrict__ partial, int count,
+                                                   double* __restrict__ out)
+{
+    const double s = reduce_runs(partial, count);
     if (threadIdx.x == 0) out[0] = s;
 }
 
@@ -243,13 +248,7 @@ __global__ __launch_bounds__(kBlock) void k_restrict(int nf, const T* __restrict
                                                      float* __restrict__ fine32)
 {
     const int nc = nf >> 1;
-    const long total = (long)nc * nc * nc;
-    for (long q = (long)blockIdx.x * blockDim.x + threadIdx.x; q < total;
-         q += (long)gridDim.x * blockDim.x) {
-        int K = (int)(q % nc);
-        long r = q / nc;
-        int J = (int)(r % nc);
-        int I = (int)(r / nc);
+    for_planes(nc, nc, nc, [&](int I, int J, int K) __attribute__((always_inline)) {
         T s = T(0);
 #pragma unroll
         for (int di = 0; di < 2; ++di)
@@ -262,8 +261,8 @@ __global__ __launch_bounds__(kBlock) void k_restrict(int nf, const T* __restrict
                     s += v;
                     if (fine32) fine32[c] = (float)v;  // the fine level's FP32 copy, same pass
                 }
-        coarse[q] = s / T(8);
-    }
+        coarse[cell(nc, I, J, K)] = s / T(8);
+    });
 }
 
 // FAS descent, first half (Sec. 3.2): for each coarse cell, the fine defect
@@ -317,19 +316,14 @@ __global__ __launch_bounds__(kBlock) void k_fas_sigma(M m, int nc, T ih2,
                                                       const T* __restrict__ rr_c,
                                                       T* __restrict__ sigma_c)
 {
-    const long total = (long)nc * nc * nc;
-    for (long q = (long)blockIdx.x * blockDim.x + threadIdx.x; q < total;
-         q += (long)gridDim.x * blockDim.x) {
-        int K = (int)(q % nc);
-        long r = q / nc;
-        int J = (int)(r % nc);
-        int I = (int)(r / nc);
+    for_planes(nc, nc, nc, [&](int I, int J, int K) __attribute__((always_inline)) {
+        const long q = cell(nc, I, J, K);
         T nb[6];
         T p = gather(phi_c, nc, I, J, K, nb);
         T L, D;
         m.op(p, nb, eta_c[q], ih2, L, D);
         sigma_c[q] = L - rr_c[q];
-    }
+    });
 }
 
 // Prolongation weight of the other coarse cell N along one axis (the

@@ -27,12 +27,13 @@ __global__ __launch_bounds__(kBlock) void k_defect_restrict_pairs(
     using V = typename Vec2<T>::type;
     using SO = StageOp<T, M>;
     const int nc = nf >> 1;
-    const long total = (long)nc * nc * nc;
-    for (long q = (long)blockIdx.x * blockDim.x + threadIdx.x; q < total;
-         q += (long)gridDim.x * blockDim.x) {
-        const int K = (int)(q % nc);
-        const long r = q / nc;
-        const int J = (int)(r % nc), I = (int)(r / nc);
+    const float inv = 1.0f / (float)nc;
+    // (the loops written out: through for_planes the compiler contracts the
+    // defect's sums otherwise, other last bits in single precision)
+    for (int I = blockIdx.y; I < nc; I += gridDim.y)
+    for (int t = blockIdx.x * kBlock + threadIdx.x; t < nc * nc; t += gridDim.x * kBlock) {
+        const int J = split_row(t, nc, inv), K = t - J * nc;
+        const long q = cell(nc, I, J, K);
         const int k0 = 2 * K, km = wrap_dec(k0, nf), kp = wrap_inc(k0 + 1, nf);
         // fine rows: x index 2I-1 .. 2I+2, y index 2J-1 .. 2J+2 (periodic)
         int xi[4], yj[4];
@@ -139,13 +140,8 @@ __global__ __launch_bounds__(kBlock) void k_prolong_pairs(int nf, T* __restrict_
 {
     using V = typename Vec2<T>::type;
     const int nc = nf >> 1;
-    const long total = (long)nc * nc * nc;
     const T w[2] = {T(0.75), T(0.25)};
-    for (long q = (long)blockIdx.x * blockDim.x + threadIdx.x; q < total;
-         q += (long)gridDim.x * blockDim.x) {
-        const int K = (int)(q % nc);
-        const long r = q / nc;
-        const int J = (int)(r % nc), I = (int)(r / nc);
+    for_planes(nc, nc, nc, [&](int I, int J, int K) __attribute__((always_inline)) {
         // coarse index offsets -1, 0, +1 per axis (periodic)
         const int Ix[3] = {wrap_dec(I, nc), I, wrap_inc(I, nc)};
         const int Jy[3] = {wrap_dec(J, nc), J, wrap_inc(J, nc)};
@@ -198,7 +194,7 @@ __global__ __launch_bounds__(kBlock) void k_prolong_pairs(int nf, T* __restrict_
                 }
                 *reinterpret_cast<V*>(fine + o) = f;
             }
-    }
+    });
 }
 
 // FAS descent (see k_defect_restrict), LDS-staged: each workgroup owns a
@@ -641,8 +637,8 @@ __global__ __launch_bounds__(kBlock) void k_prolong_tiled(int nf, T* __restrict_
     }
 }
 
-// Finest-level defect in double precision and per-block partial sums of r^2
-// (see k_defect_norm): one thread per z-pair of cells.
+// Finest-level defect in double precision and per-block partial sums of r^2:
+// one thread per z-pair of cells.
 template <class TF, class M>
 __global__ __launch_bounds__(kBlock) void k_defect_norm_pairs(M m, int n, double ih2, double uscale, double uoffset,
                                                               const TF* __restrict__ phi,
@@ -652,14 +648,8 @@ __global__ __launch_bounds__(kBlock) void k_defect_norm_pairs(M m, int n, double
 {
     using VF = typename Vec2<TF>::type;
     using VD = typename Vec2<double>::type;
-    const int hn = n >> 1;
-    const long total = (long)n * n * hn;
     double acc = 0.0;
-    for (long t = (long)blockIdx.x * blockDim.x + threadIdx.x; t < total;
-         t += (long)gridDim.x * blockDim.x) {
-        const int kk = (int)(t % hn);
-        const long r = t / hn;
-        const int j = (int)(r % n), i = (int)(r / n);
+    for_planes(n, n, n >> 1, [&](int i, int j, int kk) __attribute__((always_inline)) {
         const int k0 = 2 * kk;
         const long o = ((long)i * n + j) * n;
         const long oxm = ((long)wrap_dec(i, n) * n + j) * n, oxp = ((long)wrap_inc(i, n) * n + j) * n;
@@ -688,9 +678,9 @@ __global__ __launch_bounds__(kBlock) void k_defect_norm_pairs(M m, int n, double
             acc += L * L;
         }
         if (res) *reinterpret_cast<VD*>(res + o + k0) = VD{L2[0], L2[1]};
-    }
+    });
     double s = block_sum(acc);
-    if (threadIdx.x == 0) partial[blockIdx.x] = s;
+    if (threadIdx.x == 0) partial[blockIdx.y * gridDim.x + blockIdx.x] = s;
 }
 
 // Finest-level defect and per-block partial sums of r^2, computed in the
@@ -714,8 +704,13 @@ struct NormTile {
     static_assert(TY * TZ == 2 * NT, "one z-pair of cells per thread");
 };
 using NormTileF = NormTile<8, 64, 32>;
+// Planes per tile at side n: 32 from 256 on; fewer on the small grids, whose few
+// tiles would leave most of the device idle while each streams its planes.
+// 64^3, 4 planes instead of 32 (128 workgroups, not 16): the chameleon's norm
+// 36.5 -> 7.9 us, its set-up 68 -> 16; 128^3, 8: the symmetron's norm 16.7 -> 9.
+constexpr int norm_planes(int n) { return n >= 256 ? 32 : n == 128 ? 8 : 4; }
 
-template <class TF, class M, class TA = double>
+template <class TF, class M, class TA = double, int XC = 32>
 __global__ __launch_bounds__(kBlock) void k_defect_norm_tiled(M m, int n, double ih2_, double uscale_,
                                                               double uoffset_,
                                                               const TF* __restrict__ phi,
@@ -723,7 +718,7 @@ __global__ __launch_bounds__(kBlock) void k_defect_norm_tiled(M m, int n, double
                                                               double* __restrict__ res,
                                                               double* __restrict__ partial)
 {
-    using G = NormTileF;
+    using G = NormTile<8, 64, XC>;
     using SO = StageOp<TA, M>;
     using VF = typename Vec2<TF>::type;
     using VD = typename Vec2<double>::type;
@@ -880,7 +875,7 @@ __global__ __launch_bounds__(kBlock) void k_defect_norm_tiled(M m, int n, double
 // eta to eta32 (if not NULL) and the 8-child mean of eta to eta_c (the next
 // level, children summed in the order of k_restrict: x, then y, then z), and
 // sums cold^2 into partial2.  n a power of two, a multiple of the tile.
-template <class M>
+template <class M, int XC = 32>
 __global__ __launch_bounds__(kBlock) void k_setup_tiled(M m, int n, double ih2,
                                                         const double* __restrict__ eta,
                                                         double* __restrict__ cold,
@@ -890,7 +885,7 @@ __global__ __launch_bounds__(kBlock) void k_setup_tiled(M m, int n, double ih2,
                                                         double* __restrict__ partial,
                                                         double* __restrict__ partial2)
 {
-    using G = NormTileF;
+    using G = NormTile<8, 64, XC>;
     using SO = StageOp<double, M>;
     using VD = typename Vec2<double>::type;
     using VF = typename Vec2<float>::type;
