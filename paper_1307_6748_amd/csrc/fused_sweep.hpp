@@ -582,12 +582,14 @@ inline int fused_chunk(int n)
 // faster than 64-plane chunks; 256^3, 12 per tile column, FP32 f(R) 9% faster
 // than 32-plane chunks, which filled two thirds of the slots).  Otherwise, or
 // when the occupancy is unknown (resident <= 0), fused_chunk() planes per
-// chunk.
+// chunk.  Below 256^3 the chunks may be 8 planes long (16 of them at 128^3):
+// there a pass is one short round and takes as long as its longest chunk.
 inline int fused_chunks(int n, int tiles, int resident)
 {
     if (resident > 0 && resident % tiles == 0 && resident / tiles <= 16 &&
-        resident / tiles <= n / 16)
+        resident / tiles <= n / (n >= 256 ? 16 : 8))
         return resident / tiles;
+    if (n == 128) return 16;
     return n / fused_chunk(n);
 }
 

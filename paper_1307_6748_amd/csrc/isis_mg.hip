@@ -21,6 +21,7 @@
 
 #include "../../include/isis_mg.h"
 #include "amr.hpp"
+#include "block_sweep.hpp"
 #include "bottom.hpp"
 #include "force.hpp"
 #include "full_weighting.hpp"
@@ -285,6 +286,16 @@ int launch_halfsweep(const M& m, int n, double h, T* phi, const T* eta, const T*
 // solver: there the streaming pipeline of the fused kernel has too few
 // workgroups to hide its per-plane latency.
 constexpr int kFusedSolverMinN = 256;
+// In double precision from 128 on, in 16 chunks of planes: a pass of two sweeps
+// with the prolongation or the defect on it takes 36 us there and one sweep 21
+// (symmetron), against 11.8 us for each of six half-sweeps and 12 for the
+// defect, restriction and prolongation.
+constexpr int kFusedSolverMinN64 = 128;
+template <class T>
+constexpr int fused_solver_min()
+{
+    return sizeof(T) == 8 ? kFusedSolverMinN64 : kFusedSolverMinN;
+}
 
 template <class T, int PW = 0>
 int launch_prolong(int nf, T* fine, const T* coarse, const T* coarse_hat, hipStream_t s,
@@ -304,7 +315,7 @@ constexpr int weighted_code()
 }
 
 template <class T, class M>
-bool fused_level(int n, int tb, int min_fused_n = kFusedSolverMinN)
+bool fused_level(int n, int tb, int min_fused_n = fused_solver_min<T>())
 {
     return tb >= 1 && n >= min_fused_n && fused_supported<T, M>(n);
 }
@@ -312,7 +323,7 @@ bool fused_level(int n, int tb, int min_fused_n = kFusedSolverMinN)
 // Whether a smoothing step of `count` sweeps takes the prolongation inside
 // its first fused pass (fused level, single-sweep first pass).
 template <class T, class M>
-bool prolong_fused(int n, int count, int tb, int min_fused_n = kFusedSolverMinN)
+bool prolong_fused(int n, int count, int tb, int min_fused_n = fused_solver_min<T>())
 {
     return count > 0 && fused_level<T, M>(n, tb, min_fused_n) && fused_first_pass(count, tb) == 1;
 }
@@ -322,8 +333,8 @@ bool prolong_fused(int n, int count, int tb, int min_fused_n = kFusedSolverMinN)
 // the coefficient-weighted prolongation (always its own kernel).
 template <class T, class M>
 int launch_sweeps(const M& m, int n, double h, T** phi, T** tmp, const T* eta, const T* sigma,
-                  int count, int tb, hipStream_t s, char* err, int min_fused_n = kFusedSolverMinN,
-                  const T* cphi = nullptr, const T* cphat = nullptr, bool pw = false,
+                  int count, int tb, hipStream_t s, char* err,
+                  int min_fused_n = fused_solver_min<T>(), const T* cphi = nullptr, const T* cphat = nullptr, bool pw = false,
                   const float* in32 = nullptr, double in_scale = 1.0, double in_offset = 0.0)
 {
     constexpr int PWc = weighted_code<T, M>();
@@ -866,7 +877,7 @@ int timed_block(isis_mg* H, const M& m, LevP<T>& f, int l, int count, const T* c
         }
     }
     int r = launch_sweeps<T, M>(m, f.n, f.h, &f.phi, &f.tmp, f.eta, f.sigma, count, tb, H->s,
-                                H->err, kFusedSolverMinN, cphi, cphat, false, in32,
+                                H->err, fused_solver_min<T>(), cphi, cphat, false, in32,
                                 H->in32_scale, H->in32_offset);
     if (r) return r;
     if (timed) {
@@ -932,7 +943,7 @@ int launch_bottom_levels(isis_mg* H, const M& m, const BottomArgs<T>& a)
 
 // Levels l .. nlev-1 of the V-cycle in one launch of k_bottom_cycle.
 template <class T, class M>
-int launch_bottom(isis_mg* H, const M& m, LevP<T>* L, int l, double* updates)
+int launch_bottom(isis_mg* H, const M& m, LevP<T>* L, int l, double* updates, bool from_rr)
 {
     const isis_mg_desc& d = H->d;
     BottomArgs<T> a{};
@@ -941,7 +952,8 @@ int launch_bottom(isis_mg* H, const M& m, LevP<T>* L, int l, double* updates)
     a.nu_post = H->nu_post;
     a.nu_coarse = d.nu_coarse;
     a.phi0 = L[l].phi;
-    a.sigma0 = L[l].sigma;
+    a.sigma0 = from_rr ? L[l].rr : L[l].sigma;
+    a.from_rr = from_rr ? 1 : 0;
     for (int q = 0; q < nlev; ++q) {
         const LevP<T>& v = L[l + q];
         a.eta[q] = v.eta;
@@ -953,14 +965,126 @@ int launch_bottom(isis_mg* H, const M& m, LevP<T>* L, int l, double* updates)
                      : launch_bottom_levels<T, M, 2>(H, m, a);
 }
 
+// Levels whose sweeps run in k_block_sweep: sides 32 and 64, unless the caller
+// asked for one launch per colour (temporal_block 0).  Below, the bottom
+// kernel.  At 128^3 the halo's work exceeds what the launches save (symmetron,
+// double precision, us per cycle: 55 + 45 + 23 in blocks against 6 x 11.8 +
+// 11 + 12 per colour).
+inline bool block_level(const isis_mg* H, int n)
+{
+    return H->tb >= 1 && (n == 32 || n == 64);
+}
+
+// One sweep of level f, DESC: followed by the restriction into c; PROL: after
+// the correction from c.  from_rr: the level's FAS source is still to be
+// formed from its restricted defect.
+template <class T, class M, bool DESC, bool PROL, int PW = 0>
+int launch_block(isis_mg* H, const M& m, LevP<T>& f, LevP<T>& c, bool from_rr)
+{
+    using G = BlockTile<DESC, PROL>;
+    constexpr int lds = block_lds_bytes<T, M, DESC, PROL>();
+    static_assert(lds <= 160 * 1024, "LDS overflow");
+    auto kern = k_block_sweep<T, M, DESC, PROL, PW>;
+    static std::atomic<unsigned> lds_done{0};  // per instantiation: devices set up
+    HIP_TRY(H->err, ensure_dynamic_lds((const void*)kern, lds, lds_done));
+    BlockArgs<T> a{};
+    a.n = f.n;
+    a.ih2 = (T)(1.0 / (f.h * f.h));
+    a.in = f.phi;
+    a.out = f.tmp;
+    a.eta = f.eta;
+    a.sigma = f.sigma;
+    a.rr = from_rr ? f.rr : nullptr;
+    a.cphi = c.phi;
+    a.cphat = c.phihat;
+    a.phi_c = c.phi;
+    a.phihat_c = c.phihat;
+    a.rr_c = c.rr;
+    hipLaunchKernelGGL(kern, dim3((f.n / G::TX) * (f.n / G::TY) * (f.n / G::TZ)), dim3(G::NT), lds,
+                       H->s, m, a);
+    LAUNCH_CHECK(H->err, "k_block_sweep");
+    std::swap(f.phi, f.tmp);
+    return ISIS_OK;
+}
+
 template <class T, class M>
-int vcycle(isis_mg* H, const M& m, LevP<T>* L, int l, double* updates)
+int vcycle(isis_mg* H, const M& m, LevP<T>* L, int l, double* updates, bool from_rr = false);
+
+// A level of the V-cycle through k_block_sweep (nu_pre, nu_post >= 1).
+template <class T, class M>
+int vcycle_block(isis_mg* H, const M& m, LevP<T>* L, int l, double* updates, bool from_rr)
+{
+    const isis_mg_desc& d = H->d;
+    LevP<T>&f = L[l], &c = L[l + 1];
+    const double n3 = (double)f.n * f.n * f.n;
+    constexpr int PWc = weighted_code<T, M>();
+    int r;
+    // finest level, profiling on: pre- and post-smoothing timed as one step each
+    auto timed = [&](int count, auto&& body) -> int {
+        const int q = H->ntimed;
+        const bool on = H->profile && l == 0 && q < isis_mg::kMaxTimed;
+        if (on) HIP_TRY(H->err, hipEventRecord(H->ev0[q], H->s));
+        int rr = body();
+        if (rr) return rr;
+        if (on) {
+            HIP_TRY(H->err, hipEventRecord(H->ev1[q], H->s));
+            H->tlaunch[q] = count;
+            H->tupd[q] = n3 * count;
+            H->tbytes[q] = (double)count * n3 * 3.0 * sizeof(T);
+            H->tprec[q] = sizeof(T) == 4 ? 1 : 0;
+            H->tlevel[q] = l;
+            H->tprol[q] = 0;
+            H->ntimed = q + 1;
+        }
+        return ISIS_OK;
+    };
+    r = timed(d.nu_pre, [&]() -> int {
+        for (int q = 0; q < d.nu_pre; ++q) {
+            const bool first_rr = from_rr && q == 0;
+            const int e = q + 1 == d.nu_pre && !H->fw
+                              ? launch_block<T, M, true, false>(H, m, f, c, first_rr)
+                              : launch_block<T, M, false, false>(H, m, f, c, first_rr);
+            if (e) return e;
+        }
+        return (int)ISIS_OK;
+    });
+    if (r) return r;
+    *updates += d.nu_pre * n3;
+    if (H->fw && (r = launch_descend<T, M>(m, f.n, f.h, f.phi, f.eta, f.sigma, c.eta, c.phi,
+                                           c.phihat, c.sigma, c.rr, H->s, H->err, f.tmp)))
+        return r;
+    if ((r = vcycle<T, M>(H, m, L, l + 1, updates, !H->fw))) return r;
+    r = timed(H->nu_post, [&]() -> int {
+        for (int q = 0; q < H->nu_post; ++q) {
+            int e;
+            if (q > 0)
+                e = launch_block<T, M, false, false>(H, m, f, c, false);
+            else if (PWc != 0 && H->pw)
+                e = launch_block<T, M, false, true, PWc>(H, m, f, c, false);
+            else
+                e = launch_block<T, M, false, true>(H, m, f, c, false);
+            if (e) return e;
+        }
+        return (int)ISIS_OK;
+    });
+    if (r) return r;
+    *updates += H->nu_post * n3;
+    return ISIS_OK;
+}
+
+// from_rr: the level's FAS source sigma is still to be formed from its
+// restricted defect rr (its parent was a block level, whose restriction stops
+// there; the levels below one are block levels or the bottom kernel's).
+template <class T, class M>
+int vcycle(isis_mg* H, const M& m, LevP<T>* L, int l, double* updates, bool from_rr)
 {
     const isis_mg_desc& d = H->d;
     LevP<T>& f = L[l];
     const double n3 = (double)f.n * f.n * f.n;
     int r;
-    if (l == H->lb) return launch_bottom<T, M>(H, m, L, l, updates);
+    if (l == H->lb) return launch_bottom<T, M>(H, m, L, l, updates, from_rr);
+    if (block_level(H, f.n) && d.nu_pre > 0 && H->nu_post > 0)
+        return vcycle_block<T, M>(H, m, L, l, updates, from_rr);
     if (l == H->nlev - 1) {
         *updates += (double)d.nu_coarse * n3;
         return launch_coarse<T, M>(m, f.h, f.phi, f.eta, f.sigma, d.nu_coarse, H->s, H->err);
