@@ -1570,6 +1570,19 @@ int static_scratch(double** out, char* err)
     return ISIS_OK;
 }
 
+// Most blocks of sweeps a patch solve queues between two looks at its state:
+// 64 blocks of 4 sweeps are about 600 launches, which queue faster than they run.
+constexpr int kPatchBatch = 64;
+
+// Workspace of a patch solve: the pre-iteration field, the norm's partial sums,
+// the control block and a byte per cell (k_patch_kind).  Without room for the
+// last (callers that sized it when there was none) the sweeps read the masks.
+size_t patch_bytes(int n, bool kinds)
+{
+    const size_t n3 = (size_t)n * n * n;
+    return (n3 + 2 * kReduceBlocks + 16) * sizeof(double) + 256 + (kinds ? n3 + 256 : 0);
+}
+
 }  // namespace
 
 extern "C" {
@@ -1967,9 +1980,9 @@ int isis_op_masked_defect(const isis_model_params* p, double a, int n, double h,
     if (!masked_args_ok(n, h, {phi, eta, mask, u_int, u_pre, out})) return ISIS_ERR_INVALID_ARG;
     if (!ptrs_aligned({phi, eta, sigma, mask, u_int, u_pre, out})) return ISIS_ERR_INVALID_ARG;
     return with_model<double>(*p, a, [&](auto m) {
-        hipLaunchKernelGGL((k_masked_defect<decltype(m)>), dim3(grid_for((long)n * n * n)),
-                           dim3(kBlock), 0, (hipStream_t)stream, m, n, 1.0 / (h * h), phi, eta,
-                           sigma, mask, u_int, u_pre, out, nullptr);
+        hipLaunchKernelGGL((k_masked_defect<decltype(m)>), plane_grid(n), dim3(kBlock), 0,
+                           (hipStream_t)stream, m, n, 1.0 / (h * h), phi, eta, sigma, mask, u_int,
+                           u_pre, out, nullptr, nullptr);
         LAUNCH_CHECK(g_err, "k_masked_defect");
         return (int)ISIS_OK;
     });
@@ -1986,10 +1999,9 @@ int isis_op_masked_halfsweep(const isis_model_params* p, double a, int n, double
     }
     if (!ptrs_aligned({phi, eta, sigma, mask, u_int, u_pre})) return ISIS_ERR_INVALID_ARG;
     return with_model<double>(*p, a, [&](auto m) {
-        hipLaunchKernelGGL((k_masked_halfsweep<decltype(m)>),
-                           dim3(grid_for((long)n * n * n / 2)), dim3(kBlock), 0,
-                           (hipStream_t)stream, m, n, 1.0 / (h * h), phi, eta, sigma, mask, u_int,
-                           u_pre, colour);
+        hipLaunchKernelGGL((k_masked_halfsweep<decltype(m)>), plane_grid(n, (long)n * n / 2),
+                           dim3(kBlock), 0, (hipStream_t)stream, m, n, 1.0 / (h * h), phi, eta,
+                           sigma, mask, u_int, u_pre, colour, nullptr);
         LAUNCH_CHECK(g_err, "k_masked_halfsweep");
         return (int)ISIS_OK;
     });
@@ -1997,8 +2009,7 @@ int isis_op_masked_halfsweep(const isis_model_params* p, double a, int n, double
 
 size_t isis_patch_workspace_size(int n)
 {
-    if (!op_grid_ok(n, 2)) return 0;
-    return (size_t)n * n * n * sizeof(double) + (2 * kReduceBlocks + 16) * sizeof(double) + 256;
+    return op_grid_ok(n, 2) ? patch_bytes(n, true) : 0;
 }
 
 int isis_patch_solve(const isis_model_params* p, double a, int n, double h, double* phi,
@@ -2013,61 +2024,87 @@ int isis_patch_solve(const isis_model_params* p, double a, int n, double h, doub
         return ISIS_ERR_INVALID_ARG;
     }
     if (!ptrs_aligned({phi, eta, mask, u_int}) || !aligned(workspace, 256) ||
-        workspace_bytes < isis_patch_workspace_size(n)) {
+        workspace_bytes < patch_bytes(n, false)) {
         fmt_err(g_err, "patch_solve: aligned arrays and a 256-byte aligned workspace of >= %zu "
-                       "bytes needed", isis_patch_workspace_size(n));
+                       "bytes needed", patch_bytes(n, false));
         return ISIS_ERR_INVALID_ARG;
     }
     hipStream_t s = (hipStream_t)stream;
     const long n3 = (long)n * n * n;
     double* pre = static_cast<double*>(workspace);
-    double* partial = pre + n3 + 32;  // per-block sums, then their totals
-    double* scal = partial + 2 * kReduceBlocks;
+    double* partial = pre + n3 + 32;  // per-block sums, then the control block
+    PatchState* state = reinterpret_cast<PatchState*>(partial + 2 * kReduceBlocks);
     const double ih2 = 1.0 / (h * h);
+    const dim3 dg = plane_grid(n, (long)n * n, kReduceBlocks), hg = plane_grid(n, (long)n * n / 2);
     return with_model<double>(*p, a, [&](auto m) {
         using M = decltype(m);
-        const int g = std::min(kReduceBlocks, grid_for(n3));
-        // RMS of the defect over the inside cells, boundary values from phi
-        auto rms = [&](double* out) -> int {
-            HIP_TRY(g_err, hipMemcpyAsync(pre, phi, sizeof(double) * n3, hipMemcpyDeviceToDevice, s));
-            hipLaunchKernelGGL((k_masked_defect<M>), dim3(g), dim3(kBlock), 0, s, m, n, ih2, phi,
-                               eta, nullptr, mask, u_int, pre, nullptr, partial);
+        unsigned char* kind = nullptr;
+        if (workspace_bytes >= patch_bytes(n, true)) {
+            kind = reinterpret_cast<unsigned char*>(state) + 16 * sizeof(double);
+            hipLaunchKernelGGL(k_patch_kind, plane_grid(n), dim3(kBlock), 0, s, n, mask, kind);
+            LAUNCH_CHECK(g_err, "k_patch_kind");
+        }
+        // RMS of the defect over the inside cells, boundary values from phi,
+        // which becomes the next block's pre-iteration field in the same pass
+        auto judge = [&](int sweeps) -> int {
+            hipLaunchKernelGGL((k_masked_defect<M>), dg, dim3(kBlock), 0, s, m, n, ih2, phi, eta,
+                               nullptr, mask, u_int, phi, nullptr, partial, pre);
             LAUNCH_CHECK(g_err, "k_masked_defect");
-            hipLaunchKernelGGL(k_reduce, dim3(1), dim3(kBlock), 0, s, partial, g, scal);
-            hipLaunchKernelGGL(k_reduce, dim3(1), dim3(kBlock), 0, s, partial + g, g, scal + 1);
-            LAUNCH_CHECK(g_err, "k_reduce");
-            double host[2];
-            HIP_TRY(g_err, hipMemcpyAsync(host, scal, 2 * sizeof(double), hipMemcpyDeviceToHost, s));
-            HIP_TRY(g_err, hipStreamSynchronize(s));
-            *out = host[1] > 0.0 ? std::sqrt(host[0] / host[1]) : 0.0;
+            hipLaunchKernelGGL(k_patch_judge, dim3(1), dim3(kBlock), 0, s, partial,
+                               (int)(dg.x * dg.y), sweeps, max_sweeps, tol, state);
+            LAUNCH_CHECK(g_err, "k_patch_judge");
             return (int)ISIS_OK;
         };
-        double r = 0.0;
-        int rc = rms(&r);
-        if (rc) return rc;
-        int sweeps = 0;
-        while (r > tol && sweeps < max_sweeps) {
-            // the boundary values are set from the field before each block
-            HIP_TRY(g_err, hipMemcpyAsync(pre, phi, sizeof(double) * n3, hipMemcpyDeviceToDevice, s));
-            for (int b = 0; b < block && sweeps < max_sweeps; ++b, ++sweeps) {
-                for (int colour = 0; colour < 2; ++colour) {
-                    hipLaunchKernelGGL((k_masked_halfsweep<M>), dim3(grid_for(n3 / 2)),
-                                       dim3(kBlock), 0, s, m, n, ih2, phi, eta, nullptr, mask,
-                                       u_int, pre, colour);
-                    LAUNCH_CHECK(g_err, "k_masked_halfsweep");
-                }
+        auto halfsweep = [&](int colour) -> int {
+            if (kind)
+                hipLaunchKernelGGL((k_patch_halfsweep<M>), hg, dim3(kBlock), 0, s, m, n, ih2, phi,
+                                   eta, mask, u_int, pre, kind, colour, state);
+            else
+                hipLaunchKernelGGL((k_masked_halfsweep<M>), hg, dim3(kBlock), 0, s, m, n, ih2, phi,
+                                   eta, nullptr, mask, u_int, pre, colour, state);
+            LAUNCH_CHECK(g_err, "k_patch_halfsweep");
+            return (int)ISIS_OK;
+        };
+        PatchState st{0.0, 0, 0};
+        auto fetch = [&]() -> int {
+            HIP_TRY(g_err, hipMemcpyAsync(&st, state, sizeof(st), hipMemcpyDeviceToHost, s));
+            HIP_TRY(g_err, hipStreamSynchronize(s));
+            return (int)ISIS_OK;
+        };
+        hipLaunchKernelGGL(k_patch_begin, dim3(1), dim3(1), 0, s, state);
+        LAUNCH_CHECK(g_err, "k_patch_begin");
+        int rc = judge(0);
+        if (!rc) rc = fetch();
+        // Blocks of sweeps, judged on the device after each; the host reads
+        // the state once per batch.  Launches queued behind the block that
+        // meets tol store nothing, so a batch is as long as the last factor
+        // predicts (a host round trip per block was a quarter of a 68^3
+        // solve, and the launches after it started on an idle device).
+        int queued = 0, batch = 1;  // sweeps queued so far; blocks in the next batch
+        while (!rc && !st.stop) {
+            const double r0 = st.rms;
+            for (int q = 0; q < batch && queued < max_sweeps && !rc; ++q) {
+                const int count = std::min(block, max_sweeps - queued);
+                for (int b = 0; b < 2 * count && !rc; ++b) rc = halfsweep(b & 1);
+                queued += count;
+                if (!rc) rc = judge(count);
             }
-            if ((rc = rms(&r))) return rc;
-            if (!std::isfinite(r)) {
-                fmt_err(g_err, "patch_solve: non-finite defect after %d sweeps", sweeps);
-                if (sweeps_out) *sweeps_out = sweeps;
-                if (rms_out) *rms_out = r;
-                return (int)ISIS_ERR_DIVERGED;
-            }
+            if (!rc) rc = fetch();
+            if (rc || st.stop) break;
+            const double rho = std::pow(st.rms / r0, 1.0 / batch);
+            const double left = std::log(tol / st.rms) / std::log(rho);
+            batch = rho < 1.0 && left >= 1.0 ? (int)std::min(std::ceil(left), 4.0 * batch)
+                                             : std::min(2 * batch, 8);
+            batch = std::max(1, std::min(batch, kPatchBatch));
         }
-        if (sweeps_out) *sweeps_out = sweeps;
-        if (rms_out) *rms_out = r;
-        return r <= tol ? (int)ISIS_OK : (int)ISIS_ERR_NOT_CONVERGED;
+        if (rc) return rc;
+        if (sweeps_out) *sweeps_out = st.sweeps;
+        if (rms_out) *rms_out = st.rms;
+        if (st.sweeps > 0 && !std::isfinite(st.rms)) {
+            fmt_err(g_err, "patch_solve: non-finite defect after %d sweeps", st.sweeps);
+            return (int)ISIS_ERR_DIVERGED;
+        }
+        return st.rms <= tol ? (int)ISIS_OK : (int)ISIS_ERR_NOT_CONVERGED;
     });
 }
 

@@ -1,0 +1,102 @@
+"""The solver's small levels and patches where their kernels change over:
+the bottom kernel's ladders (8^3, 16^3), the block sweeps of 32^3 and 64^3,
+the double-precision fused sweeps of 128^3, and the patch solve's batches of
+blocks, against the oracle."""
+import ctypes as C
+
+import numpy as np
+import pytest
+import torch
+
+from gpucase import cubic, density, dev, field_for, models
+
+pytestmark = pytest.mark.gpu
+
+# Two V-cycles differ from the oracle's by rounding only: a few tens of
+# dependent operations per cell and cycle, each good to half an ulp (1.1e-16,
+# 6e-8), damped by the smoothing: 1e-12 and 1e-6 of the field's size.
+TOL = {"fp64": 1e-12, "mixed": 1e-6}
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("name,n,pre,post,fw,pw", [
+    ("symmetron_a1", 8, 1, 1, 0, 0), ("fofr", 8, 2, 2, 0, 1), ("chameleon", 16, 1, 3, 1, 0),
+    ("linear", 16, 2, 2, 0, 0), ("fofr_a07", 16, 3, 1, 1, 1), ("symmetron_a05", 32, 1, 2, 0, 0),
+    ("fofr", 32, 1, 1, 0, 1), ("chameleon", 32, 3, 1, 0, 1), ("linear", 32, 2, 3, 0, 0),
+    ("symmetron_a1", 32, 2, 1, 1, 0), ("fofr", 64, 3, 1, 0, 0), ("fofr_a07", 64, 1, 3, 1, 1),
+    ("chameleon_n05", 64, 2, 1, 0, 0), ("symmetron_a1", 64, 0, 2, 0, 0), ("linear", 64, 2, 0, 0, 0),
+    ("symmetron_a1", 128, 1, 3, 0, 0), ("fofr", 128, 2, 2, 0, 1), ("chameleon", 128, 3, 1, 1, 0),
+])
+def test_cycles_of_small_grids(orc, name, n, pre, post, fw, pw, precision):
+    from paper_1307_6748_amd import solver as S
+    om, sp, a = models(name)
+    if precision == "mixed" and 0 in (pre, post):
+        pytest.skip("FP64 schedule only")
+    box = 4.0 * n
+    eta = density(n, 400 + n)
+    cfg = orc.Cfg(nu_pre=pre, nu_post=post, restrict_fw=bool(fw), prolong_w=bool(pw))
+    ref = orc.vcycles(om, eta, box, orc.cold_start(om, eta), 2, cfg=cfg)
+    s = S.Solver(n, box, nu_pre=pre, nu_post=post, max_cycles=2, precision=precision,
+                 restriction=fw, prolongation=pw)
+    phi, st = s.solve(dev(eta), sp, a, 1e-300, check=False)
+    assert st.cycles == 2
+    err = np.max(np.abs(cubic(phi, n) - ref.phi)) / (np.abs(ref.phi).max() + 1.0)
+    assert err <= TOL[precision], err
+
+
+def _patch(name, n, seed):
+    rng = np.random.default_rng(seed)
+    idx = np.arange(n)
+    ins = (idx >= 2) & (idx < n - 2)
+    mask = np.where(ins[:, None, None] & ins[None, :, None] & ins[None, None, :],
+                    0.4 + 0.6 * rng.random((n, n, n)), -rng.random((n, n, n)))
+    mask[n // 2, n // 2, n // 2] = -0.5   # a hole
+    phi = field_for(name, n, seed)
+    return phi, density(n, seed + 1), mask, phi + 0.01 * rng.standard_normal(phi.shape)
+
+
+@pytest.mark.parametrize("name", ["symmetron_a1", "fofr", "chameleon", "linear"])
+@pytest.mark.parametrize("n", [8, 24, 30])
+@pytest.mark.parametrize("block,sweeps", [(4, 0), (4, 1), (3, 8), (1, 21)])
+@pytest.mark.parametrize("room", [True, False])
+def test_patch_blocks(orc, name, n, block, sweeps, room):
+    """A bounded number of sweeps, whole blocks or not, gives the oracle's
+    iterate, sweep count and defect, with and without room in the workspace
+    for the kinds of cells.  Tolerance: 1e-12 of the field per sweep made."""
+    from paper_1307_6748_amd import _capi as A
+    om, sp, a = models(name)
+    h = 0.7
+    phi, eta, mask, u_int = _patch(name, n, 70 + n)
+    ref, sw, rms = orc.patch_solve(om, h, phi, eta, mask, u_int, block=block, max_sweeps=sweeps,
+                                   tol=1e-14)
+    g, e, mk, ui = dev(phi), dev(eta), dev(mask), dev(u_int)
+    nbytes = A.lib().isis_patch_workspace_size(n) - (0 if room else n ** 3 + 256)
+    ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+    count, got = C.c_int(), C.c_double()
+    pc = sp.c()
+    ptr = [C.c_void_p(t.data_ptr()) for t in (g, e, mk, ui)]
+    rc = A.lib().isis_patch_solve(C.byref(pc), a, n, h, *ptr, block, sweeps, 1e-14,
+                                  C.c_void_p(ws.data_ptr()), nbytes, C.byref(count), C.byref(got),
+                                  C.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert rc == A.ISIS_ERR_NOT_CONVERGED and count.value == sw == sweeps
+    tol = 1e-12 * max(sweeps, 1) * (np.abs(ref).max() + 1.0)
+    assert np.max(np.abs(cubic(g, n) - ref)) <= tol
+    # the defect weighs the field's error with up to 12 exp(|phi|) / h^2
+    scale = 12.0 * np.exp(np.abs(ref).max() if name.startswith(("fofr", "cham")) else 1.0) / h ** 2
+    assert abs(got.value - rms) <= 1e-12 * rms + tol * scale
+
+
+def test_patch_with_nothing_finite_to_judge():
+    """A NaN from the start: no sweep is made, as an unmet tolerance.  A defect
+    whose square overflows: divergence, after the first block."""
+    from paper_1307_6748_amd import _capi as A
+    from paper_1307_6748_amd import solver as S
+    _, sp, a = models("linear")
+    phi, eta, mask, u_int = _patch("linear", 24, 5)
+    bad = eta.copy()
+    bad[12, 13, 11] = np.nan
+    rc, sweeps, rms = S.patch_solve(sp, a, 0.7, dev(phi), dev(bad), dev(mask), dev(u_int), check=False)
+    assert (rc, sweeps) == (A.ISIS_ERR_NOT_CONVERGED, 0) and np.isnan(rms)
+    rc, sweeps, rms = S.patch_solve(sp, a, 0.7, dev(1e200 * phi), dev(eta), dev(mask), dev(u_int),
+                                    block=3, check=False)
+    assert (rc, sweeps) == (A.ISIS_ERR_DIVERGED, 3) and not np.isfinite(rms)
