@@ -23,7 +23,7 @@
 // weight gradient is a split-K GEMM over voxel chunks with a fixed-order
 // reduction of the partial sums (deterministic).  On sides >= 64 the input is
 // staged in LDS (k_conv3_lds; k_conv3_ring streams along x for 16 input
-// channels), and the prediction's last decoder convolution reads its
+// channels, k_conv3_planes for 16 output channels), and the prediction's last decoder convolution reads its
 // upsampled and skip inputs directly instead of a materialised concatenation.
 #include <hip/hip_runtime.h>
 
@@ -296,8 +296,8 @@ __global__ __launch_bounds__(kThreads, 1) void k_conv3_small(const bf16_t* __res
 }
 
 // The same convolution with its input and weights staged in LDS (sides n >=
-// 64).  A workgroup of NW waves computes 16 NT output channels of an NW (y) x
-// 64 (z) tile of two x-planes, one z-row of 64 voxels of both planes per wave
+// 64, 32 output channels and more).  A workgroup of NW waves computes 16 NT
+// output channels of an NW (y) x 64 (z) tile of two x-planes, one z-row of 64 voxels of both planes per wave
 // (eight M tiles of 16).  For each 16-channel slice of the input it stages the
 // 4 x (NW + 2) x 66 voxels its 27 taps read and the slice's 27 x 16 NT
 // weights.  LDS holds both as arrays of 16-byte units, one per half of 8
@@ -309,39 +309,41 @@ __global__ __launch_bounds__(kThreads, 1) void k_conv3_small(const bf16_t* __res
 // contiguous ranges with x fastest, so neighbouring planes share an L2.
 // Bound: with one plane per wave and the weights read from memory by each
 // wave, the weight reads (32 lines of 32 bytes per operand) held the kernel at
-// 0.38-0.55 PFLOP/s; now it reaches 0.5 (NT = 1: one LDS operand per MFMA) to
-// 0.9 (NT = 3, 4).  What is left is the L2: a 32-byte slice of a voxel fetches
-// its whole line, which is often gone before the next slice.  Each output adds
-// slices, taps and channels in the same order as before.
-//   48 -> 16 at 128^3: 0.218 -> 0.171 ms; 64 -> 64 at 64^3: 0.166 -> 0.084 ms;
-//   64 -> 128 at 64^3: 0.293 -> 0.133 ms; 96 -> 32 at 128^3: 0.73 -> 0.48 ms
+// 0.38-0.55 PFLOP/s; now it reaches 0.73 to 0.92, held by the LDS (NT = 2: one
+// and a half operands per MFMA) and by the L2: a 32-byte slice of a voxel
+// fetches its whole line, which is often gone before the next slice.  Plane by
+// plane the staging needs three address registers where voxel by voxel it took
+// eleven and spilled (32 -> 32 at 128^3: 0.139 -> 0.127 ms).  Each output adds
+// slices, taps and channels in the order of k_conv3.
+//   64 -> 64 at 64^3: 0.135 -> 0.080 ms; 64 -> 128 at 64^3: 0.297 -> 0.138 ms;
+//   96 -> 32 at 128^3: 0.71 -> 0.45 ms
 constexpr int kLZ = 64;                            // output columns (z)
 constexpr int kLPX = 2, kLPZ = kLZ + 2;            // output planes; staged columns
 template <int NT, int NW>
 struct ConvTile {
     static constexpr int NTH = 64 * NW;
     static constexpr int PY = NW + 2;
-    static constexpr int VOX = (kLPX + 2) * PY * kLPZ;      // staged voxels per slice
+    // staged voxels per slice, whole 256-byte rows of the banks: a 16-byte read
+    // serves lanes 0-3 and 12-15 of one half with 4-11 of the other in a cycle
+    static constexpr int VOX = ((kLPX + 2) * PY * kLPZ + 15) / 16 * 16;
     static constexpr int XU = 2 * VOX, WU = 27 * 16 * NT * 2;  // 16-byte units: input, weights
-    static constexpr int XPT = (XU + NTH - 1) / NTH, WPT = (WU + NTH - 1) / NTH;
+    static constexpr int WPT = (WU + NTH - 1) / NTH;
+    // a thread's units: PR rounds of each plane, then TR of what is left of all
+    static constexpr int PU = 2 * PY * kLPZ, PR = PU / NTH, TU = PU % NTH;
+    static constexpr int TR = ((kLPX + 2) * TU + NTH - 1) / NTH;
+    static_assert(TU % 2 == 0 && TU > 0, "a thread keeps its channel half");
     static constexpr int LDS = (XU + WU) * 16;
 };
 
-//
-// CLO > 0: the input is the concatenation [nearest upsampling of lo, x] of a
-// coarse [(n/2)^3][CLO] tensor and a fine [n^3][CIN - CLO] tensor (the
-// decoder's skip), read directly instead of materialised.
-template <int CIN, int COUT, int NT, int NW, int CLO = 0>
+template <int CIN, int COUT, int NT, int NW>
 __global__ __launch_bounds__(64 * NW, 2) void k_conv3_lds(const bf16_t* __restrict__ x, int n,
                                                           const bf16_t* __restrict__ w,
                                                           const float* __restrict__ bias, int relu,
                                                           bf16_t* __restrict__ y,
-                                                          float* __restrict__ yf, int vec,
-                                                          const bf16_t* __restrict__ lo = nullptr)
+                                                          float* __restrict__ yf, int vec)
 {
     using G = ConvTile<NT, NW>;
-    static_assert(CIN % 16 == 0 && COUT % (16 * NT) == 0 && CLO % 16 == 0 && CLO < CIN,
-                  "whole 16-channel slices");
+    static_assert(CIN % 16 == 0 && COUT % (16 * NT) == 0, "whole 16-channel slices");
     extern __shared__ __align__(16) unsigned char smem_raw[];
     u4* tile = reinterpret_cast<u4*>(smem_raw);  // [8-channel half][plane][row][z]
     u4* wl = tile + G::XU;                       // [tap][8-channel half][output channel]
@@ -374,39 +376,53 @@ __global__ __launch_bounds__(64 * NW, 2) void k_conv3_lds(const bf16_t* __restri
     const int hh = g & 1, side = g >> 1;
     const u4* th = tile + hh * G::VOX + wv * kLPZ + m;  // this lane's half, row and column
     const u4* wh = wl + hh * 16 * NT + m;
-    // staged vectors of this thread (tail clamped; its stores are skipped):
-    // offsets computed once for all slices of a source
+    // staged vectors of this thread: the same in-plane offsets for every plane
+    // (whose pointers are uniform), and voxels of the planes' remainders (tail
+    // clamped; its stores are skipped)
     const int h = tid & 1;  // an even stride: a thread's vectors share a channel half
-    unsigned vo[G::XPT], wo[G::WPT];
-    auto offsets = [&](int sh) __attribute__((always_inline)) {  // sh = 1: of the coarse tensor
-        const int nn = n >> sh;
-#pragma unroll
-        for (int q = 0; q < G::XPT; ++q) {
-            const int vox = min(tid + q * G::NTH, G::XU - 1) >> 1;
-            const int zz = vox % kLPZ, rr = (vox / kLPZ) % G::PY, pp = vox / (kLPZ * G::PY);
-            const int xf = (x0 - 1 + pp) & msk, yf_ = (y0 - 1 + rr) & msk, zf = (z0 - 1 + zz) & msk;
-            vo[q] = (unsigned)(((xf >> sh) * nn + (yf_ >> sh)) * nn + (zf >> sh));
-        }
+    unsigned po[G::PR], to[G::TR], wo[G::WPT];
+    auto in_plane = [&](int vox) __attribute__((always_inline)) {
+        return ((y0 - 1 + vox / kLPZ) & msk) * n + ((z0 - 1 + vox % kLPZ) & msk);
     };
+#pragma unroll
+    for (int q = 0; q < G::PR; ++q)
+        po[q] = (unsigned)(in_plane((tid + q * G::NTH) >> 1) * CIN + 8 * h);
+#pragma unroll
+    for (int q = 0; q < G::TR; ++q) {
+        const int e = min(tid + q * G::NTH, (kLPX + 2) * G::TU - 1);
+        to[q] = (unsigned)(((x0 - 1 + e / G::TU) & msk) * n * n +
+                           in_plane((G::PR * G::NTH + e % G::TU) >> 1));
+    }
 #pragma unroll
     for (int q = 0; q < G::WPT; ++q) {
         const int e = min(tid + q * G::NTH, G::WU - 1) >> 1;  // tap * 16 NT + channel
         wo[q] = (unsigned)((e / (16 * NT) * COUT + co0 + e % (16 * NT)) * CIN + 8 * h);
     }
-    u4 v[G::XPT], wr[G::WPT];
-    // slice at channel c0 of src's C channels (w's channel wc) into registers
-    auto load = [&](const bf16_t* src, int C, int c0, int wc) __attribute__((always_inline)) {
+    u4 v[kLPX + 2][G::PR], vt[G::TR], wr[G::WPT];
+    auto load = [&](int c0) __attribute__((always_inline)) {
 #pragma unroll
-        for (int q = 0; q < G::XPT; ++q)
-            v[q] = *reinterpret_cast<const u4*>(src + (size_t)vo[q] * C + c0 + 8 * h);
+        for (int pp = 0; pp < kLPX + 2; ++pp) {
+            const bf16_t* pl = x + (size_t)((x0 - 1 + pp) & msk) * n * n * CIN + c0;
 #pragma unroll
-        for (int q = 0; q < G::WPT; ++q) wr[q] = *reinterpret_cast<const u4*>(w + wo[q] + wc);
+            for (int q = 0; q < G::PR; ++q) v[pp][q] = *reinterpret_cast<const u4*>(pl + po[q]);
+        }
+#pragma unroll
+        for (int q = 0; q < G::TR; ++q)
+            vt[q] = *reinterpret_cast<const u4*>(x + (size_t)to[q] * CIN + c0 + 8 * h);
+#pragma unroll
+        for (int q = 0; q < G::WPT; ++q) wr[q] = *reinterpret_cast<const u4*>(w + wo[q] + c0);
     };
     auto put = [&]() __attribute__((always_inline)) {
 #pragma unroll
-        for (int q = 0; q < G::XPT; ++q) {
+        for (int pp = 0; pp < kLPX + 2; ++pp)
+#pragma unroll
+            for (int q = 0; q < G::PR; ++q)
+                tile[h * G::VOX + (pp * G::PU + tid + q * G::NTH) / 2] = v[pp][q];
+#pragma unroll
+        for (int q = 0; q < G::TR; ++q) {
             const int e = tid + q * G::NTH;
-            if ((q + 1) * G::NTH <= G::XU || e < G::XU) tile[h * G::VOX + (e >> 1)] = v[q];
+            if ((q + 1) * G::NTH <= (kLPX + 2) * G::TU || e < (kLPX + 2) * G::TU)
+                tile[h * G::VOX + (e / G::TU * G::PU + G::PR * G::NTH + e % G::TU) / 2] = vt[q];
         }
 #pragma unroll
         for (int q = 0; q < G::WPT; ++q) {
@@ -415,16 +431,10 @@ __global__ __launch_bounds__(64 * NW, 2) void k_conv3_lds(const bf16_t* __restri
                 wl[(k / (16 * NT) * 2 + h) * 16 * NT + k % (16 * NT)] = wr[q];
         }
     };
-    offsets(CLO > 0 ? 1 : 0);
     for (int c0 = 0; c0 < CIN; c0 += 16) {
         // (the next slice held in registers during this one's MFMAs measured
         // 10 to 30 % slower: the registers cost waves)
-        if (CLO > 0 && c0 < CLO) {
-            load(lo, CLO, c0, c0);
-        } else {
-            if (CLO > 0 && c0 == CLO) offsets(0);
-            load(x, CIN - CLO, c0 - CLO, c0);
-        }
+        load(c0);
         if (c0) __syncthreads();  // the previous slice has been consumed
         put();
         __syncthreads();
@@ -466,6 +476,155 @@ __global__ __launch_bounds__(64 * NW, 2) void k_conv3_lds(const bf16_t* __restri
             for (int t = 0; t < 4; ++t)
                 store4(acc[p][t][u] + bb, relu, vec, y, yf, (v0 + 16 * t) * COUT + co);
         }
+    }
+}
+
+// 16 output channels from several slices of input (sides n >= 64): a 4 x 64
+// (y, z) tile streams along x over xc output planes with every channel of four
+// planes in LDS, three that the taps read and one being filled from registers
+// loaded an output plane earlier.  A line is fetched once per tile (slice by
+// slice, k_conv3_lds fetched it up to three times), all weights stay in
+// registers, and the one barrier per plane and the stores of the plane to come
+// stand among the MFMAs, whose operands are read five or six pairs of taps
+// ahead (an LDS read under load takes three pairs' MFMAs).
+// CLO > 0: the input is the concatenation [nearest upsampling of lo, x] of a
+// coarse [(n/2)^3][CLO] tensor and a fine [n^3][CIN - CLO] tensor (the
+// decoder's skip), read directly instead of materialised.
+// LDS: [plane mod 4][slice][8-channel half][row][z] in 16-byte units, the
+// halves in phase modulo the banks: a 16-byte read serves lanes 0-3 and 12-15
+// of one with 4-11 of the other in a cycle.  Slices, pairs of taps and channels
+// are added as k_conv3_lds does, bit for bit.
+// Bound: the LDS, one kilobyte read per MFMA (97 % of 128 bytes per cycle).
+// Before (two x-planes per wave, slice by slice) and with this:
+//   48 -> 16 at 128^3: 0.171 -> 0.108 ms, at 256^3 (CLO = 32) 1.24 -> 0.8 ms;
+//   32 -> 16 at 128^3: 0.092 -> 0.063 ms
+constexpr int kPY = 4;                        // tile rows
+constexpr int kPVox = (kPY + 2) * kLPZ;       // staged voxels per plane
+constexpr int kPVP = (kPVox + 15) / 16 * 16;
+template <int CIN, int CLO>
+struct ConvPlanes {
+    static constexpr int NTH = 64 * kPY, NS = CIN / 16, MT = 4;
+    // 16-byte units of a plane: of the coarse tensor (CLO > 0), of x; rounds
+    static constexpr int UL = kPVox * CLO / 8, UX = kPVox * (CIN - CLO) / 8;
+    static constexpr int RL = (UL + NTH - 1) / NTH, RX = (UX + NTH - 1) / NTH, R = RL + RX;
+    static constexpr int SL = 2 * kPVP + 5;  // a slice; 5: its stores fall on other banks
+    static constexpr int PLANE = NS * SL;
+    // operands in flight, pairs of taps (a divisor of all, so that their
+    // registers match from one output plane to the next); the pair before which
+    // the plane being staged has to be complete; pairs per staged unit
+    static constexpr int PAIRS = 14 * NS, AHEAD = NS == 3 ? 6 : 7, SYNC = 9 - (AHEAD - 1);
+    static constexpr int EVERY = (PAIRS - SYNC) / R;
+    static_assert(PAIRS % AHEAD == 0 && SYNC >= 0 && EVERY >= 1 && AHEAD <= 9, "schedule");
+    static constexpr int LDS = 4 * PLANE * 16;
+    static_assert(LDS <= 160 * 1024, "LDS overflow");
+};
+template <int CIN, int CLO>
+__global__ __launch_bounds__(64 * kPY, 1) void k_conv3_planes(
+    const bf16_t* __restrict__ x, const bf16_t* __restrict__ lo, int n, int xc,
+    const bf16_t* __restrict__ w, const float* __restrict__ bias, int relu,
+    bf16_t* __restrict__ y, float* __restrict__ yf, int vec)
+{
+    using G = ConvPlanes<CIN, CLO>;
+    constexpr int COUT = 16, CX = CIN - CLO;
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    u4* buf = reinterpret_cast<u4*>(smem_raw);
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int m = lane & 15, g = lane >> 4, hh = g & 1, side = g >> 1;
+    const int msk = n - 1, nyt = n / kPY, nzt = n / kLZ;
+    const int nb = gridDim.x;
+    int b = blockIdx.x;
+    if ((nb & 7) == 0) b = (b & 7) * (nb >> 3) + (b >> 3);  // rows that share a halo share an L2
+    const int y0 = (b % nyt) * kPY, z0 = (b / nyt) % nzt * kLZ, x0 = b / (nyt * nzt) * xc;
+    // this thread's units: element offsets in a plane of the source, positions
+    // in the staged plane (tails clamped: stored twice)
+    unsigned src[G::R], dst[G::R];
+#pragma unroll
+    for (int q = 0; q < G::R; ++q) {
+        const bool l = q < G::RL;
+        const int units = l ? G::UL : G::UX, hc = (l ? CLO : CX) / 8, sh = l ? 1 : 0;
+        const int e = min(tid + (l ? q : q - G::RL) * G::NTH, units - 1);
+        const int v = e / hc, c = e % hc;
+        const int yy = (y0 - 1 + v / kLPZ) & msk, zz = (z0 - 1 + v % kLPZ) & msk;
+        src[q] = (unsigned)(((yy >> sh) * (n >> sh) + (zz >> sh)) * (8 * hc) + 8 * c);
+        const int cc = c + (l ? 0 : CLO / 8);
+        dst[q] = (unsigned)(cc / 2 * G::SL + cc % 2 * kPVP + v);
+    }
+    u4 pre[G::R];
+    auto load = [&](int q, int xp) __attribute__((always_inline)) {
+        xp &= msk;
+        const bf16_t* pl = q < G::RL ? lo + (size_t)(xp >> 1) * (n >> 1) * (n >> 1) * CLO
+                                     : x + (size_t)xp * n * n * CX;
+        pre[q] = *reinterpret_cast<const u4*>(pl + src[q]);
+    };
+    // the operand of each slice and pair of taps (k of the MFMA as in
+    // k_conv3_lds; nothing in the second half of the 14th pair)
+    u4 wr[G::NS][14];
+#pragma unroll
+    for (int s = 0; s < G::NS; ++s)
+#pragma unroll
+        for (int pr = 0; pr < 14; ++pr)
+            wr[s][pr] = pr == 13 && side
+                            ? u4{}
+                            : *reinterpret_cast<const u4*>(
+                                  w + ((2 * pr + side) * COUT + m) * CIN + 16 * s + 8 * hh);
+    const f4 bb = bias4(bias, 4 * g);
+#pragma unroll
+    for (int d = 0; d < 4; ++d)
+#pragma unroll
+        for (int q = 0; q < G::R; ++q) {
+            load(q, x0 - 1 + d);
+            if (d < 3) buf[d * G::PLANE + dst[q]] = pre[q];
+        }
+    // the 14th pair's second half (which reads a voxel past the 27th tap's)
+    const u4 first = side ? u4{0, 0, 0, 0} : u4{~0u, ~0u, ~0u, ~0u};
+    const u4* own = buf + hh * kPVP + wv * kLPZ + m;  // this lane's half, row and column
+    // output plane i reads staged planes i .. i + 2; q >= PAIRS: the next one's.
+    // A pair's two taps are neighbours in a row, the ends of two rows, or (taps
+    // 8 and 9) those of two planes.
+    u4 a[G::AHEAD][G::MT];
+    auto fetch = [&](int i, int q) __attribute__((always_inline)) {
+        if (q >= G::PAIRS) q -= G::PAIRS, ++i;
+        const int s = q / 14, pr = q % 14, j = 2 * pr % 9, d = 2 * pr / 9;
+        const u4* p = own + ((i + d) & 3) * G::PLANE;
+        if (pr == 4)
+            p = side ? own + ((i + 1) & 3) * G::PLANE : p + 2 * kLPZ + 2;
+        else
+            p += (j / 3) * kLPZ + j % 3 + (j % 3 == 2 && pr < 13 ? 64 : 1) * side;
+#pragma unroll
+        for (int t = 0; t < G::MT; ++t) a[q % G::AHEAD][t] = p[s * G::SL + 16 * t];
+    };
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < G::AHEAD - 1; ++q) fetch(0, q);
+    for (int i = 0; i < xc; ++i) {
+        u4* next = buf + ((i + 3) & 3) * G::PLANE;
+        f4 acc[G::MT];
+#pragma unroll
+        for (int t = 0; t < G::MT; ++t) acc[t] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int q = 0; q < G::PAIRS; ++q) {
+            // plane i + 2 is staged, and plane i - 1's last readers are done
+            if (q == G::SYNC) __syncthreads();
+            fetch(i, q + G::AHEAD - 1);
+            const int u = (q - G::SYNC) / G::EVERY;
+            if (q >= G::SYNC && (q - G::SYNC) % G::EVERY == 0 && u < G::R) {
+                next[dst[u]] = pre[u];  // plane i + 3, among the MFMAs
+                load(u, x0 + i + 3);
+            }
+#pragma unroll
+            for (int t = 0; t < G::MT; ++t) {
+                u4 av = a[q % G::AHEAD][t];
+                if (q % 14 == 13) av &= first;
+                acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                    __builtin_bit_cast(bf8v, wr[q / 14][q % 14]), __builtin_bit_cast(bf8v, av),
+                    acc[t], 0, 0, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);  // or the reads move next to their use
+        }
+        const size_t v0 = ((size_t)(x0 + i) * n + (y0 + wv)) * n + z0 + m;
+#pragma unroll
+        for (int t = 0; t < G::MT; ++t)
+            store4(acc[t] + bb, relu, vec, y, yf, (v0 + 16 * t) * COUT + 4 * g);
     }
 }
 
@@ -1299,22 +1458,40 @@ int vec_ok(const bf16_t* y, const float* yf)
     return ((uintptr_t)y & 7) == 0 && ((uintptr_t)yf & 15) == 0;
 }
 
-template <int CIN, int COUT, int CLO = 0>
+template <int CIN, int COUT>
 int launch_conv_lds(const bf16_t* x, int n, const bf16_t* w, const float* bias, int relu,
-                    bf16_t* y, float* yf, const bf16_t* lo, hipStream_t s)
+                    bf16_t* y, float* yf, hipStream_t s)
 {
     // output channels per workgroup: 16 NT; eight waves where the weights
     // fill most of the LDS (one workgroup per CU), four otherwise (two per CU)
-    constexpr int NT = COUT == 16 ? 1 : COUT == 32 ? 2 : COUT == 96 ? 3 : 4;
+    constexpr int NT = COUT == 32 ? 2 : COUT == 96 ? 3 : 4;
     constexpr int NW = NT >= 3 ? 8 : 4;
     using G = ConvTile<NT, NW>;
     static std::atomic<unsigned> lds_done{0};  // per instantiation: devices set up
-    auto kern = k_conv3_lds<CIN, COUT, NT, NW, CLO>;
+    auto kern = k_conv3_lds<CIN, COUT, NT, NW>;
     UCHECK(isis::ensure_dynamic_lds((const void*)kern, G::LDS, lds_done));
     const long blocks = (long)(n / kLPX) * (n / NW) * (n / kLZ) * (COUT / (16 * NT));
     hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(G::NTH), G::LDS, s, x, n, w, bias, relu,
-                       y, yf, vec_ok(y, yf), lo);
+                       y, yf, vec_ok(y, yf));
     ULAUNCH("k_conv3_lds");
+    return ISIS_OK;
+}
+
+template <int CIN, int CLO>
+int launch_conv_planes(const bf16_t* x, const bf16_t* lo, int n, const bf16_t* w,
+                       const float* bias, int relu, bf16_t* y, float* yf, hipStream_t s)
+{
+    using G = ConvPlanes<CIN, CLO>;
+    static std::atomic<unsigned> lds_done{0};  // per instantiation: devices set up
+    auto kern = k_conv3_planes<CIN, CLO>;
+    UCHECK(isis::ensure_dynamic_lds((const void*)kern, G::LDS, lds_done));
+    // planes per workgroup: as many as leave one workgroup per CU
+    const long cols = (long)(n / kPY) * (n / kLZ);
+    int xc = n;
+    while (xc > 2 && cols * (n / xc) < 256) xc /= 2;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(cols * (n / xc))), dim3(G::NTH), G::LDS, s, x, lo, n,
+                       xc, w, bias, relu, y, yf, vec_ok(y, yf));
+    ULAUNCH("k_conv3_planes");
     return ISIS_OK;
 }
 
@@ -1350,7 +1527,12 @@ int launch_conv(const bf16_t* x, int n, int cin, const bf16_t* w, const float* b
 #define CONV_CASE(CI, CO)                                                                   \
     if (cin == CI && cout == CO) {                                                          \
         if constexpr (CI > 16)                                                              \
-            if (lds) return launch_conv_lds<CI, CO>(x, n, w, bias, relu, y, yf, nullptr, s); \
+            if (lds) {                                                                      \
+                if constexpr (CO == 16)                                                     \
+                    return launch_conv_planes<CI, 0>(x, nullptr, n, w, bias, relu, y, yf, s); \
+                else                                                                        \
+                    return launch_conv_lds<CI, CO>(x, n, w, bias, relu, y, yf, s); \
+            }                                                                               \
         if (n == 32)  /* rows per workgroup: what fits the LDS */                           \
             return launch_conv_small<CI, (CO % 64 == 0 ? 4 : CO % 32 == 0 ? 2 : 1), 32,     \
                                      (CI > 64 ? 2 : 4), 1>(x, w, bias, CO, relu, y, yf, s); \
@@ -1384,7 +1566,7 @@ int launch_conv_cat(const bf16_t* lo, const bf16_t* skip, int n, int cin, int cl
              clo, cout, n);
         return ISIS_ERR_UNSUPPORTED;
     }
-    return launch_conv_lds<48, 16, 32>(skip, n, w, bias, relu, y, nullptr, lo, s);
+    return launch_conv_planes<48, 32>(skip, lo, n, w, bias, relu, y, nullptr, s);
 }
 
 int dw_chunk(long nvox) { return (int)std::min<long>(nvox, 4096); }

@@ -101,6 +101,13 @@ def test_conv_forward_staged(cin, cout, n):
         assert np.array_equal(gb.reshape(got.shape)[sel], U.bf16(got[sel]).astype(np.float32))
 
 
+@pytest.mark.parametrize("cin,cout,n", [(32, 16, 64), (32, 16, 128), (64, 32, 64), (32, 96, 64),
+                                        (64, 128, 64)])
+def test_conv_forward_staged_gradient_shapes(cin, cout, n):
+    """The data gradients' channel counts on the staged kernels."""
+    test_conv_forward_staged(cin, cout, n)
+
+
 @pytest.mark.parametrize("cin,cout,n", [(16, 16, 64), (16, 48, 64), (32, 32, 64), (64, 64, 64),
                                         (32, 96, 64), (48, 16, 64)])
 def test_conv_unaligned_outputs(cin, cout, n):
@@ -270,6 +277,23 @@ def test_network_forward(n):
     got = out.cpu().numpy().reshape(n, n, n)
     assert _rel(got, ref) < 1e-2, _rel(got, ref)
     assert np.allclose(guess.cpu().numpy().reshape(n, n, n), cold + got, rtol=0, atol=1e-7)
+
+
+@pytest.mark.parametrize("n", [16, 64, 128])
+def test_prediction_equals_forward(n):
+    """The prediction's shortcuts (upsampled and skip inputs read in place at
+    side 64 and up) add what the training forward adds, bit for bit: with
+    output, guess or both asked for, at any alignment of theirs."""
+    from paper_1307_6748_amd import warmstart as W
+    eta, cold, _ = (torch.from_numpy(t).cuda() for t in _sample(n, 12))
+    net = W.WarmStart(params=W.init_params(5))
+    ref = net.forward(eta, cold, 0.7)
+    both = torch.empty(n ** 3 + 1, dtype=torch.float32, device="cuda")[1:]
+    guess = net.predict(eta, cold, 0.7, guess=torch.empty_like(eta), out=both)
+    only = net.predict(eta, cold, 0.7, out=torch.empty_like(ref))
+    assert torch.equal(both, ref) and torch.equal(only, ref)
+    assert torch.equal(guess.flatten(), cold.flatten() + ref.double())
+    assert torch.equal(net.predict(eta, cold, 0.7).flatten(), guess.flatten())
 
 
 def test_network_gradient_and_adam():
