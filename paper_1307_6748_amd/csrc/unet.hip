@@ -648,12 +648,24 @@ constexpr int kRY = 4, kRW = 1;                    // tile rows, rows per wave
 constexpr int kRPY = kRY + 2, kRPZ = kLZ + 2;
 constexpr int kRVox = kRPY * kRPZ;                 // staged voxels per plane
 constexpr int kRPad = kRVox + (48 - kRVox % 32) % 32;  // = 16 mod 32
+// HEAD: the network's last convolution in a prediction, whose 16 channels only
+// the head reads: no output y, but out and guess as k_head makes them (each
+// NULL if not wanted; the channels' products added in its order, passed from
+// the four lanes of a voxel to the next four).
+struct HeadOut {
+    const float* wh;
+    const double* cold;
+    float* out;
+    double* guess;
+};
+template <bool HEAD>
 __global__ __launch_bounds__(kThreads, 2) void k_conv3_ring(const bf16_t* __restrict__ x, int n,
                                                             int xc, const bf16_t* __restrict__ w,
                                                             const float* __restrict__ bias,
                                                             int cout, int relu,
                                                             bf16_t* __restrict__ y,
-                                                            float* __restrict__ yf, int vec)
+                                                            float* __restrict__ yf, int vec,
+                                                            HeadOut head)
 {
     constexpr int CIN = 16;
     constexpr int PV = kRVox * 2;                        // 16-byte input vectors per plane
@@ -703,6 +715,12 @@ __global__ __launch_bounds__(kThreads, 2) void k_conv3_ring(const bf16_t* __rest
     for (int t = 0; t < 27; ++t)
         bw[t] = *reinterpret_cast<const s4*>(w + ((size_t)t * cout + 16 * cg + m) * CIN + 4 * g);
     const f4 bb = bias4(bias, 16 * cg + 4 * g);
+    float wh[4] = {}, whb = 0.f;  // this lane's channels of the head, its bias
+    if constexpr (HEAD) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) wh[i] = head.wh[4 * g + i];
+        whb = head.wh[16];
+    }
     f4 acc[3][kRW][4];
     // input plane xp (in buf[par]): taps 0..8 into S (output plane xp + 1,
     // begun here), 9..17 into M (xp), 18..26 into F (xp - 1, stored)
@@ -749,6 +767,27 @@ __global__ __launch_bounds__(kThreads, 2) void k_conv3_ring(const bf16_t* __rest
             // D[row = 4g + r][col = m]: channel 16 cg + 4g + r, voxel z0 + 16t + m
 #pragma unroll
             for (int r = 0; r < kRW; ++r) {
+                if constexpr (HEAD) {
+                    const size_t v = ((size_t)(xp - 1) * n + (y0 + wv * kRW + r)) * n + z0 + lane;
+                    const double cold = head.guess ? head.cold[v] : 0.0;
+                    float res = 0.f;
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) {
+                        float s = whb;
+                        const f4 d = F[r][t] + bb;
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            if (q > 0) s = __shfl(s, 16 * (q - 1) + m, 64);
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) s += bf2f(f2bf(fmaxf(d[i], 0.f))) * wh[i];
+                        }
+                        s = __shfl(s, 48 + m, 64);
+                        if (g == t) res = s;
+                    }
+                    if (head.out) head.out[v] = res;
+                    if (head.guess) head.guess[v] = cold + (double)res;
+                    continue;
+                }
                 const size_t v0 = ((size_t)(xp - 1) * n + (y0 + wv * kRW + r)) * n + z0 + m;
 #pragma unroll
                 for (int t = 0; t < 4; ++t) {
@@ -1156,26 +1195,30 @@ __global__ __launch_bounds__(kThreads) void k_chan_sum(bf16_t* __restrict__ a,
         part[(long)blockIdx.x * C + tid] = ((red[tid] + red[C + tid]) + red[2 * C + tid]) + red[3 * C + tid];
 }
 
-// Weights for the data gradient: wt[t'][ci][co] = w[26 - t][co][ci] (bf16).
-__global__ void k_flip_weights(const float* __restrict__ w, int cin, int cout,
-                               bf16_t* __restrict__ wt)
+// BF16 weights of all convolutions (one per blockIdx.y) from the FP32
+// parameters: as they are, or, FLIP, for the data gradient: wt[t'][ci][co] =
+// w[26 - t'][co][ci].  (A launch per layer: 14 times 2.4 or 4.5 us.)
+struct ConvWeights {
+    const float* src[14];
+    bf16_t* dst[14];
+    int cin[14], cout[14];
+};
+template <bool FLIP>
+__global__ void k_conv_weights(ConvWeights a)
 {
+    const int c = blockIdx.y, cin = a.cin[c], cout = a.cout[c];
     const long total = 27L * cin * cout;
+    const float* w = a.src[c];
     for (long e = (long)blockIdx.x * blockDim.x + threadIdx.x; e < total;
          e += (long)gridDim.x * blockDim.x) {
-        const int co = (int)(e % cout);
-        const long r = e / cout;
-        const int ci = (int)(r % cin);
-        const int tp = (int)(r / cin);
-        wt[e] = f2bf(w[((long)(26 - tp) * cout + co) * cin + ci]);
+        long from = e;
+        if (FLIP) {
+            const int co = (int)(e % cout);
+            const long r = e / cout;
+            from = ((26 - r / cin) * cout + co) * cin + r % cin;
+        }
+        a.dst[c][e] = f2bf(w[from]);
     }
-}
-
-__global__ void k_to_bf16(const float* __restrict__ src, long total, bf16_t* __restrict__ dst)
-{
-    for (long e = (long)blockIdx.x * blockDim.x + threadIdx.x; e < total;
-         e += (long)gridDim.x * blockDim.x)
-        dst[e] = f2bf(src[e]);
 }
 
 // ---------------------------------------------------------------------------
@@ -1509,21 +1552,27 @@ int launch_conv_small(const bf16_t* x, const bf16_t* w, const float* bias, int c
     return ISIS_OK;
 }
 
+template <bool HEAD>
+int launch_conv_ring(const bf16_t* x, int n, const bf16_t* w, const float* bias, int cout,
+                     int relu, bf16_t* y, float* yf, const HeadOut& head, hipStream_t s)
+{
+    // planes per workgroup: a power of two up to 64 that leaves >= 512
+    // workgroups (two per CU)
+    const long cols = (long)(n / kRY) * (n / kLZ) * (cout / 16);
+    int xc = 2;
+    while (xc < 64 && cols * (n / (2 * xc)) >= 512) xc *= 2;
+    hipLaunchKernelGGL(k_conv3_ring<HEAD>, dim3((unsigned)(cols * (n / xc))), dim3(kThreads), 0, s,
+                       x, n, xc, w, bias, cout, relu, y, yf, vec_ok(y, yf), head);
+    ULAUNCH("k_conv3_ring");
+    return ISIS_OK;
+}
+
 int launch_conv(const bf16_t* x, int n, int cin, const bf16_t* w, const float* bias, int cout,
                 int relu, bf16_t* y, float* yf, hipStream_t s)
 {
     const bool lds = n >= kLZ;  // powers of two: whole tiles
-    if (lds && cin == 16 && (cout == 16 || cout == 32 || cout == 48)) {
-        // planes per workgroup: a power of two up to 64 that leaves >= 512
-        // workgroups (two per CU)
-        const long cols = (long)(n / kRY) * (n / kLZ) * (cout / 16);
-        int xc = 2;
-        while (xc < 64 && cols * (n / (2 * xc)) >= 512) xc *= 2;
-        hipLaunchKernelGGL(k_conv3_ring, dim3((unsigned)(cols * (n / xc))), dim3(kThreads), 0, s,
-                           x, n, xc, w, bias, cout, relu, y, yf, vec_ok(y, yf));
-        ULAUNCH("k_conv3_ring");
-        return ISIS_OK;
-    }
+    if (lds && cin == 16 && (cout == 16 || cout == 32 || cout == 48))
+        return launch_conv_ring<false>(x, n, w, bias, cout, relu, y, yf, HeadOut{}, s);
 #define CONV_CASE(CI, CO)                                                                   \
     if (cin == CI && cout == CO) {                                                          \
         if constexpr (CI > 16)                                                              \
@@ -1731,14 +1780,28 @@ Plan make_plan(int n, int training, char* base)
 // fuse_cat: the last decoder stage reads its upsampled and skip inputs
 // directly (prediction; training keeps the concatenation for the weight
 // gradient).
-int run_forward(const Plan& P, const float* params, hipStream_t s, bool fuse_cat = false)
+template <bool FLIP>
+int launch_conv_weights(const float* params, bf16_t* const* dst, hipStream_t s)
 {
+    ConvWeights a;
     for (int c = 0; c < 14; ++c) {
-        const long e = 27L * kConvs[c].cin * kConvs[c].cout;
-        hipLaunchKernelGGL(k_to_bf16, dim3(grid_of(e)), dim3(kThreads), 0, s,
-                           params + param_offset(c), e, P.wf[c]);
-        ULAUNCH("k_to_bf16");
+        a.src[c] = params + param_offset(c);
+        a.dst[c] = dst[c];
+        a.cin[c] = kConvs[c].cin;
+        a.cout[c] = kConvs[c].cout;
     }
+    hipLaunchKernelGGL(k_conv_weights<FLIP>, dim3(54, 14), dim3(kThreads), 0, s, a);
+    ULAUNCH("k_conv_weights");
+    return ISIS_OK;
+}
+
+// predict: out and guess come from the head, which joins the last convolution
+// on sides that k_conv3_ring takes, as the last decoder stage's concatenation
+// joins its convolution; no activation is then kept for a backward pass.
+int run_forward(const Plan& P, const float* params, const double* phi_cold, float* out,
+                double* guess, bool predict, hipStream_t s)
+{
+    TRY(launch_conv_weights<false>(params, P.wf, s));
     auto conv = [&](int c, const bf16_t* x) -> int {
         const int lv = level_of(c);
         return launch_conv(x, P.n[lv], kConvs[c].cin, P.wf[c],
@@ -1783,14 +1846,23 @@ int run_forward(const Plan& P, const float* params, hipStream_t s, bool fuse_cat
     TRY(upcat(P.o[9], 2, 64, P.o[3], 32, P.c10));
     TRY(conv(10, P.c10));
     TRY(conv(11, P.o[10]));
-    if (fuse_cat && P.n[0] >= kLZ) {
+    const bool fuse = predict && P.n[0] >= kLZ;
+    if (fuse) {
         TRY(launch_conv_cat(P.o[11], P.o[1], P.n[0], 48, 32, P.wf[12],
                             params + param_offset(12) + 27L * 48 * 16, 16, 1, P.o[12], s));
     } else {
         TRY(upcat(P.o[11], 1, 32, P.o[1], 16, P.c12));
         TRY(conv(12, P.c12));
     }
+    const HeadOut head{params + param_offset(14), phi_cold, out, guess};
+    if (fuse)
+        return launch_conv_ring<true>(P.o[12], P.n[0], P.wf[13],
+                                      params + param_offset(13) + 27L * 16 * 16, 16, 1, nullptr,
+                                      nullptr, head, s);
     TRY(conv(13, P.o[12]));
+    hipLaunchKernelGGL(k_head, dim3(grid_of(P.nv[0])), dim3(kThreads), 0, s, P.o[13], head.wh,
+                       P.nv[0], out, phi_cold, guess);
+    ULAUNCH("k_head");
     return ISIS_OK;
 }
 
@@ -1798,12 +1870,7 @@ int run_forward(const Plan& P, const float* params, hipStream_t s, bool fuse_cat
 // P.grad (the head's part is written by the caller).
 int run_backward(const Plan& P, const float* params, hipStream_t s)
 {
-    for (int c = 1; c < 14; ++c) {
-        hipLaunchKernelGGL(k_flip_weights, dim3(grid_of(27L * kConvs[c].cin * kConvs[c].cout)),
-                           dim3(kThreads), 0, s, params + param_offset(c), kConvs[c].cin,
-                           kConvs[c].cout, P.wb[c]);
-        ULAUNCH("k_flip_weights");
-    }
+    TRY(launch_conv_weights<true>(params, P.wb, s));
     // back(c, g, x, dx): g = d(o_c) (masked in place), weight and bias
     // gradients from the layer input x, dx = d(x) (skipped when NULL).
     auto back = [&](int c, bf16_t* g, const bf16_t* x, bf16_t* dx) -> int {
@@ -1894,11 +1961,7 @@ int isis_unet_predict(const float* params, const double* eta, const double* phi_
     hipLaunchKernelGGL(k_make_input, dim3(grid_of(P.nv[0])), dim3(kThreads), 0, s, eta, phi_cold,
                        a, P.nv[0], P.in);
     ULAUNCH("k_make_input");
-    TRY(run_forward(P, params, s, true));
-    hipLaunchKernelGGL(k_head, dim3(grid_of(P.nv[0])), dim3(kThreads), 0, s, P.o[13],
-                       params + param_offset(14), P.nv[0], out, phi_cold, guess);
-    ULAUNCH("k_head");
-    return ISIS_OK;
+    return run_forward(P, params, phi_cold, out, guess, true, s);
 }
 
 int isis_unet_forward(const float* params, const double* eta, const double* phi_cold, double a,
@@ -1919,10 +1982,7 @@ int isis_unet_forward(const float* params, const double* eta, const double* phi_
     hipLaunchKernelGGL(k_make_input, dim3(grid_of(P.nv[0])), dim3(kThreads), 0, s, eta, phi_cold,
                        a, P.nv[0], P.in);
     ULAUNCH("k_make_input");
-    TRY(run_forward(P, params, s));
-    hipLaunchKernelGGL(k_head, dim3(grid_of(P.nv[0])), dim3(kThreads), 0, s, P.o[13],
-                       params + param_offset(14), P.nv[0], P.out, nullptr, nullptr);
-    ULAUNCH("k_head");
+    TRY(run_forward(P, params, nullptr, P.out, nullptr, false, s));
     if (out) UCHECK(hipMemcpyAsync(out, P.out, P.nv[0] * sizeof(float), hipMemcpyDeviceToDevice, s));
     return ISIS_OK;
 }
@@ -2096,9 +2156,13 @@ int isis_conv3_flip_weights(const float* w, int cin, int cout, uint16_t* wt, voi
         uerr("conv3_flip_weights: invalid arguments");
         return ISIS_ERR_INVALID_ARG;
     }
-    hipLaunchKernelGGL(k_flip_weights, dim3(grid_of(27L * cin * cout)), dim3(kThreads), 0,
-                       (hipStream_t)stream, w, cin, cout, wt);
-    ULAUNCH("k_flip_weights");
+    ConvWeights a{};
+    a.src[0] = w;
+    a.dst[0] = wt;
+    a.cin[0] = cin;
+    a.cout[0] = cout;
+    hipLaunchKernelGGL(k_conv_weights<true>, dim3(54), dim3(kThreads), 0, (hipStream_t)stream, a);
+    ULAUNCH("k_conv_weights");
     return ISIS_OK;
 }
 
