@@ -619,7 +619,10 @@ struct isis_mg {
     LevP<float> L32[kMaxLevels];
     double* partial;  // 2 * kReduceBlocks
     double* scal;     // 16: [0] reduction result, [8] safeguard counter (64-bit)
-    double* host;     // pinned, 16
+    // 16, pinned and coherent: kernels write the judges' sums and the count of
+    // safeguarded updates straight into it (a copy of 8 bytes on the stream
+    // after a judge kept the device idle 3 us longer)
+    double* host;
     double* tmp0;     // finest-level scratch field (workspace)
     char err[512];
     // smoothing timing (profiling on): one event pair per smoothing step of
@@ -798,10 +801,9 @@ int fine_rms(isis_mg* H, const M& m, const TF* phi, const double* eta, double* r
 {
     const int n = H->d.N;
     const long n3 = (long)n * n * n;
-    int r = launch_defect_norm<TF, M>(m, n, H->L64[0].h, phi, eta, res, H->partial, H->scal, H->s,
+    int r = launch_defect_norm<TF, M>(m, n, H->L64[0].h, phi, eta, res, H->partial, H->host, H->s,
                                       H->err, uscale, uoffset);
     if (r) return r;
-    HIP_TRY(H->err, hipMemcpyAsync(H->host, H->scal, sizeof(double), hipMemcpyDeviceToHost, H->s));
     HIP_TRY(H->err, hipStreamSynchronize(H->s));
     *out = std::sqrt(H->host[0] / (double)n3);
     return ISIS_OK;
@@ -829,9 +831,8 @@ int fine_rms_fp32(isis_mg* H, const M& m, const float* phi, const float* eta, do
     hipLaunchKernelGGL(kern, dim3(g), dim3(kBlock), 0, H->s, m, n, 1.0 / (h * h), 1.0, 0.0, phi, eta,
                        nullptr, H->partial);
     LAUNCH_CHECK(H->err, "k_defect_norm_tiled");
-    hipLaunchKernelGGL(k_reduce, dim3(1), dim3(kBlock), 0, H->s, H->partial, g, H->scal);
+    hipLaunchKernelGGL(k_reduce, dim3(1), dim3(kBlock), 0, H->s, H->partial, g, H->host);
     LAUNCH_CHECK(H->err, "k_reduce");
-    HIP_TRY(H->err, hipMemcpyAsync(H->host, H->scal, sizeof(double), hipMemcpyDeviceToHost, H->s));
     HIP_TRY(H->err, hipStreamSynchronize(H->s));
     *out = std::sqrt(H->host[0] / (double)n3);
     return ISIS_OK;
@@ -1194,13 +1195,11 @@ int solve_impl(isis_mg* H, const M64& m64, const M32& m32, const isis_model_para
             if ((r = launch_restrict<double>(H->L64[l - 1].n, H->L64[l - 1].eta, H->L64[l].eta,
                                              H->s, H->err, mixed ? H->L32[l - 1].eta : nullptr)))
                 return r;
-        hipLaunchKernelGGL(k_reduce, dim3(1), dim3(kBlock), 0, H->s, H->partial, g, H->scal);
+        hipLaunchKernelGGL(k_reduce, dim3(1), dim3(kBlock), 0, H->s, H->partial, g, H->host);
         LAUNCH_CHECK(H->err, "k_reduce");
         hipLaunchKernelGGL(k_reduce, dim3(1), dim3(kBlock), 0, H->s, H->partial + kReduceBlocks, g,
-                           H->scal + 1);
+                           H->host + 1);
         LAUNCH_CHECK(H->err, "k_reduce");
-        HIP_TRY(H->err, hipMemcpyAsync(H->host, H->scal, 2 * sizeof(double),
-                                       hipMemcpyDeviceToHost, H->s));
         HIP_TRY(H->err, hipStreamSynchronize(H->s));
         r_ref = std::sqrt(H->host[0] / (double)n3);
         cold_rms = std::sqrt(H->host[1] / (double)n3);
@@ -1214,10 +1213,8 @@ int solve_impl(isis_mg* H, const M64& m64, const M32& m32, const isis_model_para
                            density, cold, cold32 ? H->L32[0].phi : nullptr, M32::kVar,
                            -shift32 * M32::kVar, H->partial);
         LAUNCH_CHECK(H->err, "k_cold_start_sumsq");
-        hipLaunchKernelGGL(k_reduce, dim3(1), dim3(kBlock), 0, H->s, H->partial, g, H->scal);
+        hipLaunchKernelGGL(k_reduce, dim3(1), dim3(kBlock), 0, H->s, H->partial, g, H->host);
         LAUNCH_CHECK(H->err, "k_reduce");
-        HIP_TRY(H->err,
-                hipMemcpyAsync(H->host, H->scal, sizeof(double), hipMemcpyDeviceToHost, H->s));
         HIP_TRY(H->err, hipStreamSynchronize(H->s));
         cold_rms = std::sqrt(H->host[0] / (double)n3);
         if ((r = fine_rms<double, M64>(H, m64, cold, density, nullptr, &r_ref))) return r;
@@ -1444,8 +1441,8 @@ int solve_impl(isis_mg* H, const M64& m64, const M32& m32, const isis_model_para
         F.phi = field;
     }
     unsigned long long* hits_host = reinterpret_cast<unsigned long long*>(H->host + 8);
-    HIP_TRY(H->err, hipMemcpyAsync(hits_host, H->hits(), sizeof(unsigned long long),
-                                   hipMemcpyDeviceToHost, H->s));
+    hipLaunchKernelGGL(k_copy_count, dim3(1), dim3(1), 0, H->s, H->hits(), hits_host);
+    LAUNCH_CHECK(H->err, "k_copy_count");
     HIP_TRY(H->err, hipStreamSynchronize(H->s));
     if (st && H->profile) {
         for (int q = 0; q < H->ntimed; ++q) {
@@ -1618,7 +1615,8 @@ int isis_mg_create(const isis_mg_desc* desc, isis_mg_t** out)
     H->s = (hipStream_t)desc->stream;
     H->err[0] = 0;
     if (hipGetDevice(&H->device) != hipSuccess ||
-        hipHostMalloc((void**)&H->host, 16 * sizeof(double), hipHostMallocDefault) != hipSuccess) {
+        hipHostMalloc((void**)&H->host, 16 * sizeof(double),
+                      hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
         fmt_err(g_err, "HIP device or pinned host buffer unavailable");
         delete H;
         return ISIS_ERR_HIP;

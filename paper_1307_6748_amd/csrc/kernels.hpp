@@ -230,6 +230,13 @@ __global__ __launch_bounds__(kBlock) void k_reduce(const double* __restrict__ pa
     if (threadIdx.x == 0) out[0] = s;
 }
 
+// *to = *from (to: pinned host memory).
+__global__ void k_copy_count(const unsigned long long* __restrict__ from,
+                             unsigned long long* __restrict__ to)
+{
+    *to = *from;
+}
+
 // f -= sum[0] / total (removes the mean of the singular linear problem).
 template <class T>
 __global__ __launch_bounds__(kBlock) void k_sub_mean(long total, T* __restrict__ f,
