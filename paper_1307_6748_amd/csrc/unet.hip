@@ -309,14 +309,16 @@ __global__ __launch_bounds__(kThreads, 1) void k_conv3_small(const bf16_t* __res
 // contiguous ranges with x fastest, so neighbouring planes share an L2.
 // Bound: with one plane per wave and the weights read from memory by each
 // wave, the weight reads (32 lines of 32 bytes per operand) held the kernel at
-// 0.38-0.55 PFLOP/s; now it reaches 0.73 to 0.92, held by the LDS (NT = 2: one
+// 0.38-0.55 PFLOP/s; now it reaches 0.73 to 1.05, held by the LDS (NT = 2: one
 // and a half operands per MFMA) and by the L2: a 32-byte slice of a voxel
 // fetches its whole line, which is often gone before the next slice.  Plane by
 // plane the staging needs three address registers where voxel by voxel it took
-// eleven and spilled (32 -> 32 at 128^3: 0.139 -> 0.127 ms).  Each output adds
-// slices, taps and channels in the order of k_conv3.
-//   64 -> 64 at 64^3: 0.135 -> 0.080 ms; 64 -> 128 at 64^3: 0.297 -> 0.138 ms;
-//   96 -> 32 at 128^3: 0.71 -> 0.45 ms
+// eleven and spilled, and the operands are read a step or three before their
+// MFMAs (the compiler's own order put the reads next to their use).  Each
+// output adds slices, taps and channels in the order of k_conv3.
+//   64 -> 64 at 64^3: 0.135 -> 0.063 ms (0.080 in the compiler's order);
+//   128 -> 64 at 64^3: 0.248 -> 0.110 ms (0.143); 64 -> 128 at 64^3: 0.296 ->
+//   0.119 ms (0.139); 96 -> 32 at 128^3: 0.72 -> 0.47 ms (0.45)
 constexpr int kLZ = 64;                            // output columns (z)
 constexpr int kLPX = 2, kLPZ = kLZ + 2;            // output planes; staged columns
 template <int NT, int NW>
@@ -333,6 +335,7 @@ struct ConvTile {
     static constexpr int TR = ((kLPX + 2) * TU + NTH - 1) / NTH;
     static_assert(TU % 2 == 0 && TU > 0, "a thread keeps its channel half");
     static constexpr int LDS = (XU + WU) * 16;
+    static constexpr int AHEAD = NT == 2 ? 4 : 2;  // operands in flight: what the registers hold
 };
 
 template <int CIN, int COUT, int NT, int NW>
@@ -431,6 +434,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_conv3_lds(const bf16_t* __restri
                 wl[(k / (16 * NT) * 2 + h) * 16 * NT + k % (16 * NT)] = wr[q];
         }
     };
+    const u4 first = side ? u4{0, 0, 0, 0} : u4{~0u, ~0u, ~0u, ~0u};
     for (int c0 = 0; c0 < CIN; c0 += 16) {
         // (the next slice held in registers during this one's MFMAs measured
         // 10 to 30 % slower: the registers cost waves)
@@ -438,29 +442,43 @@ __global__ __launch_bounds__(64 * NW, 2) void k_conv3_lds(const bf16_t* __restri
         if (c0) __syncthreads();  // the previous slice has been consumed
         put();
         __syncthreads();
+        // step q: plane q & 1 of pair q / 2 of the taps, its operands read
+        // AHEAD - 1 steps before.  Pair 13 is tap 26 alone: lanes
+        // of the second half read its (valid) addresses and zero what they get.
+        u4 a[G::AHEAD][4], bw[G::AHEAD / 2 + 1][NT];
+        auto fetch = [&](int q) __attribute__((always_inline)) {
+            const int pr = q / 2, p = q % 2, t0 = 2 * pr, t1 = pr < 13 ? t0 + 1 : t0;
+            const int o0 = ((t0 / 9) * G::PY + (t0 / 3) % 3) * kLPZ + t0 % 3;
+            const int o1 = ((t1 / 9) * G::PY + (t1 / 3) % 3) * kLPZ + t1 % 3;
+            const u4* src = th + o0 + (side ? o1 - o0 : 0) + p * G::PY * kLPZ;
 #pragma unroll
-        for (int pr = 0; pr < 14; ++pr) {
-            // pair 13: taps 26 and (nonexistent) 27; lanes of the second half
-            // read tap 26's (valid) addresses and zero what they loaded
-            const bool live = pr < 13 || side == 0;
-            const int tap = live ? 2 * pr + side : 26;
-            const int off = ((tap / 9) * G::PY + (tap / 3) % 3) * kLPZ + tap % 3;
-            bf8v bw[NT];
+            for (int t = 0; t < 4; ++t) a[q % G::AHEAD][t] = src[16 * t];
+            if (p == 0) {
+                const u4* ws = wh + 32 * NT * t0 + (side ? 32 * NT * (t1 - t0) : 0);
 #pragma unroll
-            for (int u = 0; u < NT; ++u) {
-                bw[u] = *reinterpret_cast<const bf8v*>(wh + (tap * 2 * NT + u) * 16);
-                if (!live) bw[u] = bf8v{};
+                for (int u = 0; u < NT; ++u) bw[pr % (G::AHEAD / 2 + 1)][u] = ws[16 * u];
             }
+        };
 #pragma unroll
-            for (int p = 0; p < kLPX; ++p)
+        for (int q = 0; q < G::AHEAD - 1; ++q) fetch(q);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    bf8v a = *reinterpret_cast<const bf8v*>(th + off + p * G::PY * kLPZ + 16 * t);
-                    if (!live) a = bf8v{};
+        for (int q = 0; q < 28; ++q) {
+            if (q + G::AHEAD - 1 < 28) fetch(q + G::AHEAD - 1);
 #pragma unroll
-                    for (int u = 0; u < NT; ++u)
-                        acc[p][t][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bw[u], a, acc[p][t][u], 0, 0, 0);
+            for (int t = 0; t < 4; ++t) {
+                u4 av = a[q % G::AHEAD][t];
+                if (q >= 26) av &= first;
+#pragma unroll
+                for (int u = 0; u < NT; ++u) {
+                    u4 bv = bw[q / 2 % (G::AHEAD / 2 + 1)][u];
+                    if (q >= 26) bv &= first;
+                    acc[q & 1][t][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                        __builtin_bit_cast(bf8v, bv), __builtin_bit_cast(bf8v, av),
+                        acc[q & 1][t][u], 0, 0, 0);
                 }
+            }
+            __builtin_amdgcn_sched_barrier(0);  // or the reads move next to their use
         }
     }
     // the weights are the row operand: D[row = 4g + r][col = m] is channel
