@@ -30,8 +30,6 @@ TOL = {"fp64": 1e-12, "mixed": 1e-6}
 def test_cycles_of_small_grids(orc, name, n, pre, post, fw, pw, precision):
     from paper_1307_6748_amd import solver as S
     om, sp, a = models(name)
-    if precision == "mixed" and 0 in (pre, post):
-        pytest.skip("FP64 schedule only")
     box = 4.0 * n
     eta = density(n, 400 + n)
     cfg = orc.Cfg(nu_pre=pre, nu_post=post, restrict_fw=bool(fw), prolong_w=bool(pw))
