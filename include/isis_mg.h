@@ -534,10 +534,11 @@ size_t isis_patch_workspace_size(int n);
  * the RMS defect over the inside cells (boundary values from the final
  * field) is <= tol (absolute) or max_sweeps sweeps are done.  phi: in the
  * initial field (its outside values are not changed), out the solution.
- * workspace: device, 256-byte aligned, >= isis_patch_workspace_size(n).
+ * workspace: device, 256-byte aligned, isis_patch_workspace_size(n) bytes
+ * (n^3 + 256 fewer are accepted; the sweeps then read the masks themselves).
  * *sweeps_out, *rms_out (host, may be NULL): sweeps made, final RMS.
  * Returns ISIS_OK, ISIS_ERR_NOT_CONVERGED or ISIS_ERR_DIVERGED; synchronises
- * the stream once per block. */
+ * the stream every few blocks. */
 int isis_patch_solve(const isis_model_params* p, double a, int n, double h, double* phi,
                      const double* eta, const double* mask, const double* u_int, int block,
                      int max_sweeps, double tol, void* workspace, size_t workspace_bytes,

@@ -970,7 +970,8 @@ int launch_bottom(isis_mg* H, const M& m, LevP<T>* L, int l, double* updates, bo
 // asked for one launch per colour (temporal_block 0).  Below, the bottom
 // kernel.  At 128^3 the halo's work exceeds what the launches save (symmetron,
 // double precision, us per cycle: 55 + 45 + 23 in blocks against 6 x 11.8 +
-// 11 + 12 per colour).
+// 11 + 12 per colour; f(R), single precision: 23 + 40 + 34 + 23 against
+// 8 x 8.6 + 17 + 15).
 inline bool block_level(const isis_mg* H, int n)
 {
     return H->tb >= 1 && (n == 32 || n == 64);
