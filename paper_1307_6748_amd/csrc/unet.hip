@@ -318,7 +318,7 @@ __global__ __launch_bounds__(kThreads, 1) void k_conv3_small(const bf16_t* __res
 // output adds slices, taps and channels in the order of k_conv3.
 //   64 -> 64 at 64^3: 0.135 -> 0.063 ms (0.080 in the compiler's order);
 //   128 -> 64 at 64^3: 0.248 -> 0.110 ms (0.143); 64 -> 128 at 64^3: 0.296 ->
-//   0.119 ms (0.139); 96 -> 32 at 128^3: 0.72 -> 0.47 ms (0.45)
+//   0.119 ms (0.139); 96 -> 32 at 128^3: 0.72 -> 0.45 ms (0.47)
 constexpr int kLZ = 64;                            // output columns (z)
 constexpr int kLPX = 2, kLPZ = kLZ + 2;            // output planes; staged columns
 template <int NT, int NW>
