@@ -28,6 +28,7 @@
 #include "fused_sweep.hpp"
 #include "kernels.hpp"
 #include "pair_kernels.hpp"
+#include "patch_schedule.hpp"
 
 using namespace isis;
 
@@ -1568,10 +1569,6 @@ int static_scratch(double** out, char* err)
     return ISIS_OK;
 }
 
-// Most blocks of sweeps a patch solve queues between two looks at its state:
-// 64 blocks of 4 sweeps are about 600 launches, which queue faster than they run.
-constexpr int kPatchBatch = 64;
-
 // Workspace of a patch solve: the pre-iteration field, the norm's partial sums,
 // the control block and a byte per cell (k_patch_kind).  Without room for the
 // last (callers that sized it when there was none) the sweeps read the masks.
@@ -2075,26 +2072,23 @@ int isis_patch_solve(const isis_model_params* p, double a, int n, double h, doub
         int rc = judge(0);
         if (!rc) rc = fetch();
         // Blocks of sweeps, judged on the device after each; the host reads
-        // the state once per batch.  Launches queued behind the block that
-        // meets tol store nothing, so a batch is as long as the last factor
-        // predicts (a host round trip per block was a quarter of a 68^3
-        // solve, and the launches after it started on an idle device).
+        // the state once per batch (next_patch_batch).  Launches queued behind
+        // the block that meets tol store nothing (a host round trip per block
+        // was a quarter of a 68^3 solve, and the launches after it started on
+        // an idle device).
         int queued = 0, batch = 1;  // sweeps queued so far; blocks in the next batch
         while (!rc && !st.stop) {
             const double r0 = st.rms;
             for (int q = 0; q < batch && queued < max_sweeps && !rc; ++q) {
                 const int count = std::min(block, max_sweeps - queued);
-                for (int b = 0; b < 2 * count && !rc; ++b) rc = halfsweep(b & 1);
+                for (int b = 0; b < count && !rc; ++b)
+                    for (int colour = 0; colour < 2 && !rc; ++colour) rc = halfsweep(colour);
                 queued += count;
                 if (!rc) rc = judge(count);
             }
             if (!rc) rc = fetch();
             if (rc || st.stop) break;
-            const double rho = std::pow(st.rms / r0, 1.0 / batch);
-            const double left = std::log(tol / st.rms) / std::log(rho);
-            batch = rho < 1.0 && left >= 1.0 ? (int)std::min(std::ceil(left), 4.0 * batch)
-                                             : std::min(2 * batch, 8);
-            batch = std::max(1, std::min(batch, kPatchBatch));
+            batch = next_patch_batch(batch, r0, st.rms, tol);
         }
         if (rc) return rc;
         if (sweeps_out) *sweeps_out = st.sweeps;

@@ -98,3 +98,55 @@ def test_patch_with_nothing_finite_to_judge():
     rc, sweeps, rms = S.patch_solve(sp, a, 0.7, dev(1e200 * phi), dev(eta), dev(mask), dev(u_int),
                                     block=3, check=False)
     assert (rc, sweeps) == (A.ISIS_ERR_DIVERGED, 3) and not np.isfinite(rms)
+
+
+def _blocks_queued(h, tol):
+    """Blocks that a solve with RMS h[k] after k blocks queues until it has seen
+    h[k] <= tol (csrc/patch_schedule.hpp)."""
+    done, batch = 0, 1
+    while True:
+        r0, done = h[done], done + batch
+        if done >= len(h) or min(h[:done + 1]) <= tol:
+            return done
+        rho = (h[done] / r0) ** (1.0 / batch)
+        left = np.log(tol / h[done]) / np.log(rho) if rho < 1.0 else 0.0
+        batch = 1 if left < 1.0 else int(min(np.ceil(left), 4.0 * batch, 64.0))
+
+
+@pytest.mark.parametrize("name", ["symmetron_a1", "fofr"])
+@pytest.mark.parametrize("room", [True, False])
+def test_patch_launches_past_the_end_store_nothing(name, room):
+    """A solve stopped by its tolerance, with blocks already queued behind the one
+    that met it, leaves the field, sweep count and RMS of one stopped there by
+    its sweep limit, which queues none: bit for bit."""
+    from paper_1307_6748_amd import _capi as A
+    _, sp, a = models(name)
+    n, block, h = 16, 4, 0.7
+    phi, eta, mask, u_int = _patch(name, n, 90)
+    e, mk, ui = dev(eta), dev(mask), dev(u_int)
+    nbytes = A.lib().isis_patch_workspace_size(n) - (0 if room else n ** 3 + 256)
+    ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+    pc = sp.c()
+
+    def solve(sweeps, tol):
+        g = dev(phi)
+        count, got = C.c_int(), C.c_double()
+        ptr = [C.c_void_p(t.data_ptr()) for t in (g, e, mk, ui)]
+        rc = A.lib().isis_patch_solve(C.byref(pc), a, n, h, *ptr, block, sweeps, tol,
+                                      C.c_void_p(ws.data_ptr()), nbytes, C.byref(count),
+                                      C.byref(got),
+                                      C.c_void_p(torch.cuda.current_stream().cuda_stream))
+        return rc, cubic(g, n), count.value, got.value
+
+    ref = [solve(block * k, 1e-300) for k in range(25)]
+    rms = [r[3] for r in ref]
+    past = 0
+    for k in range(2, 25):
+        tol = 1.0001 * rms[k]
+        if min(rms[:k]) <= tol:
+            continue
+        rc, field, sweeps, got = solve(10000, tol)
+        assert rc == A.ISIS_OK and sweeps == ref[k][2] == block * k and got == rms[k]
+        assert np.array_equal(field, ref[k][1])
+        past += _blocks_queued(rms, tol) > k
+    assert past >= 3  # else this test asks nothing
