@@ -69,8 +69,10 @@ struct PatchState {
 };
 
 // One colour of the red-black Newton-Gauss-Seidel sweep over the inside
-// cells; masked cells keep their values.  With state: nothing is stored once
-// state->stop is set (asked last, so that the load is not waited for first).
+// cells; masked cells keep their values and cost a mask (a refinement fills
+// what it will of its patch's box: 128^3 f(R) with 3 % inside, 10.8 us; 22.8
+// with the operator formed everywhere).  With state: nothing is done once
+// state->stop is set.
 template <class M>
 __global__ __launch_bounds__(kBlock) void k_masked_halfsweep(
     M m, int n, double ih2, double* __restrict__ phi, const double* __restrict__ eta,
@@ -82,10 +84,11 @@ __global__ __launch_bounds__(kBlock) void k_masked_halfsweep(
     for_planes(n, n, n >> 1, [&](int i, int j, int kk) __attribute__((always_inline)) {
         const int k = 2 * kk + ((i + j + colour) & 1);
         const long c = cell(n, i, j, k);
+        if (!(mask[c] > 0.0) || stop) return;
         double L, D;
         masked_op(m, n, ih2, phi, eta, mask, u_int, u_pre, i, j, k, L, D);
         const double eps = L - (sigma ? sigma[c] : 0.0);
-        if (mask[c] > 0.0 && !stop) phi[c] = phi[c] - m.limit(gs_step(eps, D));
+        phi[c] = phi[c] - m.limit(gs_step(eps, D));
     });
 }
 
@@ -129,6 +132,7 @@ __global__ __launch_bounds__(kBlock) void k_patch_halfsweep(
         const int k = 2 * kk + ((i + j + colour) & 1);
         const long c = cell(n, i, j, k);
         const int kd = kind[c];
+        if (kd == 0 || stop) return;
         const double e = eta[c];
         double nb[6], enb[6], L, D;
         const double p = gather(phi, n, i, j, k, nb);
@@ -139,7 +143,7 @@ __global__ __launch_bounds__(kBlock) void k_patch_halfsweep(
             for (int f = 0; f < 6; ++f) enb[f] = SO::stage(nb[f], exptab);
             SO::eval(m, p, nb, SO::stage(p, exptab), enb, e, ih2, L, D);
         }
-        if (kd != 0 && !stop) phi[c] = p - m.limit(gs_step(L, D));
+        phi[c] = p - m.limit(gs_step(L, D));
     });
 }
 
