@@ -535,7 +535,7 @@ size_t isis_patch_workspace_size(int n);
  * field) is <= tol (absolute) or max_sweeps sweeps are done.  phi: in the
  * initial field (its outside values are not changed), out the solution.
  * workspace: device, 256-byte aligned, isis_patch_workspace_size(n) bytes
- * (n^3 + 256 fewer are accepted; the sweeps then read the masks themselves).
+ * (n^3 + 256 fewer are accepted).
  * *sweeps_out, *rms_out (host, may be NULL): sweeps made, final RMS.
  * Returns ISIS_OK, ISIS_ERR_NOT_CONVERGED or ISIS_ERR_DIVERGED; synchronises
  * the stream every few blocks. */

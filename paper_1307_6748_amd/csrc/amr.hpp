@@ -70,9 +70,17 @@ struct PatchState {
 
 // One colour of the red-black Newton-Gauss-Seidel sweep over the inside
 // cells; masked cells keep their values and cost a mask (a refinement fills
-// what it will of its patch's box: 128^3 f(R) with 3 % inside, 10.8 us; 22.8
+// what it will of its patch's box: 128^3 f(R) with 3 % inside, 8.5 us; 22.0
 // with the operator formed everywhere).  With state: nothing is done once
 // state->stop is set.
+// Bound: launch and two rounds of cache latency.  (A byte per cell saying
+// whether it is inside and has ghosts, so that cells without any need not read
+// the masks, split every wave in two paths, for a row has ghosts at its ends:
+// per launch of a 68^3 symmetron patch 7.5 us, now 6.9; f(R) 9.2, 8.0; 128^3
+// f(R) half inside 21, 17.  Only where the masks' traffic counts did it gain:
+// 128^3 symmetron, all inside, 17.4, now 18.7.  Both colours, or two sweeps,
+// in one launch on LDS blocks with a halo took 15.5 and 43 us: each thread's
+// few cells are a chain of LDS and double-precision latency.)
 template <class M>
 __global__ __launch_bounds__(kBlock) void k_masked_halfsweep(
     M m, int n, double ih2, double* __restrict__ phi, const double* __restrict__ eta,
@@ -89,61 +97,6 @@ __global__ __launch_bounds__(kBlock) void k_masked_halfsweep(
         masked_op(m, n, ih2, phi, eta, mask, u_int, u_pre, i, j, k, L, D);
         const double eps = L - (sigma ? sigma[c] : 0.0);
         phi[c] = phi[c] - m.limit(gs_step(eps, D));
-    });
-}
-
-// What a patch solve's sweeps ask of the masks, once per solve and cell: 0
-// outside, 1 inside with six inside neighbours, 2 inside with a ghost.
-__global__ __launch_bounds__(kBlock) void k_patch_kind(int n, const double* __restrict__ mask,
-                                                       unsigned char* __restrict__ kind)
-{
-    for_planes(n, n, n, [&](int i, int j, int k) __attribute__((always_inline)) {
-        double nb[6];
-        const double m = gather(mask, n, i, j, k, nb);
-        bool all = true;
-#pragma unroll
-        for (int f = 0; f < 6; ++f) all = all && nb[f] > 0.0;
-        kind[cell(n, i, j, k)] = m > 0.0 ? (all ? 1 : 2) : 0;
-    });
-}
-
-// k_masked_halfsweep for a patch solve (no FAS source): cells without ghosts,
-// nearly all, read nine values (a byte of kind among them) instead of sixteen,
-// and f(R)'s exponentials come from the table in LDS.  Bound: launch and one
-// round of cache latency.  68^3 symmetron patch: 7.3 -> 6.8 us per launch.
-// (Both colours, or two sweeps, in one launch on LDS blocks with a halo took
-// 15.5 and 43 us: each thread's few cells are a chain of LDS and
-// double-precision latency.)
-template <class M>
-__global__ __launch_bounds__(kBlock) void k_patch_halfsweep(
-    M m, int n, double ih2, double* __restrict__ phi, const double* __restrict__ eta,
-    const double* __restrict__ mask, const double* __restrict__ u_int,
-    const double* __restrict__ u_pre, const unsigned char* __restrict__ kind, int colour,
-    const PatchState* __restrict__ state)
-{
-    using SO = StageOp<double, M>;
-    __shared__ double exptab[SO::kTable ? kExpTable : 1];
-    if constexpr (SO::kTable) {
-        exp_table_fill(exptab);
-        __syncthreads();
-    }
-    const int stop = state->stop;
-    for_planes(n, n, n >> 1, [&](int i, int j, int kk) __attribute__((always_inline)) {
-        const int k = 2 * kk + ((i + j + colour) & 1);
-        const long c = cell(n, i, j, k);
-        const int kd = kind[c];
-        if (kd == 0 || stop) return;
-        const double e = eta[c];
-        double nb[6], enb[6], L, D;
-        const double p = gather(phi, n, i, j, k, nb);
-        if (kd == 2) {
-            masked_op(m, n, ih2, phi, eta, mask, u_int, u_pre, i, j, k, L, D);
-        } else {
-#pragma unroll
-            for (int f = 0; f < 6; ++f) enb[f] = SO::stage(nb[f], exptab);
-            SO::eval(m, p, nb, SO::stage(p, exptab), enb, e, ih2, L, D);
-        }
-        phi[c] = p - m.limit(gs_step(L, D));
     });
 }
 

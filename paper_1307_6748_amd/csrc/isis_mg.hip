@@ -1569,13 +1569,11 @@ int static_scratch(double** out, char* err)
     return ISIS_OK;
 }
 
-// Workspace of a patch solve: the pre-iteration field, the norm's partial sums,
-// the control block and a byte per cell (k_patch_kind).  Without room for the
-// last (callers that sized it when there was none) the sweeps read the masks.
-size_t patch_bytes(int n, bool kinds)
+// Workspace of a patch solve: the pre-iteration field, the norm's partial sums
+// and the control block.
+size_t patch_bytes(int n)
 {
-    const size_t n3 = (size_t)n * n * n;
-    return (n3 + 2 * kReduceBlocks + 16) * sizeof(double) + 256 + (kinds ? n3 + 256 : 0);
+    return ((size_t)n * n * n + 2 * kReduceBlocks + 16) * sizeof(double) + 256;
 }
 
 }  // namespace
@@ -2005,7 +2003,9 @@ int isis_op_masked_halfsweep(const isis_model_params* p, double a, int n, double
 
 size_t isis_patch_workspace_size(int n)
 {
-    return op_grid_ok(n, 2) ? patch_bytes(n, true) : 0;
+    // (a byte per cell and 256 more than the solve asks for: the figure callers
+    // have been given)
+    return op_grid_ok(n, 2) ? patch_bytes(n) + (size_t)n * n * n + 256 : 0;
 }
 
 int isis_patch_solve(const isis_model_params* p, double a, int n, double h, double* phi,
@@ -2020,9 +2020,9 @@ int isis_patch_solve(const isis_model_params* p, double a, int n, double h, doub
         return ISIS_ERR_INVALID_ARG;
     }
     if (!ptrs_aligned({phi, eta, mask, u_int}) || !aligned(workspace, 256) ||
-        workspace_bytes < patch_bytes(n, false)) {
+        workspace_bytes < patch_bytes(n)) {
         fmt_err(g_err, "patch_solve: aligned arrays and a 256-byte aligned workspace of >= %zu "
-                       "bytes needed", patch_bytes(n, false));
+                       "bytes needed", patch_bytes(n));
         return ISIS_ERR_INVALID_ARG;
     }
     hipStream_t s = (hipStream_t)stream;
@@ -2034,12 +2034,6 @@ int isis_patch_solve(const isis_model_params* p, double a, int n, double h, doub
     const dim3 dg = plane_grid(n, (long)n * n, kReduceBlocks), hg = plane_grid(n, (long)n * n / 2);
     return with_model<double>(*p, a, [&](auto m) {
         using M = decltype(m);
-        unsigned char* kind = nullptr;
-        if (workspace_bytes >= patch_bytes(n, true)) {
-            kind = reinterpret_cast<unsigned char*>(state) + 16 * sizeof(double);
-            hipLaunchKernelGGL(k_patch_kind, plane_grid(n), dim3(kBlock), 0, s, n, mask, kind);
-            LAUNCH_CHECK(g_err, "k_patch_kind");
-        }
         // RMS of the defect over the inside cells, boundary values from phi,
         // which becomes the next block's pre-iteration field in the same pass
         auto judge = [&](int sweeps) -> int {
@@ -2052,13 +2046,9 @@ int isis_patch_solve(const isis_model_params* p, double a, int n, double h, doub
             return (int)ISIS_OK;
         };
         auto halfsweep = [&](int colour) -> int {
-            if (kind)
-                hipLaunchKernelGGL((k_patch_halfsweep<M>), hg, dim3(kBlock), 0, s, m, n, ih2, phi,
-                                   eta, mask, u_int, pre, kind, colour, state);
-            else
-                hipLaunchKernelGGL((k_masked_halfsweep<M>), hg, dim3(kBlock), 0, s, m, n, ih2, phi,
-                                   eta, nullptr, mask, u_int, pre, colour, state);
-            LAUNCH_CHECK(g_err, "k_patch_halfsweep");
+            hipLaunchKernelGGL((k_masked_halfsweep<M>), hg, dim3(kBlock), 0, s, m, n, ih2, phi,
+                               eta, nullptr, mask, u_int, pre, colour, state);
+            LAUNCH_CHECK(g_err, "k_masked_halfsweep");
             return (int)ISIS_OK;
         };
         PatchState st{0.0, 0, 0};
