@@ -96,7 +96,7 @@ __global__ __launch_bounds__(kBlock) void k_masked_halfsweep(
         double L, D;
         masked_op(m, n, ih2, phi, eta, mask, u_int, u_pre, i, j, k, L, D);
         const double eps = L - (sigma ? sigma[c] : 0.0);
-        phi[c] = phi[c] - m.limit(gs_step(eps, D));
+        phi[c] = phi[c] - m.limit(eps / D);
     });
 }
 

@@ -79,8 +79,6 @@ __global__ __launch_bounds__(512) void k_block_sweep(M m, BlockArgs<T> a)
     T* ph = reinterpret_cast<T*>(smem_raw);
     T* ex = ph + G::CELLS;
     T* aux = ph + G::CELLS * (STAGED ? 2 : 1);  // DESC: the block's defect; PROL: the coarse window
-    __shared__ double exptab[SO::kTable ? kExpTable : 1];
-    if constexpr (SO::kTable) exp_table_fill(exptab);
 
     const int tid = threadIdx.x;
     const int n = a.n, msk = n - 1;
@@ -158,14 +156,13 @@ __global__ __launch_bounds__(512) void k_block_sweep(M m, BlockArgs<T> a)
             }
         }
     }
-    if constexpr (SO::kTable) __syncthreads();
 #pragma unroll
     for (int q = 0; q < G::PER; ++q) {
         const int o = lx[q] * SX + ly[q] * SY + lz[q];
         if ((q + 1) * G::NT <= G::PAIRS || tid + q * G::NT < G::PAIRS) {
             *reinterpret_cast<V*>(ph + o) = f2[q];
             if constexpr (STAGED)
-                *reinterpret_cast<V*>(ex + o) = V{SO::stage(f2[q].x, exptab), SO::stage(f2[q].y, exptab)};
+                *reinterpret_cast<V*>(ex + o) = V{SO::stage(f2[q].x), SO::stage(f2[q].y)};
         }
     }
     __syncthreads();
@@ -239,10 +236,10 @@ __global__ __launch_bounds__(512) void k_block_sweep(M m, BlockArgs<T> a)
                 if constexpr (M::kGuard) {
                     if (own(q)) hits += m.guarded(p, e);
                 }
-                const T v = p - m.limit(gs_step(L - s, D));
+                const T v = p - m.limit((L - s) / D);
                 ph[o] = v;
                 if constexpr (STAGED) {
-                    if (DESC || colour == 0) ex[o] = SO::stage(v, exptab);
+                    if (DESC || colour == 0) ex[o] = SO::stage(v);
                 }
             }
         }

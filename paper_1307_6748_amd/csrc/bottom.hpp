@@ -95,12 +95,12 @@ __device__ __forceinline__ void lane_neighbours(T v, int lane, T nb[6])
 // sweep again, are added).  Returns the lane's value.
 template <class T, class M>
 __device__ __forceinline__ T coarsest_sweeps(const M& m, T ih2, T p, T e, T s, int nu,
-                                             const double* exptab, unsigned& hits)
+                                             unsigned& hits)
 {
     using SO = StageOp<T, M>;
     const int lane = threadIdx.x & 63;
     const int par = ((lane >> 4) + (lane >> 2) + lane) & 1;
-    T ep = SO::stage(p, exptab);
+    T ep = SO::stage(p);
     for (int it = 0; it < nu; ++it) {
         bool moved = false;
         unsigned h = 0;
@@ -113,10 +113,10 @@ __device__ __forceinline__ T coarsest_sweeps(const M& m, T ih2, T p, T e, T s, i
                 T L, D;
                 SO::eval(m, p, nb, ep, enb, e, ih2, L, D);
                 if constexpr (M::kGuard) h += m.guarded(p, e);
-                const T v = p - m.limit(gs_step(L - s, D));
+                const T v = p - m.limit((L - s) / D);
                 moved = moved || v != p;
                 p = v;
-                if constexpr (SO::kStaged) ep = SO::stage(p, exptab);
+                if constexpr (SO::kStaged) ep = SO::stage(p);
             }
         }
         hits += h;
@@ -137,7 +137,6 @@ __global__ __launch_bounds__((bottom_threads<T, M>())) void k_bottom_cycle(M m, 
     constexpr int NT = bottom_threads<T, M>();
     constexpr int N0 = 4 << (NLEV - 1), N3 = N0 * N0 * N0;
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    __shared__ double exptab[SO::kTable ? kExpTable : 1];
     T* base = reinterpret_cast<T*>(smem_raw);
     const int tid = threadIdx.x;
     T *phi[NLEV], *ex[NLEV], *eta[NLEV], *sig[NLEV], *hat[NLEV];
@@ -159,10 +158,6 @@ __global__ __launch_bounds__((bottom_threads<T, M>())) void k_bottom_cycle(M m, 
                 off += 3 * n3;
             }
         }
-    }
-    if constexpr (SO::kTable) {
-        exp_table_fill(exptab);
-        __syncthreads();
     }
     // cell t of a colour's list on a side-n grid (t < n^3 / 2)
     auto cell_of = [](int n, int t, int colour, int& i, int& j, int& k)
@@ -195,7 +190,7 @@ __global__ __launch_bounds__((bottom_threads<T, M>())) void k_bottom_cycle(M m, 
     };
     auto put = [&](int q, int c, T v) __attribute__((always_inline)) {
         phi[q][c] = v;
-        if constexpr (STAGED) ex[q][c] = SO::stage(v, exptab);
+        if constexpr (STAGED) ex[q][c] = SO::stage(v);
     };
 
     // the first level's cells of this thread: density and source, per colour
@@ -261,7 +256,7 @@ __global__ __launch_bounds__((bottom_threads<T, M>())) void k_bottom_cycle(M m, 
                 T p, L, D;
                 oper(q, n, i, j, k, e, a.ih2[q], p, L, D);
                 if constexpr (M::kGuard) hits += m.guarded(p, e);
-                put(q, (i * n + j) * n + k, p - m.limit(gs_step(L - s, D)));
+                put(q, (i * n + j) * n + k, p - m.limit((L - s) / D));
             });
             __syncthreads();
         }
@@ -390,7 +385,7 @@ __global__ __launch_bounds__((bottom_threads<T, M>())) void k_bottom_cycle(M m, 
     if (tid < 64) {  // the 4^3 grid in the first wave
         constexpr int q = NLEV - 1;
         phi[q][tid] = coarsest_sweeps(m, a.ih2[q], phi[q][tid], eta[q][tid], sig[q][tid],
-                                      a.nu_coarse, exptab, hits);
+                                      a.nu_coarse, hits);
     }
     __syncthreads();
     static_for<0, NLEV - 1>([&](auto rc) {

@@ -75,18 +75,6 @@ __device__ __forceinline__ void static_for(F&& f)
     }
 }
 
-// The Newton-Gauss-Seidel step eps / D of the per-level kernels: the quotient
-// in single precision, in double precision the product with the refined
-// reciprocal (within an ulp of the quotient, a third of its instructions).
-template <class T>
-__device__ __forceinline__ T gs_step(T eps, T D)
-{
-    if constexpr (sizeof(T) == 4)
-        return eps / D;
-    else
-        return eps * recip(D);
-}
-
 // Visits the items (i, j, k) of a [planes][rows][cols] grid: planes over
 // gridDim.y, the rows x cols items of a plane over gridDim.x, both strided, so
 // any grid size is safe.  One float product splits a plane's index (exact up
@@ -157,7 +145,7 @@ __global__ __launch_bounds__(kBlock) void k_halfsweep(M m, int n, T ih2, T* __re
         const T s = sigma ? sigma[c] : T(0);
         m.op(p, nb, e, ih2, L, D);
         if constexpr (M::kGuard) hits += m.guarded(p, e);
-        phi[c] = p - m.limit(gs_step(L - s, D));
+        phi[c] = p - m.limit((L - s) / D);
     });
     guard_flush(m, hits);
 }

@@ -150,3 +150,26 @@ def test_patch_launches_past_the_end_store_nothing(name, room):
         assert np.array_equal(field, ref[k][1])
         past += _blocks_queued(rms, tol) > k
     assert past >= 3  # else this test asks nothing
+
+
+@pytest.mark.parametrize("masked", [False, True])
+@pytest.mark.parametrize("n", [6, 32])
+def test_halfsweep_steps_are_quotients(n, masked):
+    """The Newton-Gauss-Seidel step is the correctly rounded quotient L / D in
+    double precision.  Linear model, m2 = 1, h = 1, density 1, whole numbers on
+    the black cells and zero on the red: L is a whole number, D = -7, and a red
+    cell becomes sum(neighbours) / 7, bit for bit."""
+    from paper_1307_6748_amd import solver as S
+    sp = S.linear(1.3, 1.0)
+    rng = np.random.default_rng(7)
+    i = np.arange(n)
+    red = (i[:, None, None] + i[None, :, None] + i[None, None, :]) % 2 == 0
+    phi = np.where(red, 0.0, rng.integers(-10 ** 6, 10 ** 6, (n, n, n)).astype(float))
+    nb = sum(np.roll(phi, s, axis) for axis in range(3) for s in (-1, 1))
+    ref = np.where(red, nb / 7.0, phi)
+    one, g = np.ones((n, n, n)), dev(phi)
+    if masked:
+        S.masked_halfsweep(sp, 1.0, 1.0, g, dev(one), dev(one), dev(phi), dev(phi), colour=0)
+    else:
+        S.halfsweep(sp, 1.0, 1.0, g, dev(one), colour=0)
+    assert np.array_equal(cubic(g, n), ref)
