@@ -13,7 +13,8 @@
 
 namespace isis {
 
-// One thread per coarse cell, the 64 fine values read directly (small levels).
+// One thread per coarse cell, the 64 fine values read directly (small levels),
+// the 16 of a plane before their sums (200^3: 25 us; 36 row by row).
 template <class T>
 __global__ __launch_bounds__(kBlock) void k_restrict_fw(int nf, const T* __restrict__ fine,
                                                         T* __restrict__ coarse)
@@ -21,18 +22,25 @@ __global__ __launch_bounds__(kBlock) void k_restrict_fw(int nf, const T* __restr
     const int nc = nf >> 1;
     const T w[4] = {T(0.125), T(0.375), T(0.375), T(0.125)};
     for_planes(nc, nc, nc, [&](int I, int J, int K) __attribute__((always_inline)) {
+        const int i[4] = {wrap_dec(2 * I, nf), 2 * I, 2 * I + 1, wrap_inc(2 * I + 1, nf)};
+        const int j[4] = {wrap_dec(2 * J, nf), 2 * J, 2 * J + 1, wrap_inc(2 * J + 1, nf)};
+        const int k[4] = {wrap_dec(2 * K, nf), 2 * K, 2 * K + 1, wrap_inc(2 * K + 1, nf)};
         T sx = T(0);
 #pragma unroll
         for (int a = 0; a < 4; ++a) {
-            const int i = wrap(2 * I - 1 + a, nf);
+            T v[4][4];
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                const T* row = fine + ((long)i[a] * nf + j[b]) * nf;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) v[b][c] = row[k[c]];
+            }
             T sy = T(0);
 #pragma unroll
             for (int b = 0; b < 4; ++b) {
-                const int j = wrap(2 * J - 1 + b, nf);
-                const T* row = fine + ((long)i * nf + j) * nf;
                 T sz = T(0);
 #pragma unroll
-                for (int c = 0; c < 4; ++c) sz += w[c] * row[wrap(2 * K - 1 + c, nf)];
+                for (int c = 0; c < 4; ++c) sz += w[c] * v[b][c];
                 sy += w[b] * sz;
             }
             sx += w[a] * sy;

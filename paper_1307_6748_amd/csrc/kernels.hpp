@@ -59,7 +59,6 @@ struct Vec2 {
 
 __device__ __forceinline__ int wrap_dec(int i, int n) { return i == 0 ? n - 1 : i - 1; }
 __device__ __forceinline__ int wrap_inc(int i, int n) { return i == n - 1 ? 0 : i + 1; }
-__device__ __forceinline__ int wrap(int i, int n) { return i < 0 ? i + n : i >= n ? i - n : i; }
 __device__ __forceinline__ long cell(int n, int i, int j, int k)
 {
     return ((long)i * n + j) * n + k;
@@ -75,27 +74,55 @@ __device__ __forceinline__ void static_for(F&& f)
     }
 }
 
-// Visits the items (i, j, k) of a [planes][rows][cols] grid: planes over
-// gridDim.y, the rows x cols items of a plane over gridDim.x, both strided, so
-// any grid size is safe.  One float product splits a plane's index (exact up
-// to 2^23 items with the correction by one) where flat 64-bit indices cost
-// every item two 64-bit divisions: 128^3 in double precision, symmetron, a
-// half-sweep 12.0 -> 11.8 us (it waits for the caches).
+// Row of item t of a grid of rows of `cols` items, inv = 1 / cols: one float
+// product, exact up to 2^23 items with the correction by one (flat 64-bit
+// indices cost every item two 64-bit divisions: 128^3 in double precision,
+// symmetron, a half-sweep 12.0 -> 11.8 us; it waits for the caches).
 __device__ __forceinline__ int split_row(int t, int cols, float inv)
 {
     const int j = (int)((float)t * inv);
     const int k = t - j * cols;
     return j + (k < 0 ? -1 : k >= cols ? 1 : 0);
 }
+
+// The walk of a kernel over the items (i, j, k) of a [planes][rows][cols] grid:
+// planes over gridDim.y, a plane's items over gridDim.x, both strided, so any
+// grid size is safe.  Planes of fewer than kBlock items are walked as one list,
+// gridDim.y = 1: a workgroup per plane would leave its lanes idle and spread a
+// few hundred cells over all XCDs, whose L2s then pass them on between kernels
+// (8^3 f(R), double precision: 98 us a cycle in one workgroup per kernel, 110
+// in eight).  Host side: plane_grid().
+struct PlaneWalk {
+    int rows, cols, planes, items;  // items of one step of gridDim.y
+    bool list;
+    float inv, invr;
+    __device__ __forceinline__ PlaneWalk(int planes_, int rows_, int cols_)
+        : rows(rows_), cols(cols_), planes(planes_), items(rows_ * cols_), list(items < kBlock),
+          inv(1.0f / (float)cols_), invr(1.0f / (float)rows_)
+    {
+        if (list) {
+            items *= planes;
+            planes = 1;
+        }
+    }
+    // item t of step p
+    __device__ __forceinline__ void at(int p, int t, int& i, int& j, int& k) const
+    {
+        const int r = split_row(t, cols, inv);
+        k = t - r * cols;
+        i = list ? split_row(r, rows, invr) : p;
+        j = list ? r - i * rows : r;
+    }
+};
 template <class F>
 __device__ __forceinline__ void for_planes(int planes, int rows, int cols, F&& f)
 {
-    const float inv = 1.0f / (float)cols;
-    const int items = rows * cols;
-    for (int i = blockIdx.y; i < planes; i += gridDim.y)
-        for (int t = blockIdx.x * kBlock + threadIdx.x; t < items; t += gridDim.x * kBlock) {
-            const int j = split_row(t, cols, inv);
-            f(i, j, t - j * cols);
+    const PlaneWalk w(planes, rows, cols);
+    for (int p = blockIdx.y; p < w.planes; p += gridDim.y)
+        for (int t = blockIdx.x * kBlock + threadIdx.x; t < w.items; t += gridDim.x * kBlock) {
+            int i, j, k;
+            w.at(p, t, i, j, k);
+            f(i, j, k);
         }
 }
 

@@ -173,3 +173,61 @@ def test_halfsweep_steps_are_quotients(n, masked):
     else:
         S.halfsweep(sp, 1.0, 1.0, g, dev(one), colour=0)
     assert np.array_equal(cubic(g, n), ref)
+
+
+# Sides where the walk over planes changes: a plane of fewer than 256 items is
+# walked with the others as one list (half planes: up to n = 22; planes: 14), and
+# from 16 workgroups on (n = 62) their number per plane is rounded up.
+@pytest.mark.parametrize("n", [2, 14, 16, 22, 24, 60, 62, 66])
+def test_walk_over_planes(orc, n):
+    """Every cell is visited once.  Tolerances: a few roundings of a dozen terms."""
+    from paper_1307_6748_amd import solver as S
+    h = 0.8
+    for name in ("symmetron_a1", "fofr"):
+        om, sp, a = models(name)
+        phi, eta = field_for(name, n, 200 + n), density(n, 201 + n)
+        if n > 2:
+            mask = np.where(np.random.default_rng(n).random((n, n, n)) < 0.3, 1.0, -1.0)
+            mask[:1], mask[:, :1], mask[:, :, :1] = -1.0, -1.0, -1.0
+            g = dev(phi)
+            S.masked_halfsweep(sp, a, h, g, dev(eta), dev(mask), dev(phi), dev(phi), colour=1)
+            ref = orc.masked_halfsweep(om, h, phi, eta, mask, phi, phi, colour=1)
+            assert np.max(np.abs(cubic(g, n) - ref)) <= 1e-13 * (np.abs(ref).max() + 1.0)
+        g = dev(phi)
+        S.halfsweep(sp, a, h, g, dev(eta), colour=1)
+        ref = orc.halfsweep(om, h, phi, eta, None, 1)
+        assert np.max(np.abs(cubic(g, n) - ref)) <= 1e-13 * (np.abs(ref).max() + 1.0)
+        scale = 12.0 * np.exp(np.abs(phi).max()) * (np.abs(phi).max() + 1.0) / h ** 2
+        ref = orc.defect(om, h, phi, eta)
+        got = cubic(S.defect(sp, a, h, dev(phi), dev(eta)), n)
+        assert np.max(np.abs(got - ref)) <= 1e-14 * (scale + np.abs(ref).max())
+        force = S.force(sp, a, h * n, field=dev(phi), potential=dev(eta))
+        for f, r in zip(force, orc.force(om, h, phi, eta)):
+            assert np.max(np.abs(cubic(f, n) - r)) <= 1e-14 * (np.abs(r).max() + 10.0)
+
+
+@pytest.mark.parametrize("nc", [2, 14, 16, 60, 62])
+def test_walk_over_coarse_planes(orc, nc):
+    """The same for the kernels that walk the coarse cells."""
+    from paper_1307_6748_amd import solver as S
+    n = 2 * nc
+    rng = np.random.default_rng(nc)
+    fine, ch = rng.standard_normal((n, n, n)), rng.standard_normal((nc, nc, nc))
+    c = ch + rng.standard_normal((nc, nc, nc))
+    assert np.max(np.abs(cubic(S.restrict(dev(fine)), nc) - orc.restrict(fine))) <= 1e-15 * np.abs(fine).max()
+    assert np.max(np.abs(cubic(S.restrict_fw(dev(fine)), nc) - orc.restrict_fw(fine))) <= 4e-15 * np.abs(fine).max()
+    for gpu, cpu in ((S.prolong_correct, orc.prolong_correct),
+                     (S.prolong_correct_w, orc.prolong_correct_w)):
+        g = dev(fine)
+        gpu(g, dev(c), dev(ch))
+        ref = cpu(fine, c, ch)
+        assert np.max(np.abs(cubic(g, n) - ref)) <= 1e-14 * (np.abs(ref).max() + 1.0)
+    om, sp, a = models("symmetron_a1")
+    phi, eta = field_for("symmetron_a1", n, nc), density(n, nc)
+    eta_c, phi_c = orc.restrict(eta), orc.restrict(phi)
+    for fw in (False, True):
+        d = orc.defect(om, 0.7, phi, eta)
+        ref = orc.defect(om, 1.4, phi_c, eta_c) - (orc.restrict_fw(d) if fw else orc.restrict(d))
+        got = S.fas_descend(sp, a, 0.7, dev(phi), dev(eta), None, dev(eta_c), full_weighting=fw)
+        assert np.max(np.abs(cubic(got[0], nc) - phi_c)) <= 2e-15
+        assert np.max(np.abs(cubic(got[2], nc) - ref)) <= 1e-14 * (12.0 / 0.49 + np.abs(ref).max())
