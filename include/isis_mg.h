@@ -477,7 +477,8 @@ const char* isis_unet_last_error(void);
 /* y[v][co] = sum_t sum_ci x[v + d_t][ci] w[t][co][ci] + bias[co], ReLU if
  * relu != 0; periodic n^3 grid (n a power of two >= 2).  (cin, cout) must be
  * one of the network's shapes or their transposes.  y (bf16) and/or yf
- * (FP32) receive the result; bias may be NULL.  With weights prepared by
+ * (FP32) receive the result; bias may be NULL.  All arrays need their
+ * elements' alignment only.  With weights prepared by
  * isis_conv3_flip_weights and the channel counts swapped, this is the data
  * gradient of a convolution. */
 int isis_conv3_fwd(const uint16_t* x, int n, int cin, const uint16_t* w, const float* bias,

@@ -55,6 +55,10 @@ typedef __bf16 bf4v __attribute__((ext_vector_type(4)));
 typedef __bf16 bf8v __attribute__((ext_vector_type(8)));
 typedef float f4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u4 __attribute__((ext_vector_type(4)));  // (HIP's uint4 arrays go to scratch)
+// The convolutions' inputs and weights: callers' tensors, aligned as their bf16
+// elements are.  (The same one load instruction.)
+typedef s4 s4_any __attribute__((aligned(2)));
+typedef u4 u4_any __attribute__((aligned(2)));
 
 constexpr int kThreads = 256;
 constexpr int kMaxGrid = 65536;
@@ -139,8 +143,8 @@ __global__ __launch_bounds__(kThreads) void k_conv3(const bf16_t* __restrict__ x
             const bf16_t* wt = w + ((3 * t9 + k) * cout + co0 + m) * CIN + 4 * g;
 #pragma unroll
             for (int s = 0; s < NS; ++s) {
-                xa[p][k][s] = *reinterpret_cast<const s4*>(xs + 16 * s);
-                wa[p][k][s] = *reinterpret_cast<const s4*>(wt + 16 * s);
+                xa[p][k][s] = *reinterpret_cast<const s4_any*>(xs + 16 * s);
+                wa[p][k][s] = *reinterpret_cast<const s4_any*>(wt + 16 * s);
             }
         }
     };
@@ -211,7 +215,7 @@ __global__ __launch_bounds__(kThreads, 1) void k_conv3_small(const bf16_t* __res
         for (int k = 0; k < G::WPT; ++k) {
             const int e = min(tid + k * kThreads, G::WU - 1);
             const int q = e % (CIN / 8), c = (e / (CIN / 8)) % (16 * NT), t = e / (CIN / 8 * 16 * NT);
-            wr[k] = *reinterpret_cast<const u4*>(w + (size_t)((st * TPB + t) * cout + co0 + c) * CIN + 8 * q);
+            wr[k] = *reinterpret_cast<const u4_any*>(w + (size_t)((st * TPB + t) * cout + co0 + c) * CIN + 8 * q);
         }
     };
     // channel c of group gg sits at position c ^ 2 (q mod 8), q = 8-channel
@@ -236,7 +240,7 @@ __global__ __launch_bounds__(kThreads, 1) void k_conv3_small(const bf16_t* __res
         const int q = e % (CIN / 8), v = e / (CIN / 8);  // 8 channels 8q .. of staged voxel v
         const int zz = v % G::ZP, rr = (v / G::ZP) % (TY + 2), pp = v / (G::ZP * (TY + 2));
         const int vox = (((x0 - 1 + pp) & msk) * n + ((y0 - 1 + rr) & msk)) * n + ((zz - 1) & msk);
-        const u4 r = *reinterpret_cast<const u4*>(x + (size_t)vox * CIN + 8 * q);
+        const u4 r = *reinterpret_cast<const u4_any*>(x + (size_t)vox * CIN + 8 * q);
         s4* d = tile + 2 * q * G::VP + v;
         d[0] = __builtin_bit_cast(s4, __builtin_shufflevector(r, r, 0, 1));
         d[G::VP] = __builtin_bit_cast(s4, __builtin_shufflevector(r, r, 2, 3));
@@ -407,13 +411,13 @@ __global__ __launch_bounds__(64 * NW, 2) void k_conv3_lds(const bf16_t* __restri
         for (int pp = 0; pp < kLPX + 2; ++pp) {
             const bf16_t* pl = x + (size_t)((x0 - 1 + pp) & msk) * n * n * CIN + c0;
 #pragma unroll
-            for (int q = 0; q < G::PR; ++q) v[pp][q] = *reinterpret_cast<const u4*>(pl + po[q]);
+            for (int q = 0; q < G::PR; ++q) v[pp][q] = *reinterpret_cast<const u4_any*>(pl + po[q]);
         }
 #pragma unroll
         for (int q = 0; q < G::TR; ++q)
-            vt[q] = *reinterpret_cast<const u4*>(x + (size_t)to[q] * CIN + c0 + 8 * h);
+            vt[q] = *reinterpret_cast<const u4_any*>(x + (size_t)to[q] * CIN + c0 + 8 * h);
 #pragma unroll
-        for (int q = 0; q < G::WPT; ++q) wr[q] = *reinterpret_cast<const u4*>(w + wo[q] + c0);
+        for (int q = 0; q < G::WPT; ++q) wr[q] = *reinterpret_cast<const u4_any*>(w + wo[q] + c0);
     };
     auto put = [&]() __attribute__((always_inline)) {
 #pragma unroll
@@ -572,7 +576,7 @@ __global__ __launch_bounds__(64 * kPY, 1) void k_conv3_planes(
         xp &= msk;
         const bf16_t* pl = q < G::RL ? lo + (size_t)(xp >> 1) * (n >> 1) * (n >> 1) * CLO
                                      : x + (size_t)xp * n * n * CX;
-        pre[q] = *reinterpret_cast<const u4*>(pl + src[q]);
+        pre[q] = *reinterpret_cast<const u4_any*>(pl + src[q]);
     };
     // the operand of each slice and pair of taps (k of the MFMA as in
     // k_conv3_lds; nothing in the second half of the 14th pair)
@@ -583,7 +587,7 @@ __global__ __launch_bounds__(64 * kPY, 1) void k_conv3_planes(
         for (int pr = 0; pr < 14; ++pr)
             wr[s][pr] = pr == 13 && side
                             ? u4{}
-                            : *reinterpret_cast<const u4*>(
+                            : *reinterpret_cast<const u4_any*>(
                                   w + ((2 * pr + side) * COUT + m) * CIN + 16 * s + 8 * hh);
     const f4 bb = bias4(bias, 4 * g);
 #pragma unroll
@@ -714,7 +718,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_conv3_ring(const bf16_t* __rest
     auto load = [&](int xp) __attribute__((always_inline)) {
         const bf16_t* pl = x + (size_t)(xp & msk) * plane;
 #pragma unroll
-        for (int q = 0; q < PER; ++q) pre[q] = *reinterpret_cast<const u4*>(pl + poff[q]);
+        for (int q = 0; q < PER; ++q) pre[q] = *reinterpret_cast<const u4_any*>(pl + poff[q]);
     };
     auto put = [&](int par) __attribute__((always_inline)) {
 #pragma unroll
@@ -731,7 +735,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_conv3_ring(const bf16_t* __rest
     s4 bw[27];
 #pragma unroll
     for (int t = 0; t < 27; ++t)
-        bw[t] = *reinterpret_cast<const s4*>(w + ((size_t)t * cout + 16 * cg + m) * CIN + 4 * g);
+        bw[t] = *reinterpret_cast<const s4_any*>(w + ((size_t)t * cout + 16 * cg + m) * CIN + 4 * g);
     const f4 bb = bias4(bias, 16 * cg + 4 * g);
     float wh[4] = {}, whb = 0.f;  // this lane's channels of the head, its bias
     if constexpr (HEAD) {

@@ -108,6 +108,27 @@ def test_conv_forward_staged_gradient_shapes(cin, cout, n):
     test_conv_forward_staged(cin, cout, n)
 
 
+@pytest.mark.parametrize("cin,cout,n", [(16, 16, 4), (64, 64, 4), (32, 32, 8), (128, 64, 16),
+                                        (16, 32, 32), (16, 48, 64), (64, 64, 64), (48, 16, 64)])
+@pytest.mark.parametrize("off", [1, 2, 4])
+def test_conv_unaligned_inputs(cin, cout, n, off):
+    """Inputs and weights 2, 4 and 8 bytes into their storage, on every forward
+    kernel (sides 4; 8 to 32; 64 streaming, staged and all planes): the aligned
+    call's bits."""
+    rng = np.random.default_rng(cin + cout + n)
+    x = raw(U.bf16(rng.standard_normal((n, n, n, cin)))).reshape(-1)
+    w = raw(U.bf16(rng.standard_normal((27, cout, cin)) * 0.1)).reshape(-1)
+    got = []
+    for o in (0, off):
+        xs, ws = (torch.zeros(t.numel() + 8, dtype=t.dtype, device="cuda") for t in (x, w))
+        xs[o:o + x.numel()], ws[o:o + w.numel()] = x, w
+        y = torch.empty(n ** 3 * cout, dtype=torch.float32, device="cuda")
+        assert lib().isis_conv3_fwd(P(xs[o:]), n, cin, P(ws[o:]), None, cout, 0, None, P(y),
+                                    None) == 0
+        got.append(y.cpu().numpy())
+    assert np.array_equal(got[0], got[1])
+
+
 @pytest.mark.parametrize("cin,cout,n", [(16, 16, 64), (16, 48, 64), (32, 32, 64), (64, 64, 64),
                                         (32, 96, 64), (48, 16, 64)])
 def test_conv_unaligned_outputs(cin, cout, n):
