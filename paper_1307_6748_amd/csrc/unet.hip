@@ -2183,7 +2183,8 @@ int isis_conv3_flip_weights(const float* w, int cin, int cout, uint16_t* wt, voi
     a.dst[0] = wt;
     a.cin[0] = cin;
     a.cout[0] = cout;
-    hipLaunchKernelGGL(k_conv_weights<true>, dim3(54), dim3(kThreads), 0, (hipStream_t)stream, a);
+    hipLaunchKernelGGL(k_conv_weights<true>, dim3(grid_of(27L * cin * cout)), dim3(kThreads), 0,
+                       (hipStream_t)stream, a);
     ULAUNCH("k_conv_weights");
     return ISIS_OK;
 }

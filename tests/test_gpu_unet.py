@@ -146,6 +146,17 @@ def test_conv_unaligned_outputs(cin, cout, n):
     assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
 
 
+@pytest.mark.parametrize("cin,cout", [(1, 1), (3, 100), (512, 300)])
+def test_flip_weights_of_any_shape(cin, cout):
+    """wt[t][ci][co] = bf16(w[26 - t][co][ci]), channel counts the network does
+    not have among them."""
+    w = torch.randn((27, cout, cin), generator=torch.Generator().manual_seed(cin), dtype=torch.float32)
+    wd = w.cuda()
+    wt = torch.empty((27, cin, cout), dtype=torch.bfloat16, device="cuda")
+    assert lib().isis_conv3_flip_weights(P(wd), cin, cout, P(wt), None) == 0
+    assert torch.equal(wt.cpu(), w.flip(0).transpose(1, 2).contiguous().bfloat16())
+
+
 @pytest.mark.parametrize("cin,cout", SHAPES)
 def test_conv_data_gradient(cin, cout):
     """Flipped, transposed weights turn the forward kernel into the adjoint."""
