@@ -1693,17 +1693,19 @@ int launch_conv_dw(const bf16_t* x, int n, int cin, const bf16_t* dy, int cout, 
     if (vec && n == 32) return launch_dw_tiled<DwTile<32, 8, 1>>(x, n, cin, dy, cout, 16, part, dw, s);
     if (vec && n == 16) return launch_dw_tiled<DwTile<16, 16, 1>>(x, n, cin, dy, cout, 16, part, dw, s);
     // sides below 16 (no 16-voxel windows along z) and unaligned tensors
+    // (one chunk, sides up to 16: its sum is dw)
     const int chunk = dw_chunk(nvox);
     const int nchunk = (int)(nvox / chunk);
+    float* sums = nchunk == 1 ? dw : part;
 #define DW_CASE(CI, CO)                                                                     \
     if (cin == CI && cout == CO)                                                            \
         hipLaunchKernelGGL((k_conv3_dw<CI, CO>), dim3(27 * nchunk), dim3(kThreads), 0, s, x, \
-                           n, dy, chunk, part);
+                           n, dy, chunk, sums);
     DW_CASE(16, 16) DW_CASE(16, 32) DW_CASE(32, 32) DW_CASE(32, 64) DW_CASE(64, 64)
     DW_CASE(128, 64) DW_CASE(96, 32) DW_CASE(48, 16)
 #undef DW_CASE
     ULAUNCH("k_conv3_dw");
-    return launch_sum_chunks(part, nchunk, 27L * cin * cout, dw, s);
+    return nchunk == 1 ? (int)ISIS_OK : launch_sum_chunks(part, nchunk, 27L * cin * cout, dw, s);
 }
 
 // out[c] = sum of channel c of a (C = 16, 32, 64); with o: a = a * (o > 0) first.
