@@ -185,7 +185,11 @@ typedef struct {
                                      grid, read phi + eta and write phi (8+8+8 B
                                      per cell in FP64, 4+4+4 in FP32); a pass is
                                      one sweep, or temporal_block sweeps when
-                                     blocked                                      */
+                                     blocked.  On 32^3 and 64^3 grids the last
+                                     pre-smoothing sweep's launch restricts as
+                                     well (unless by full weighting): plus the
+                                     three coarse fields it writes, 3 x (n/2)^3
+                                     values                                       */
     int temporal_block;           /* the temporal block the solve used (0..2)     */
     double rho_hist[ISIS_MG_MAX_HIST]; /* convergence factors: [k] = rel_hist[k] /
                                      rel_hist[k-1] for 1 <= k <= cycles; [0] = 0;
@@ -209,8 +213,9 @@ typedef struct {
                                      or FP32: judged_fp32)                         */
     /* Finest-level first post-smoothing pass with the prolongation
      * phi += P(phi_c - phihat_c) fused in (fused sweep kernels with a
-     * single-sweep first pass, i.e. temporal block 1; profiling on): [0] FP64,
-     * [1] FP32.  These launches are not in fine_sweep_*. */
+     * single-sweep first pass, i.e. temporal block 1, and the block sweeps of
+     * 32^3 and 64^3 grids; profiling on): [0] FP64, [1] FP32.  These launches
+     * are not in fine_sweep_*. */
     double fine_prol_ms[2];       /* summed kernel time                           */
     int fine_prol_launches[2];    /* number of kernel launches                    */
     double fine_prol_bytes[2];    /* compulsory HBM bytes: a pass's (as in

@@ -1032,10 +1032,11 @@ int vcycle_block(isis_mg* H, const M& m, LevP<T>* L, int l, double* updates, boo
     const double n3 = (double)f.n * f.n * f.n;
     constexpr int PWc = weighted_code<T, M>();
     int r;
-    // finest level, profiling on: pre- and post-smoothing timed as one step each
-    auto timed = [&](int count, auto&& body) -> int {
+    // finest level, profiling on: `count` launches timed as one step; values: per
+    // cell, what they cannot do without (a sweep reads phi and eta and writes phi)
+    auto timed = [&](int count, double values, bool prol, auto&& body) -> int {
         const int q = H->ntimed;
-        const bool on = H->profile && l == 0 && q < isis_mg::kMaxTimed;
+        const bool on = H->profile && l == 0 && count > 0 && q < isis_mg::kMaxTimed;
         if (on) HIP_TRY(H->err, hipEventRecord(H->ev0[q], H->s));
         int rr = body();
         if (rr) return rr;
@@ -1043,15 +1044,17 @@ int vcycle_block(isis_mg* H, const M& m, LevP<T>* L, int l, double* updates, boo
             HIP_TRY(H->err, hipEventRecord(H->ev1[q], H->s));
             H->tlaunch[q] = count;
             H->tupd[q] = n3 * count;
-            H->tbytes[q] = (double)count * n3 * 3.0 * sizeof(T);
+            H->tbytes[q] = values * n3 * sizeof(T);
             H->tprec[q] = sizeof(T) == 4 ? 1 : 0;
             H->tlevel[q] = l;
-            H->tprol[q] = 0;
+            H->tprol[q] = prol ? 1 : 0;
             H->ntimed = q + 1;
         }
         return ISIS_OK;
     };
-    r = timed(d.nu_pre, [&]() -> int {
+    // the last sweep's launch writes three coarse fields besides (not with full
+    // weighting, whose descent follows)
+    r = timed(d.nu_pre, 3.0 * d.nu_pre + (H->fw ? 0.0 : 3.0 / 8), false, [&]() -> int {
         for (int q = 0; q < d.nu_pre; ++q) {
             const bool first_rr = from_rr && q == 0;
             const int e = q + 1 == d.nu_pre && !H->fw
@@ -1067,15 +1070,14 @@ int vcycle_block(isis_mg* H, const M& m, LevP<T>* L, int l, double* updates, boo
                                            c.phihat, c.sigma, c.rr, H->s, H->err, f.tmp)))
         return r;
     if ((r = vcycle<T, M>(H, m, L, l + 1, updates, !H->fw))) return r;
-    r = timed(H->nu_post, [&]() -> int {
-        for (int q = 0; q < H->nu_post; ++q) {
-            int e;
-            if (q > 0)
-                e = launch_block<T, M, false, false>(H, m, f, c, false);
-            else if (PWc != 0 && H->pw)
-                e = launch_block<T, M, false, true, PWc>(H, m, f, c, false);
-            else
-                e = launch_block<T, M, false, true>(H, m, f, c, false);
+    r = timed(1, 3.0 + 2.0 / 8, true, [&]() -> int {
+        return PWc != 0 && H->pw ? launch_block<T, M, false, true, PWc>(H, m, f, c, false)
+                                 : launch_block<T, M, false, true>(H, m, f, c, false);
+    });
+    if (r) return r;
+    r = timed(H->nu_post - 1, 3.0 * (H->nu_post - 1), false, [&]() -> int {
+        for (int q = 1; q < H->nu_post; ++q) {
+            const int e = launch_block<T, M, false, false>(H, m, f, c, false);
             if (e) return e;
         }
         return (int)ISIS_OK;

@@ -231,3 +231,28 @@ def test_walk_over_coarse_planes(orc, nc):
         got = S.fas_descend(sp, a, 0.7, dev(phi), dev(eta), None, dev(eta_c), full_weighting=fw)
         assert np.max(np.abs(cubic(got[0], nc) - phi_c)) <= 2e-15
         assert np.max(np.abs(cubic(got[2], nc) - ref)) <= 1e-14 * (12.0 / 0.49 + np.abs(ref).max())
+
+
+@pytest.mark.parametrize("name,n,precision,pre,post,fw", [
+    ("symmetron_a1", 32, "fp64", 2, 1, 0), ("symmetron_a1", 64, "mixed", 2, 2, 0),
+    ("fofr", 64, "fp64", 1, 3, 0), ("chameleon", 32, "mixed", 1, 1, 1)])
+def test_profiled_launches_of_block_sweeps(name, n, precision, pre, post, fw):
+    """32^3 and 64^3 grids, profiling on: the launch that adds the coarse-grid
+    correction counts in fine_prol_*, the other sweeps in fine_sweep_*, with the
+    bytes that each cannot do without."""
+    from paper_1307_6748_amd import solver as S
+    _, sp, a = models(name)
+    s = S.Solver(n, 4.0 * n, nu_pre=pre, nu_post=post, precision=precision, restriction=fw)
+    s.set_profiling(True)
+    _, st = s.solve(dev(density(n, 7)), sp, a, 1e-9)
+    cycles = [st.cycles - st.cycles_fp32, st.cycles_fp32]
+    assert cycles[0] > 0 and (cycles[1] > 0) == (precision == "mixed")
+    for k, size in ((0, 8), (1, 4)):
+        plain = cycles[k] * (pre + post - 1)
+        coarse = 0 if fw else cycles[k] * 3 * (n // 2) ** 3
+        assert st.fine_prol_launches[k] == cycles[k]
+        assert st.fine_prol_bytes[k] == cycles[k] * (3 * n ** 3 + 2 * (n // 2) ** 3) * size
+        assert st.fine_sweep_launches[k] == plain
+        assert st.fine_sweep_updates[k] == plain * n ** 3
+        assert st.fine_sweep_bytes[k] == (plain * 3 * n ** 3 + coarse) * size
+        assert (st.fine_prol_ms[k] > 0) == (st.fine_sweep_ms[k] > 0) == (cycles[k] > 0)
