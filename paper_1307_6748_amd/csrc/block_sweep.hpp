@@ -1,4 +1,4 @@
-// One red-black Newton-Gauss-Seidel sweep of a small level (sides 32 .. 128) in
+// One red-black Newton-Gauss-Seidel sweep of a small level (sides 32 and 64) in
 // one launch, out of place, with the steps around it in the V-cycle: the FAS
 // source from the restricted defect before it, the coarse-grid correction
 // before it, or the defect and its restriction after it.
@@ -15,9 +15,10 @@
 // it does).  Per level and cycle this makes three launches (four with two
 // post-smoothing sweeps) of what were eight or ten: 1.9 to 2.5 times the
 // updates (the halo's), which the device has room for.
-// 32^3 and 64^3: 6 to 10 us per launch.  Not from 128^3 on: 55, 45 and 23 us for
-// the three launches in double precision (symmetron) against 6 half-sweeps of
-// 11.8 us with a restriction and a prolongation of 12 together.
+// 32^3 and 64^3: 6 to 11 us per launch.  Not from 128^3 on: 55, 45 and 23 us for
+// the three launches in double precision (symmetron) against 36 and 21 in fused
+// passes, 34, 24 and 18 in single precision against six half-sweeps of 9.1 us, a
+// restriction of 10 and a prolongation of 9.
 //
 // Per cell the arithmetic is that of k_halfsweep, k_fas_sigma, k_prolong_pairs
 // and k_defect_restrict_pairs, in their order.

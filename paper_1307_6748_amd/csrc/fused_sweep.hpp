@@ -571,8 +571,9 @@ inline int fused_launches(int count, int tb) { return tb >= 2 ? (count + 1) / 2 
 inline int fused_chunk(int n)
 {
     // planes streamed per workgroup: long enough to amortise the 2*H-plane
-    // pipeline fill, short enough to give >= 1024 workgroups at 512^3
-    return n >= 512 ? 64 : (n >= 256 ? 32 : 16);
+    // pipeline fill, short enough to give >= 1024 workgroups at 512^3; at 128^3
+    // a pass is one short round and takes as long as its longest chunk
+    return n >= 512 ? 64 : n >= 256 ? 32 : n == 128 ? 8 : 16;
 }
 
 // Chunks along x per tile column.  When the device holds a whole number
@@ -582,14 +583,12 @@ inline int fused_chunk(int n)
 // faster than 64-plane chunks; 256^3, 12 per tile column, FP32 f(R) 9% faster
 // than 32-plane chunks, which filled two thirds of the slots).  Otherwise, or
 // when the occupancy is unknown (resident <= 0), fused_chunk() planes per
-// chunk.  Below 256^3 the chunks may be 8 planes long (16 of them at 128^3):
-// there a pass is one short round and takes as long as its longest chunk.
+// chunk.  Below 256^3 the chunks may be 8 planes long.
 inline int fused_chunks(int n, int tiles, int resident)
 {
     if (resident > 0 && resident % tiles == 0 && resident / tiles <= 16 &&
         resident / tiles <= n / (n >= 256 ? 16 : 8))
         return resident / tiles;
-    if (n == 128) return 16;
     return n / fused_chunk(n);
 }
 

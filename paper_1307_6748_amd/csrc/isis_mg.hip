@@ -295,7 +295,11 @@ int launch_halfsweep(const M& m, int n, double h, T* phi, const T* eta, const T*
 // *phi is the buffer that holds the result.
 // Levels smaller than this (per side) use the per-colour kernels inside the
 // solver: there the streaming pipeline of the fused kernel has too few
-// workgroups to hide its per-plane latency.
+// workgroups to hide its per-plane latency.  128^3, single precision, us per
+// cycle for sweeps, descent and prolongation: f(R) 8 x 9.0 + 17 + 16 per colour,
+// 4 x 21 + 17 + 16 fused (solves of 256^3 4.81 and 4.95 ms); symmetron 6 x 9.1 +
+// 10 + 9, 44 + 20 + 10 (2.80 and 2.83).  (Where 128^3 is the finest level the
+// fused passes took 6 % off the symmetron's solve and nothing off f(R)'s.)
 constexpr int kFusedSolverMinN = 256;
 // In double precision from 128 on, in 16 chunks of planes: a pass of two sweeps
 // with the prolongation or the defect on it takes 36 us there and one sweep 21
@@ -345,8 +349,8 @@ bool prolong_fused(int n, int count, int tb, int min_fused_n = fused_solver_min<
 template <class T, class M>
 int launch_sweeps(const M& m, int n, double h, T** phi, T** tmp, const T* eta, const T* sigma,
                   int count, int tb, hipStream_t s, char* err,
-                  int min_fused_n = fused_solver_min<T>(), const T* cphi = nullptr, const T* cphat = nullptr, bool pw = false,
-                  const float* in32 = nullptr, double in_scale = 1.0, double in_offset = 0.0)
+                  int min_fused_n = fused_solver_min<T>(), const T* cphi = nullptr,
+                  const T* cphat = nullptr, bool pw = false, const float* in32 = nullptr, double in_scale = 1.0, double in_offset = 0.0)
 {
     constexpr int PWc = weighted_code<T, M>();
     if (in32) {  // the field in single precision (fused double levels only)
@@ -979,10 +983,10 @@ int launch_bottom(isis_mg* H, const M& m, LevP<T>* L, int l, double* updates, bo
 
 // Levels whose sweeps run in k_block_sweep: sides 32 and 64, unless the caller
 // asked for one launch per colour (temporal_block 0).  Below, the bottom
-// kernel.  At 128^3 the halo's work exceeds what the launches save (symmetron,
-// double precision, us per cycle: 55 + 45 + 23 in blocks against 6 x 11.8 +
-// 11 + 12 per colour; f(R), single precision: 23 + 40 + 34 + 23 against
-// 8 x 8.6 + 17 + 15).
+// kernel.  At 128^3 the halo's work exceeds what the launches save (us per cycle:
+// symmetron, double precision, 55 + 45 + 23 in blocks, 36 + 21 in fused passes,
+// 6 x 11.8 + 11 + 12 per colour; single precision 18 + 34 + 24, 44 + 20 + 10,
+// 6 x 9.1 + 10 + 9; f(R) 23 + 41 + 35 + 23, 4 x 21 + 17 + 16, 8 x 9.0 + 17 + 16).
 inline bool block_level(const isis_mg* H, int n)
 {
     return H->tb >= 1 && (n == 32 || n == 64);

@@ -17,14 +17,16 @@
 // the 14 convolutions (weights then bias) in the order above, then the head.
 //
 // Convolutions are implicit GEMMs: M = voxels, N = output channels,
-// K = 27 * input channels, on v_mfma_f32_16x16x16_bf16.  One wave owns 64
-// consecutive voxels along z (four 16-voxel M tiles) and all output channels.
-// The data gradient is the same kernel on flipped, transposed weights; the
-// weight gradient is a split-K GEMM over voxel chunks with a fixed-order
-// reduction of the partial sums (deterministic).  On sides >= 64 the input is
-// staged in LDS (k_conv3_lds; k_conv3_ring streams along x for 16 input
-// channels, k_conv3_planes for 16 output channels), and the prediction's last decoder convolution reads its
-// upsampled and skip inputs directly instead of a materialised concatenation.
+// K = 27 * input channels, on the bf16 MFMAs of 16 x 16 outputs, with the input
+// and mostly the weights staged in LDS: sides >= 64 in k_conv3_ring (16 input
+// channels, streaming along x, v_mfma_f32_16x16x16), k_conv3_planes (16 output
+// channels, streaming along x) and k_conv3_lds (the others), both on
+// v_mfma_f32_16x16x32; sides 8 to 32 in k_conv3_small and below in k_conv3, one
+// tile straight from memory, both on 16x16x16.  The data gradient is the same
+// kernels on flipped, transposed weights; the weight gradient is a split-K GEMM
+// over regions of the grid with a fixed-order reduction of the partial sums
+// (deterministic).  The prediction's last decoder stage reads its upsampled and
+// skip inputs directly instead of a materialised concatenation.
 #include <hip/hip_runtime.h>
 
 #include <atomic>
@@ -320,9 +322,8 @@ __global__ __launch_bounds__(kThreads, 1) void k_conv3_small(const bf16_t* __res
 // eleven and spilled, and the operands are read a step or three before their
 // MFMAs (the compiler's own order put the reads next to their use).  Each
 // output adds slices, taps and channels in the order of k_conv3.
-//   64 -> 64 at 64^3: 0.135 -> 0.063 ms (0.080 in the compiler's order);
-//   128 -> 64 at 64^3: 0.248 -> 0.110 ms (0.143); 64 -> 128 at 64^3: 0.296 ->
-//   0.119 ms (0.139); 96 -> 32 at 128^3: 0.72 -> 0.45 ms (0.47)
+//   64 -> 64 at 64^3: 0.138 -> 0.063 ms; 128 -> 64 at 64^3: 0.248 -> 0.109 ms;
+//   96 -> 32 at 128^3: 0.71 -> 0.44 ms
 constexpr int kLZ = 64;                            // output columns (z)
 constexpr int kLPX = 2, kLPZ = kLZ + 2;            // output planes; staged columns
 template <int NT, int NW>
@@ -516,9 +517,13 @@ __global__ __launch_bounds__(64 * NW, 2) void k_conv3_lds(const bf16_t* __restri
 // halves in phase modulo the banks: a 16-byte read serves lanes 0-3 and 12-15
 // of one with 4-11 of the other in a cycle.  Slices, pairs of taps and channels
 // are added as k_conv3_lds does, bit for bit.
-// Bound: the LDS, one kilobyte read per MFMA (97 % of 128 bytes per cycle).
+// Bound: the LDS, one kilobyte read per MFMA: at 128 bytes per cycle its
+// instructions take 91 % of the CUs' busy cycles at 128^3 (2.2 GHz; the rest is
+// mostly the prologue of four planes per workgroup) and all of them at 256^3,
+// where the clock falls to 1.7 GHz (48 -> 16, SQ_INSTS_LDS x 8 cycles over
+// SQ_BUSY_CU_CYCLES).
 // Before (two x-planes per wave, slice by slice) and with this:
-//   48 -> 16 at 128^3: 0.171 -> 0.108 ms, at 256^3 (CLO = 32) 1.24 -> 0.8 ms;
+//   48 -> 16 at 128^3: 0.171 -> 0.10 ms, at 256^3 (CLO = 32) 1.24 -> 0.8 ms;
 //   32 -> 16 at 128^3: 0.092 -> 0.063 ms
 constexpr int kPY = 4;                        // tile rows
 constexpr int kPVox = (kPY + 2) * kLPZ;       // staged voxels per plane
@@ -664,7 +669,7 @@ __global__ __launch_bounds__(64 * kPY, 1) void k_conv3_planes(
 // 16x16x16 MFMA, each 128 bytes out of phase modulo the 64 banks.
 // Bound: the MFMA issue (66 % busy at 256^3; the 16x16x16 shape runs at half
 // the rate of 16x16x32, which adds in another order).
-//   16 -> 16 at 256^3: 0.46 -> 0.39 ms; at 128^3: 0.060 -> 0.049 ms;
+//   16 -> 16 at 256^3: 0.44 -> 0.35 ms; at 128^3: 0.055 -> 0.044 ms;
 //   16 -> 48 at 128^3: 0.254 -> 0.13 ms
 constexpr int kRY = 4, kRW = 1;                    // tile rows, rows per wave
 constexpr int kRPY = kRY + 2, kRPZ = kLZ + 2;
@@ -1801,9 +1806,7 @@ Plan make_plan(int n, int training, char* base)
         if (r_ != ISIS_OK) return r_; \
     } while (0)
 
-// fuse_cat: the last decoder stage reads its upsampled and skip inputs
-// directly (prediction; training keeps the concatenation for the weight
-// gradient).
+// All convolutions' weights in bf16, FLIP: the data gradient's.
 template <bool FLIP>
 int launch_conv_weights(const float* params, bf16_t* const* dst, hipStream_t s)
 {
@@ -1821,7 +1824,8 @@ int launch_conv_weights(const float* params, bf16_t* const* dst, hipStream_t s)
 
 // predict: out and guess come from the head, which joins the last convolution
 // on sides that k_conv3_ring takes, as the last decoder stage's concatenation
-// joins its convolution; no activation is then kept for a backward pass.
+// joins its convolution; no activation is then kept for a backward pass
+// (training keeps the concatenation for the weight gradient).
 int run_forward(const Plan& P, const float* params, const double* phi_cold, float* out,
                 double* guess, bool predict, hipStream_t s)
 {
