@@ -17,9 +17,9 @@
 // per value beside the field instead of seven times per update, the defect is
 // computed once per fine cell, and the 4^3 grid lives in one wave's registers
 // (coarsest_sweeps).
-// First level 16^3, per call, before and with this: symmetron FP64 67 -> 25 us,
-// f(R) FP32 78 -> 42 and FP64 139 -> 79, chameleon FP32 70 -> 33 and FP64
-// 128 -> 62.
+// First level 16^3, per call, before and with this: symmetron FP64 67 -> 27 us,
+// f(R) FP32 78 -> 42 and FP64 139 -> 71, chameleon FP32 70 -> 34 and FP64
+// 128 -> 61.
 #pragma once
 #include <hip/hip_runtime.h>
 
